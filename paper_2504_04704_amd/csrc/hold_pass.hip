@@ -135,7 +135,10 @@ __global__ void __launch_bounds__(512, 2) hold_pass_kernel(const PassArgs a) {
   constexpr int64_t rowbytes = (int64_t)LPR * 16;
   const int64_t coff = (int64_t)cl * 16;
 
-  const int64_t stream = stream_of(blockIdx.x / a.nseg, (int64_t)a.B * a.H, a.order);
+  // the first streams * nseg workgroups score, the rest copy sink and window rows
+  const int64_t streams = (int64_t)a.B * a.H, n_score = streams * a.nseg;
+  const bool edge = blockIdx.x >= n_score;
+  const int64_t stream = edge ? (blockIdx.x - n_score) / a.edge : stream_of(blockIdx.x / a.nseg, streams, a.order);
   const int seg = blockIdx.x % a.nseg;
   const int64_t b = stream / a.H, h = stream % a.H;
   const char* kin = a.K + b * a.sb + h * a.sh;
@@ -151,18 +154,11 @@ __global__ void __launch_bounds__(512, 2) hold_pass_kernel(const PassArgs a) {
   const float inv_D = 1.0f / (float)a.D;
   const float inv_dof = 1.0f / (float)(a.D - a.ddof);
 
-  // sink rows and the sliding window (last full chunk + remainder) are plain copies
-  if (gather && seg == 0 && S > 0) {
-    copy_rows_kv<LPR>(kin, vin, a.st, kout, vout, rowbytes, S, LPR, tid, nthreads);
-    if (iout)
-      for (int i = tid; i < S; i += nthreads) iout[i] = i;
-  }
-  if (gather && seg == a.nseg - 1) {
-    const int64_t w0 = S + a.n_s * L, o0 = S + a.n_s * k, nwin = a.T - w0;
-    copy_rows_kv<LPR>(kin + w0 * a.st, vin + w0 * a.st, a.st, kout + o0 * rowbytes,
-                      vout + o0 * rowbytes, rowbytes, nwin, LPR, tid, nthreads);
-    if (iout)
-      for (int64_t i = tid; i < nwin; i += nthreads) iout[o0 + i] = (int32_t)(w0 + i);
+  if (edge) {
+    copy_edge_rows<LPR>(kin, vin, a.st, kout, vout, iout, rowbytes, S, S + a.n_s * L, S + a.n_s * k,
+                        a.T - (S + a.n_s * L), (int)((blockIdx.x - n_score) % a.edge), a.edge, LPR, tid,
+                        nthreads);
+    return;
   }
 
   const int64_t p0 = (int64_t)seg * a.n_s / a.nseg;
@@ -569,10 +565,12 @@ static hipError_t launch_hold_t(const PassArgs& a, int nsc, dim3 grid, size_t ld
                         : launch_hold_v<ET, false>(a, nsc, grid, lds, s);
 }
 
-hipError_t launch_hold_pass(const PassArgs& a, hipStream_t s) {
+hipError_t launch_hold_pass(const PassArgs& args, hipStream_t s) {
+  PassArgs a = args;
   if (!hold_supported(a.D, a.esize, a.L, a.k) || a.variant == 2) return hipErrorInvalidValue;
   const int lpr = 16, nsc = hold_nsc(a.L, lpr), R = (kHoldWaves / 2) * (kWave / lpr);
-  const int64_t nblocks = (int64_t)a.B * a.H * a.nseg;
+  a.edge = edge_parts(a, 4 * kHoldWaves * (kWave / lpr));
+  const int64_t nblocks = (int64_t)a.B * a.H * (a.nseg + a.edge);
   if (nblocks <= 0 || nblocks > 0x7fffffffLL || a.nseg < 1 || a.nseg > a.n_s) return hipErrorInvalidValue;
   // per-lane offsets inside a step are 32 bit, and so are the step offsets of the first loads
   if (a.st * (int64_t)R * kHoldSteps >= (1LL << 31)) return hipErrorInvalidValue;

@@ -136,36 +136,47 @@ int split_nw(const Norm& n) {
   return nw >= 2 ? nw : 0;
 }
 
-// Streams are cut into segments only when there are too few of them to fill the chip: the
-// target is 2 workgroups per CU (256 CUs) of 8 wavefronts, 3 of 4, 6 of 2 (measured optima;
-// every segment reads one extra chunk for its first reference), and segments keep >= 4 chunks.
-int pick_segments_split(const Norm& n, int64_t n_s, int nw) {
-  int64_t nseg;
-  if (n.hint.nseg) {
-    nseg = n.hint.nseg;
-  } else {
-    const int64_t capacity = 256 * (nw >= 8 ? 2 : nw >= 4 ? 3 : 6);
-    nseg = n.streams >= capacity ? 1 : (capacity + n.streams - 1) / n.streams;
-    const int64_t cap = n_s / 4 > 1 ? n_s / 4 : 1;
-    if (nseg > cap) nseg = cap;
+// Segments per stream.  A launch of W = streams * segments workgroups on a chip that holds `cap` of them
+// at a time takes about ceil(W / cap) rounds of one segment each, so the count that fits a whole number
+// of rounds and still cuts the longest segment down is what pays; one that spills a few workgroups into
+// one more round doubles the time (112 streams of 32K tokens at lag 1024: 560 workgroups on 512 places
+// 750 us, 448 workgroups 589 us).  A segment of c chunks costs c chunks of rows, one more that is only read
+// for the first reference, and `fixed` rows' worth of start-up and drain, plus `per_batch` rows per batch of
+// `batch` chunks.
+int pick_segments(int64_t streams, int64_t n_s, int64_t L, int64_t cap, int64_t fixed, int64_t batch,
+                  int64_t per_batch) {
+  int64_t best = 1, best_cost = INT64_MAX;
+  const int64_t base = (streams + cap - 1) / cap;  // rounds with whole streams
+  for (int64_t rounds = base; rounds < base + 8; ++rounds) {
+    int64_t nseg = rounds * cap / streams;
+    if (nseg > n_s) nseg = n_s;
+    if (nseg < 1) nseg = 1;
+    const int64_t c = (n_s + nseg - 1) / nseg;  // chunks of the longest segment
+    nseg = (n_s + c - 1) / c;                   // ... which fewer segments may share
+    const int64_t waves = (streams * nseg + cap - 1) / cap;
+    const int64_t cost = waves * ((c + 1) * L + (c + batch - 1) / batch * per_batch + fixed);
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = nseg;
+    }
   }
-  if (nseg > n_s) nseg = n_s;
-  if (nseg < 1) nseg = 1;
-  return (int)nseg;
+  return (int)best;
 }
 
-// Segments of the register-resident kernel: one workgroup per CU is resident, so streams are
-// cut only until every CU has a workgroup (measured from 8 to 1024 streams: more segments
-// never pay - every segment reads one extra chunk and runs a short last batch).
+int clamp_segments(int64_t nseg, int64_t n_s) { return (int)(nseg > n_s ? n_s : nseg < 1 ? 1 : nseg); }
+
+// Streaming kernel: its register budget lets 16 wavefronts share a CU, its LDS fewer.
+int pick_segments_split(const Norm& n, int64_t n_s, int nw) {
+  if (n.hint.nseg) return clamp_segments(n.hint.nseg, n_s);
+  int64_t per_cu = (160 * 1024) / (int64_t)split_lds_bytes(n.D, n.esize, n.L, n.k, nw);
+  if (per_cu > 16 / nw) per_cu = 16 / nw;
+  return pick_segments(n.streams, n_s, n.L, 256 * per_cu, 64, 1, 16);
+}
+
+// Register-resident kernel: one workgroup per CU, in batches of 512 rows.
 int pick_segments_hold(const Norm& n, int64_t n_s) {
-  int64_t nseg = n.hint.nseg;
-  if (!nseg) {
-    nseg = n.streams >= 256 ? 1 : (256 + n.streams - 1) / n.streams;
-    const int64_t cap = n_s / 4 > 1 ? n_s / 4 : 1;
-    if (nseg > cap) nseg = cap;
-  }
-  if (nseg > n_s) nseg = n_s;
-  return (int)(nseg < 1 ? 1 : nseg);
+  if (n.hint.nseg) return clamp_segments(n.hint.nseg, n_s);
+  return pick_segments(n.streams, n_s, n.L, 256, 128, 512 / n.L, 96);
 }
 
 // The register-resident kernel is the default wherever it applies (rows of 256 bytes, lags

@@ -35,6 +35,7 @@ struct PassArgs {
   int32_t ddof;
   int32_t variant;
   int32_t nseg;        // segments each stream is cut into (one-shot kernels)
+  int32_t edge;        // workgroups per stream that copy its sink and window rows, after all the others
   int32_t nwaves;      // wavefronts per workgroup (one-shot kernels)
   int32_t order;       // workgroup -> stream order (see stream_of)
   int32_t sel;         // selection mode (see wg_select.hpp)
@@ -61,6 +62,16 @@ __host__ __device__ inline int64_t stream_of(int64_t i, int64_t n, int order) {
     return r;
   }
   return i;
+}
+
+// Workgroups per stream for the sink and window copies (0 when only scores are asked for): one per
+// `pass` rows (what a workgroup has in flight at once) while that leaves the launch below 512 of them
+// in all, then larger shares.
+inline int edge_parts(const PassArgs& a, int64_t pass) {
+  if (!a.K_out) return 0;
+  const int64_t rows = a.S + (a.T - (a.S + a.n_s * a.L)), streams = (int64_t)a.B * a.H;
+  const int64_t want = (rows + pass - 1) / pass, most = streams >= 512 ? 1 : 512 / streams;
+  return (int)(want < most ? want : most);
 }
 
 // In-place append + recursive compression of [streams] dense caches.

@@ -201,6 +201,47 @@ __device__ __forceinline__ void copy_rows_kv(const char* __restrict__ ks, const 
   }
 }
 
+// One workgroup's share of the rows a one-shot pass keeps without scoring them: the S sink rows and
+// the sliding window (last full chunk + remainder) of one stream, K and V, with their positions.
+// `part` of `nparts` equal shares.  Four rows per thread are in flight at a time: at the head of the
+// workgroup that scores the stream's last chunks these copies were a serial chain of one memory
+// latency per 32 rows (7 us of a 28 us call on 8 streams of 8K tokens, 50 us at lag 1024), so they
+// run in workgroups of their own.
+template <int LPR>
+__device__ __forceinline__ void copy_edge_rows(const char* __restrict__ kin, const char* __restrict__ vin,
+                                               int64_t st, char* __restrict__ kout, char* __restrict__ vout,
+                                               int32_t* __restrict__ iout, int64_t rowbytes, int64_t S,
+                                               int64_t w0, int64_t o0, int64_t nwin, int part, int nparts,
+                                               int units, int tid, int nthreads) {
+  constexpr int U = 4;
+  const int64_t n = S + nwin;
+  const int64_t r0 = n * part / nparts, r1 = n * (part + 1) / nparts;
+  const int64_t coff = (tid % LPR < units ? tid % LPR : units - 1) * 16;
+  const int64_t ng = nthreads / LPR;
+  for (int64_t r = r0 + tid / LPR; r < r1; r += U * ng) {
+    uint4 a[U], b[U];
+    int64_t dst[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t v = r + u * ng < r1 ? r + u * ng : r;  // past the end: the first row again
+      const int64_t src = v < S ? v : w0 + (v - S);
+      dst[u] = v < S ? v : o0 + (v - S);
+      a[u] = ld16(kin + src * st + coff);
+      b[u] = ld16(vin + src * st + coff);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      st16(kout + dst[u] * rowbytes + coff, a[u]);
+      st16(vout + dst[u] * rowbytes + coff, b[u]);
+    }
+  }
+  if (iout)
+    for (int64_t v = r0 + tid; v < r1; v += nthreads) {
+      const int64_t src = v < S ? v : w0 + (v - S);
+      iout[v < S ? v : o0 + (v - S)] = (int32_t)src;
+    }
+}
+
 // Rows the fused kernels take: whole 16-byte slices, 48 to 512 bytes.  A row is held by
 // LPR = 4, 8, 16 or 32 consecutive lanes, 16 bytes each; when its `units` slices do not fill
 // them, the lanes left over repeat the last slice (loads and stores of the same bytes twice are

@@ -86,7 +86,10 @@ __global__ void __launch_bounds__(512, LAGKV_SPLIT_WPE) split_pass_kernel(const 
   const int64_t rowbytes = (int64_t)units * 16;
   const int64_t coff = (int64_t)clc * 16;
 
-  const int64_t stream = stream_of(blockIdx.x / a.nseg, (int64_t)a.B * a.H, a.order);
+  // the first streams * nseg workgroups score, the rest copy sink and window rows
+  const int64_t streams = (int64_t)a.B * a.H, n_score = streams * a.nseg;
+  const bool edge = blockIdx.x >= n_score;
+  const int64_t stream = edge ? (blockIdx.x - n_score) / a.edge : stream_of(blockIdx.x / a.nseg, streams, a.order);
   const int seg = blockIdx.x % a.nseg;
   const int64_t b = stream / a.H, h = stream % a.H;
   const char* kin = a.K + b * a.sb + h * a.sh;
@@ -105,18 +108,11 @@ __global__ void __launch_bounds__(512, LAGKV_SPLIT_WPE) split_pass_kernel(const 
 
   for (int i = tid; i < k; i += nthreads) list[i] = 0;
 
-  // sink rows and the sliding window (last full chunk + remainder) are plain copies
-  if (gather && seg == 0 && S > 0) {
-    copy_rows_kv<LPR>(kin, vin, a.st, kout, vout, rowbytes, S, units, tid, nthreads);
-    if (iout)
-      for (int i = tid; i < S; i += nthreads) iout[i] = i;
-  }
-  if (gather && seg == a.nseg - 1) {
-    const int64_t w0 = S + a.n_s * L, o0 = S + a.n_s * k, nwin = a.T - w0;
-    copy_rows_kv<LPR>(kin + w0 * a.st, vin + w0 * a.st, a.st, kout + o0 * rowbytes,
-                      vout + o0 * rowbytes, rowbytes, nwin, units, tid, nthreads);
-    if (iout)
-      for (int64_t i = tid; i < nwin; i += nthreads) iout[o0 + i] = (int32_t)(w0 + i);
+  if (edge) {
+    copy_edge_rows<LPR>(kin, vin, a.st, kout, vout, iout, rowbytes, S, S + a.n_s * L, S + a.n_s * k,
+                        a.T - (S + a.n_s * L), (int)((blockIdx.x - n_score) % a.edge), a.edge, units, tid,
+                        nthreads);
+    return;
   }
 
   const int64_t p0 = (int64_t)seg * a.n_s / a.nseg;
@@ -455,10 +451,13 @@ static hipError_t launch_split_t(const PassArgs& a, int lpr, bool ring, dim3 gri
   }
 }
 
-hipError_t launch_split_pass(const PassArgs& a, hipStream_t s) {
+hipError_t launch_split_pass(const PassArgs& args, hipStream_t s) {
+  PassArgs a = args;
   const int lpr = lanes_per_row(a.D, a.esize);
-  const int64_t nblocks = (int64_t)a.B * a.H * a.nseg;
-  if (lpr == 0 || nblocks <= 0 || nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (lpr == 0) return hipErrorInvalidValue;
+  a.edge = edge_parts(a, 4 * a.nwaves * (kWave / lpr));
+  const int64_t nblocks = (int64_t)a.B * a.H * (a.nseg + a.edge);
+  if (nblocks <= 0 || nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (a.nwaves != 2 && a.nwaves != 4 && a.nwaves != 8) return hipErrorInvalidValue;
   // per-lane input offsets are 32 bit: the rows of one step must lie within 2 GiB
   if (a.st * (int64_t)((a.nwaves / 2) * (kWave / lpr)) >= (1LL << 31)) return hipErrorInvalidValue;
