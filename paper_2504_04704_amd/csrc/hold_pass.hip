@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(512, 2) hold_pass_kernel(const PassArgs a) {
 
   if (edge) {
     copy_edge_rows<LPR>(kin, vin, a.st, kout, vout, iout, rowbytes, S, S + a.n_s * L, S + a.n_s * k,
-                        a.T - (S + a.n_s * L), (int)((blockIdx.x - n_score) % a.edge), a.edge, LPR, tid,
+                        a.T - (S + a.n_s * L), (int)((blockIdx.x - n_score) % a.edge), a.edge, (int)coff, tid,
                         nthreads);
     return;
   }

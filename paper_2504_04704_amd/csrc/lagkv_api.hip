@@ -123,6 +123,8 @@ bool staged_fits(const Norm& n) {
          ((size_t)n.L + n.k) * 4 <= (size_t)kMaxLdsBytes;
 }
 
+bool aligned_to(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
+
 // Wavefronts per workgroup of the tensor-split kernel (0 = its LDS need does not fit).
 // Long chunks keep eight wavefronts streaming; for short chunks the per-chunk serial part
 // (fold, selection by one wavefront, barriers) weighs more, and smaller workgroups - more of
@@ -189,8 +191,27 @@ bool use_resident(const Norm& n) {
   return n.hint.path == LAGKV_PATH_RESIDENT || n.hint.path == LAGKV_PATH_AUTO;
 }
 
+// The chunk-at-a-time kernel.  It reads a reference chunk beside every chunk and overlaps nothing but the
+// workgroups that share a CU, so it takes (a) every call whose rows or addresses are not whole 16-byte slices -
+// the walking kernels cannot, and the three-kernel path reads such rows 2 or 4 bytes at a time (64 streams of
+// 8K rows of 200 bytes: 86 us against 570 us); and (b) calls of at most two rounds of workgroups that would
+// go to the streaming kernel (32 streams of 2335 rows, lag 246: 26 us against 37 us; 40 streams of 1228
+// rows of 128 bytes, lag 128: 10 us against 16.5 us; with four rounds it is the slower one, 36 streams of 6948 rows
+// of 128 bytes 34.6 us against 33 us).  The register-resident kernel is as fast or faster at any size.
+bool use_chunk(const Norm& n, const PassArgs& a, bool whole_slices) {
+  if (n.hint.path != LAGKV_PATH_AUTO || n.hint.waves || n.hint.nseg || n.hint.order || n.hint.sel) return false;
+  if (((a.sb | a.sh | a.st) & 3) || !chunk_supported(n.D, n.esize, n.L, a.st)) return false;
+  if (!aligned_to(a.K, 4) || !aligned_to(a.V, 4) || !aligned_to(a.K_out, 4) || !aligned_to(a.V_out, 4)) return false;
+  return !whole_slices || (!use_resident(n) && n.streams * a.n_s <= 2 * 256 * chunk_places(n.D, n.esize, n.L));
+}
+int launch_chunk(PassArgs& a, const Norm& n, hipStream_t s) {
+  a.nseg = pick_segments(n.streams, a.n_s, n.L, 256 * chunk_places(n.D, n.esize, n.L), 64, 1, 32);
+  return launch_chunk_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
+}
+
 // Launch the one-shot fused kernel.
 int launch_fused_any(PassArgs& a, const Norm& n, hipStream_t s) {
+  if (use_chunk(n, a, true)) return launch_chunk(a, n, s);
   a.order = n.hint.order;
   a.sel = n.hint.sel;
   if (use_resident(n)) {
@@ -239,8 +260,6 @@ AppendWs append_ws(const Norm& n, int64_t q, int64_t rows_staged) {
 }
 
 int hip_status(hipError_t e) { return e == hipSuccess ? LAGKV_OK : LAGKV_EHIP; }
-
-bool aligned_to(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
 void fill_pass(PassArgs* a, const Norm& n, const void* K, const void* V, int64_t T,
                const lagkv_plan_t& pl, int64_t sb, int64_t sh, int64_t st) {
@@ -344,6 +363,7 @@ int lagkv_score(const lagkv_params* p, const void* K, const void* V, int64_t T, 
   if ((force == LAGKV_PATH_FUSED || force == LAGKV_PATH_RESIDENT) && !fused_ok) return LAGKV_ESHAPE;
   if (fused_ok && force != LAGKV_PATH_STAGED) return launch_fused_any(a, n, s);
   if (!staged_fits(n)) return LAGKV_ESHAPE;
+  if (use_chunk(n, a, false)) return launch_chunk(a, n, s);
   return hip_status(launch_staged_score(a, n.S, scores, s));
 }
 
@@ -427,6 +447,7 @@ int lagkv::compress_with_workspace(const lagkv_params* p, const void* K, const v
   if (!staged_fits(n)) return LAGKV_ESHAPE;
   const StagedWs w = staged_ws(n, pl.n_scored, scores_out == nullptr);
   if (!ws || ws_bytes < w.total || !aligned_to(ws, 16)) return LAGKV_EWORKSPACE;
+  if (use_chunk(n, a, false)) return launch_chunk(a, n, s);
   float* sc = scores_out ? scores_out : (float*)((char*)ws + w.off_scores);
   int32_t* kept = (int32_t*)((char*)ws + w.off_kept);
   hipError_t e = launch_staged_score(a, n.S, sc, s);

@@ -108,6 +108,14 @@ hipError_t launch_split_pass(const PassArgs& a, hipStream_t s);
 bool hold_supported(int D, int esize, int L, int k);
 hipError_t launch_hold_pass(const PassArgs& a, hipStream_t s);
 
+// One-shot chunk-at-a-time kernel: rows of 16 to 512 bytes, a multiple of 4, on 4-byte aligned addresses.
+bool chunk_supported(int D, int esize, int L, int64_t st);
+int chunk_places(int D, int esize, int L);   // workgroups a CU holds
+hipError_t launch_chunk_pass(const PassArgs& a, hipStream_t s);
+hipError_t launch_chunk_f32(const PassArgs& a, hipStream_t s);
+hipError_t launch_chunk_bf16(const PassArgs& a, hipStream_t s);
+hipError_t launch_chunk_f16(const PassArgs& a, hipStream_t s);
+
 hipError_t launch_fused_append(const AppendArgs& a, hipStream_t s);
 // Single-round decode step (exactly one chunk completes; no intermediate append copy).
 bool decode_step_supported(const AppendArgs& a);

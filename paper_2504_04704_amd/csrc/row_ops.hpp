@@ -57,6 +57,16 @@ __device__ __forceinline__ void st16(char* p, const uint4& v) {
   *reinterpret_cast<uint4*>(p) = v;
 }
 
+// 16 bytes on a 4-byte aligned address
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ uint4 ld16_a4(const char* p) {
+  const u32x4_a4 v = *reinterpret_cast<const u32x4_a4*>(p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void st16_a4(char* p, const uint4& v) {
+  *reinterpret_cast<u32x4_a4*>(p) = u32x4_a4{v.x, v.y, v.z, v.w};
+}
+
 #ifndef LAGKV_FAST_RCP
 #define LAGKV_FAST_RCP 1
 #endif
@@ -96,6 +106,26 @@ __device__ __forceinline__ float token_var(const float (&x)[VEC], const float (&
   if (!live) ss = 0.f;
   ss = group_sum<LPR>(ss);
   return ss * inv_dof;
+}
+
+// The same in a lane whose first `dead` channels belong to its neighbour (a row that is not a whole number
+// of 16-byte slices, see chunk_pass.hpp): their iv is 0, and their centred squares are left out.
+template <int LPR, int VEC>
+__device__ __forceinline__ float token_var_part(const float (&x)[VEC], const float (&mn)[VEC],
+                                                const float (&iv)[VEC], float bias, float inv_D,
+                                                float inv_dof, int dead) {
+  float s = bias;
+#pragma unroll
+  for (int j = 0; j < VEC; ++j) s = fmaf(x[j], iv[j], s);
+  s = group_sum<LPR>(s);
+  const float mean = s * inv_D;
+  float ss[2] = {0.f, 0.f};  // (two short sums: half the rounding of one long one)
+#pragma unroll
+  for (int j = 0; j < VEC; ++j) {
+    const float d = fmaf(x[j] - mn[j], iv[j], j < dead ? 0.f : -mean);
+    ss[j & 1] = fmaf(d, d, ss[j & 1]);
+  }
+  return group_sum<LPR>(ss[0] + ss[1]) * inv_dof;
 }
 
 template <int VEC>
@@ -203,20 +233,20 @@ __device__ __forceinline__ void copy_rows_kv(const char* __restrict__ ks, const 
 
 // One workgroup's share of the rows a one-shot pass keeps without scoring them: the S sink rows and
 // the sliding window (last full chunk + remainder) of one stream, K and V, with their positions.
-// `part` of `nparts` equal shares.  Four rows per thread are in flight at a time: at the head of the
+// `part` of `nparts` equal shares; `coff` is the byte the thread's slice of a row starts at (a multiple of 4
+// if A4, else of 16).  Four rows per thread are in flight at a time: at the head of the
 // workgroup that scores the stream's last chunks these copies were a serial chain of one memory
 // latency per 32 rows (7 us of a 28 us call on 8 streams of 8K tokens, 50 us at lag 1024), so they
 // run in workgroups of their own.
-template <int LPR>
+template <int LPR, bool A4 = false>
 __device__ __forceinline__ void copy_edge_rows(const char* __restrict__ kin, const char* __restrict__ vin,
                                                int64_t st, char* __restrict__ kout, char* __restrict__ vout,
                                                int32_t* __restrict__ iout, int64_t rowbytes, int64_t S,
                                                int64_t w0, int64_t o0, int64_t nwin, int part, int nparts,
-                                               int units, int tid, int nthreads) {
+                                               int coff, int tid, int nthreads) {
   constexpr int U = 4;
   const int64_t n = S + nwin;
   const int64_t r0 = n * part / nparts, r1 = n * (part + 1) / nparts;
-  const int64_t coff = (tid % LPR < units ? tid % LPR : units - 1) * 16;
   const int64_t ng = nthreads / LPR;
   for (int64_t r = r0 + tid / LPR; r < r1; r += U * ng) {
     uint4 a[U], b[U];
@@ -226,13 +256,18 @@ __device__ __forceinline__ void copy_edge_rows(const char* __restrict__ kin, con
       const int64_t v = r + u * ng < r1 ? r + u * ng : r;  // past the end: the first row again
       const int64_t src = v < S ? v : w0 + (v - S);
       dst[u] = v < S ? v : o0 + (v - S);
-      a[u] = ld16(kin + src * st + coff);
-      b[u] = ld16(vin + src * st + coff);
+      a[u] = A4 ? ld16_a4(kin + src * st + coff) : ld16(kin + src * st + coff);
+      b[u] = A4 ? ld16_a4(vin + src * st + coff) : ld16(vin + src * st + coff);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      st16(kout + dst[u] * rowbytes + coff, a[u]);
-      st16(vout + dst[u] * rowbytes + coff, b[u]);
+      if constexpr (A4) {
+        st16_a4(kout + dst[u] * rowbytes + coff, a[u]);
+        st16_a4(vout + dst[u] * rowbytes + coff, b[u]);
+      } else {
+        st16(kout + dst[u] * rowbytes + coff, a[u]);
+        st16(vout + dst[u] * rowbytes + coff, b[u]);
+      }
     }
   }
   if (iout)

@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(512, LAGKV_SPLIT_WPE) split_pass_kernel(const 
 
   if (edge) {
     copy_edge_rows<LPR>(kin, vin, a.st, kout, vout, iout, rowbytes, S, S + a.n_s * L, S + a.n_s * k,
-                        a.T - (S + a.n_s * L), (int)((blockIdx.x - n_score) % a.edge), a.edge, units, tid,
+                        a.T - (S + a.n_s * L), (int)((blockIdx.x - n_score) % a.edge), a.edge, (int)coff, tid,
                         nthreads);
     return;
   }

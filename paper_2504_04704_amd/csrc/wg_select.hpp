@@ -60,7 +60,7 @@ constexpr int kGroupSelMaxWaves = 8;
 //   key      ordered key of token `tid` (0 when tid >= L)
 //   scratch  kGroupSelWords words of LDS; the histograms must be ZERO on entry and are
 //            left dirty (the caller zeroes them before the next use, behind a barrier)
-//   list     receives the k kept positions, ascending; slotmap (optional) [L]: output slot
+//   list     (optional) receives the k kept positions, ascending; slotmap (optional) [L]: output slot
 //            of a kept token, -1 otherwise.  Visible to other wavefronts after the
 //            caller's next barrier.
 //   pos_out  (optional, global memory) [k]: receives pos0 + position of the kept tokens,
@@ -164,7 +164,7 @@ __device__ __forceinline__ void group_topk(uint32_t key, int L, int k, uint32_t*
   const uint64_t mk = __ballot(keep);
   const int slot = base + prefix_popc(mk);
   if (keep) {
-    list[slot] = (uint32_t)tid;
+    if (list) list[slot] = (uint32_t)tid;
     if (pos_out) st4_out_at(pos_out, (uint32_t)slot * 4u, pos0 + (uint32_t)tid);
   }
   if (slotmap && live) slotmap[tid] = keep ? slot : -1;
@@ -186,7 +186,9 @@ __device__ __forceinline__ void group_sel_clear(uint32_t* scratch, int tid, int 
 // kGroupSelPremax + w for w < nw, visible to every thread: the first nw/2 bound the K
 // variances, the others the V variances (any bound at least as large as every variance
 // serves: the softmax does not depend on the shift, which is only there against overflow).
-template <bool PREMAX = false>
+// FINE (eight wavefronts): the two denominators, a factor common to a whole chunk, as pairwise sums and
+// their reciprocals to half an ulp (one Newton step, two instructions) instead of the hardware's one.
+template <bool PREMAX = false, bool FINE = false>
 __device__ __forceinline__ void group_score_select(float* vK, const float* vV, int L, int k,
                                                    bool do_select, float* gout, uint32_t* scratch,
                                                    uint32_t* list, int32_t* slotmap, int tid,
@@ -249,25 +251,161 @@ __device__ __forceinline__ void group_score_select(float* vK, const float* vV, i
     float4 r[kGroupSelMaxWaves / 2];
 #pragma unroll
     for (int i = 0; i < kGroupSelMaxWaves / 2; ++i) r[i] = reinterpret_cast<const float4*>(red + 16)[i];
+    if constexpr (FINE) {  // eight partial sums, pairwise
+      static_assert(kGroupSelMaxWaves == 8, "");
+      tK = ((r[0].x + r[0].z) + (r[1].x + r[1].z)) + ((r[2].x + r[2].z) + (r[3].x + r[3].z));
+      tV = ((r[0].y + r[0].w) + (r[1].y + r[1].w)) + ((r[2].y + r[2].w) + (r[3].y + r[3].w));
+    } else {
 #pragma unroll
-    for (int i = 0; i < kGroupSelMaxWaves / 2; ++i) {  // the same order in every thread: one value for the whole chunk
-      if (2 * i < nw) {
-        tK += r[i].x;
-        tV += r[i].y;
-      }
-      if (2 * i + 1 < nw) {
-        tK += r[i].z;
-        tV += r[i].w;
+      for (int i = 0; i < kGroupSelMaxWaves / 2; ++i) {  // the same order in every thread: one value for the whole chunk
+        if (2 * i < nw) {
+          tK += r[i].x;
+          tV += r[i].y;
+        }
+        if (2 * i + 1 < nw) {
+          tK += r[i].z;
+          tV += r[i].w;
+        }
       }
     }
   }
-  const float s = eK * fast_rcp(tK) + eV * fast_rcp(tV);
+  float rK = fast_rcp(tK), rV = fast_rcp(tV);
+  if constexpr (FINE) {
+    rK = fmaf(fmaf(-tK, rK, 1.0f), rK, rK);
+    rV = fmaf(fmaf(-tV, rV, 1.0f), rV, rV);
+  }
+  const float s = eK * rK + eV * rV;
   if (live) {
     vK[tid] = s;
     // (a store the compiler does not know of, hence does not wait for at the barriers below)
     if (gout) st4_out_at(gout, (uint32_t)tid * 4u, __float_as_uint(s));
   }
   if (do_select) group_topk(live ? ordered_key(s) : 0u, L, k, scratch, list, slotmap, tid, nw, pos_out, pos0);
+}
+
+// ---- short chunks: ranks by counting ----------------------------------------------------
+// Chunk softmax, K+V sum (Eq. 10-11) and top-k for L <= 64 * E <= kRankSelMax tokens by wavefronts 0 .. 3,
+// one on each SIMD (the caller's others wait at the barriers), for callers with nothing else to hide a selection behind.  Every wavefront takes the
+// softmax by itself, so that all of them hold all scores in registers (token e * 64 + lane is element e)
+// without a barrier; a token's place is the number of larger keys, each wavefront counting against its
+// quarter of the chunk's tokens (a key at a time through a scalar register) and adding into `rank`.
+// What bounds it is instruction issue, 4 cycles each: with all eight wavefronts, two on a SIMD, the
+// shorter count did not make up for taking the softmax twice as often on each SIMD (1.65 us at L = 128).
+// The count grows with L * L: from 257 tokens on the histograms are shorter.
+//   vK, vV   channel variances, or with `raw` finished scores in vK alone (LDS, visible to all)
+//   rank     [64 * E] LDS words, ZERO on entry for tokens < L; left dirty
+//   gout     optional global destination of the scores; slotmap [L], pos_out, pos0 as for group_topk
+// The slot map is visible behind the caller's next barrier.
+constexpr int kRankSelMax = 256;
+template <int E>
+__device__ __forceinline__ void group_rank_select(const float* vK, const float* vV, bool raw, int L, int k,
+                                                  bool do_select, float* gout, uint32_t* rank,
+                                                  int32_t* slotmap, int lane, int wave, int32_t* pos_out,
+                                                  uint32_t pos0) {
+  static_assert(64 % (16 * E) == 0, "a wavefront's share of the tokens lies inside one element");
+  if (wave >= 4) {
+    if (do_select) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    return;
+  }
+  float s[E];
+  if (raw) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) s[e] = e * kWave + lane < L ? vK[e * kWave + lane] : 0.f;
+  } else {
+    float eK[E], eV[E];
+    float mK = -INFINITY, mV = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int t = e * kWave + lane;
+      eK[e] = t < L ? std_of_var(vK[t]) : -INFINITY;
+      eV[e] = t < L ? std_of_var(vV[t]) : -INFINITY;
+      mK = fmaxf(mK, eK[e]);
+      mV = fmaxf(mV, eV[e]);
+    }
+    mK = wave_max(mK);
+    mV = wave_max(mV);
+    float aK = 0.f, aV = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int t = e * kWave + lane;
+      eK[e] = t < L ? __expf(eK[e] - mK) : 0.f;
+      eV[e] = t < L ? __expf(eV[e] - mV) : 0.f;
+      aK += eK[e];
+      aV += eV[e];
+    }
+    const float rK = 1.0f / wave_sum(aK), rV = 1.0f / wave_sum(aV);
+#pragma unroll
+    for (int e = 0; e < E; ++e) s[e] = eK[e] * rK + eV[e] * rV;
+  }
+  if (gout) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int t = e * kWave + lane;
+      if (wave == e && t < L) st4_out_at(gout, (uint32_t)t * 4u, __float_as_uint(s[e]));
+    }
+  }
+  if (!do_select) return;
+  uint32_t key[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) key[e] = e * kWave + lane < L ? ordered_key(s[e]) : 0u;
+  // this wavefront's tokens: 16 * E of them, from token wave * 16 * E on
+  uint32_t mine = key[0];
+#pragma unroll
+  for (int e = 1; e < E; ++e)
+    if (wave * E / 4 == e) mine = key[e];
+  const int l0 = (wave * 16 * E) & 63;
+  uint32_t cnt[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) cnt[e] = 0;
+#pragma unroll
+  for (int i = 0; i < 16 * E; ++i) {
+    const uint32_t u = rl_u(mine, l0 + i);
+#pragma unroll
+    for (int e = 0; e < E; ++e) cnt[e] += u > key[e] ? 1u : 0u;
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int t = e * kWave + lane;
+    if (t < L) atomicAdd(&rank[t], cnt[e]);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  uint32_t rk[E];
+  uint64_t keep[E];
+  int n = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int t = e * kWave + lane;
+    rk[e] = t < L ? rank[t] : 0xffffffffu;
+    keep[e] = __ballot(rk[e] < (uint32_t)k);
+    n += __popcll(keep[e]);
+  }
+  if (n != k) {
+    // equal keys across the edge of the kept set: they share one rank, the largest below k, and
+    // are admitted from the lowest position up
+    uint32_t edge = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) edge = umax_(edge, rk[e] < (uint32_t)k ? rk[e] : 0u);
+    edge = wave_umax(edge);
+    int need = k - (int)edge;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const uint64_t eq = __ballot(rk[e] == edge);
+      keep[e] = __ballot(rk[e] < edge || (rk[e] == edge && prefix_popc(eq) < need));
+      need -= __popcll(eq);
+    }
+  }
+  int base = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int t = e * kWave + lane;
+    if (wave == e && t < L) {
+      const bool kept = (keep[e] >> lane) & 1u;
+      const int slot = base + prefix_popc(keep[e]);
+      slotmap[t] = kept ? slot : -1;
+      if (kept && pos_out) st4_out_at(pos_out, (uint32_t)slot * 4u, pos0 + (uint32_t)t);
+    }
+    base += __popcll(keep[e]);
+  }
 }
 
 // ---- chunks longer than the workgroup: EG tokens per thread ----------------------------

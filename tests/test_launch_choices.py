@@ -34,3 +34,43 @@ def test_unhinted_pass_against_oracle(case, variant):
     sc = lagkv.score(K, V, S, L, r, variant=variant)
     torch.cuda.synchronize()
     assert torch.equal(sc, lagkv.compress(K, V, S, L, r, variant=variant, want_scores=True).scores)
+
+
+# Rows that are not whole 16-byte slices, on 4-byte aligned addresses: the chunk-at-a-time kernel, against
+# the three-kernel path on the same bytes.  Row sizes at both ends of its range and around whole slices.
+PARTIAL_ROWS = [(100, torch.bfloat16), (50, torch.float16), (10, torch.bfloat16), (34, torch.bfloat16), (66, torch.float16),
+                (5, torch.float32), (33, torch.float32), (126, torch.float32), (254, torch.bfloat16), (130, torch.float16)]
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
+@pytest.mark.parametrize("D,dtype", PARTIAL_ROWS)
+def test_rows_of_partial_slices_against_the_staged_path(D, dtype, variant):
+    say("partial slices", D, dtype, "variant", variant)
+    staged = lagkv.launch_hint(lagkv.PATH_STAGED)
+    for n, (S, L, r) in enumerate([(3, 37, 0.3), (16, 128, 0.25), (0, 129, 0.5), (1, 256, 0.125), (2, 300, 0.2)]):
+        T = S + 4 * L + 11
+        K, V = gen(2, 3, T, D, dtype, seed=D + n)
+        if n % 2:  # the layout of attention kernels, the base moved by two tokens
+            K, V = (torch.cat([x[:, :, :2], x], 2).transpose(1, 2).contiguous()[:, 2:].transpose(1, 2) for x in (K, V))
+        out, _ = run_and_check(K, V, S, L, r, variant=variant, streams=[(0, 0), (1, 2)])
+        ref = lagkv.compress(K, V, S, L, r, variant=variant, want_scores=True, launch=staged)
+        torch.cuda.synchronize()
+        # two fp32 summation orders of the same sums: a few ulp of a standard deviation of order one (the bound of
+        # 2e-6 is the derivation of the scoring kernels' own)
+        assert torch.allclose(out.scores, ref.scores, rtol=4e-6, atol=0)
+        assert torch.equal(lagkv.score(K, V, S, L, r, variant=variant), out.scores)
+
+
+def test_row_strides_that_are_not_whole_slices():
+    """Rows of 128 bytes in a tensor whose row stride is 132 bytes: no longer read element by element."""
+    K, V = gen(1, 2, 700, 66, torch.bfloat16, seed=3)
+    K, V = K[..., :64], V[..., :64]
+    assert lagkv.workspace_bytes(lagkv.params_for(K, 16, 100, 0.25), 700) > 0
+    run_and_check(K, V, 16, 100, 0.25)
+    # equal tokens across the edge of the kept set, both counting ranges
+    for L in (60, 128, 250):
+        K2, V2 = K.clone(), V.clone()
+        K2[:, :, 16:16 + 2 * L] = K[:, :, 16:17]
+        V2[:, :, 16:16 + 2 * L] = V[:, :, 16:17]
+        K2[:, :, 16 + 2 * L:16 + 2 * L + 5] = K[:, :, 300:305]
+        run_and_check(K2[..., :62], V2[..., :62], 16, L, 0.3)
