@@ -518,38 +518,51 @@ int lagkv_append_and_compress(const lagkv_params* p, lagkv_cache* c, const void*
                         fused_supported(n.D, n.esize, sb, sh, st, c->K, c->V, K_new, V_new);
   if ((force == LAGKV_PATH_FUSED || force == LAGKV_PATH_RESIDENT) && !fused_ok) return LAGKV_ESHAPE;
   hipError_t e = hipSuccess;
+  AppendArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.K = (char*)c->K;
+  a.V = (char*)c->V;
+  a.pos = c->pos;
+  a.K_new = (const char*)K_new;
+  a.V_new = (const char*)V_new;
+  a.nsb = sb;
+  a.nsh = sh;
+  a.nst = st;
+  a.capacity = c->capacity;
+  a.n_static = c->n_static;
+  a.n_tail = c->n_tail;
+  a.n_seen = c->n_seen;
+  a.n_new = n_new;
+  a.rounds = q;
+  a.B = n.B;
+  a.H = n.H;
+  a.D = n.D;
+  a.S = n.S;
+  a.L = n.L;
+  a.k = n.k;
+  a.esize = n.esize;
+  a.f16 = n.f16;
+  a.ddof = n.ddof;
+  a.variant = n.variant;
+  a.sel = n.hint.sel;
+  // the kernels for 4-byte aligned rows, unless a launch is asked for
+  const bool free_launch = force == LAGKV_PATH_AUTO && n.hint.waves == 0 && n.hint.sel == 0;
+  const bool a4 = free_launch && !((sb | sh | st | n.rowbytes) & 3) && aligned_to(c->K, 4) && aligned_to(c->V, 4) &&
+                  aligned_to(K_new, 4) && aligned_to(V_new, 4);
   if (fused_ok && force != LAGKV_PATH_STAGED) {
     if (n_new > 0 || q > 0) {
-      AppendArgs a;
-      std::memset(&a, 0, sizeof(a));
-      a.K = (char*)c->K;
-      a.V = (char*)c->V;
-      a.pos = c->pos;
-      a.K_new = (const char*)K_new;
-      a.V_new = (const char*)V_new;
-      a.nsb = sb;
-      a.nsh = sh;
-      a.nst = st;
-      a.capacity = c->capacity;
-      a.n_static = c->n_static;
-      a.n_tail = c->n_tail;
-      a.n_seen = c->n_seen;
-      a.n_new = n_new;
-      a.rounds = q;
-      a.B = n.B;
-      a.H = n.H;
-      a.D = n.D;
-      a.S = n.S;
-      a.L = n.L;
-      a.k = n.k;
-      a.esize = n.esize;
-      a.f16 = n.f16;
-      a.ddof = n.ddof;
-      a.variant = n.variant;
-      a.sel = n.hint.sel;
       a.nwaves = pick_waves(n);
-      // the single-round kernel serves the steady decode step unless a launch shape is forced
-      if (n.hint.waves == 0 && decode_step_supported(a)) e = launch_decode_step(a, s);
+      // One round.  append_round_kernel asks for everything at once and is shorter per stream: lag 128, rows of
+      // 256 bytes, 256 streams 14.6 us against 19.0 us, 512 streams 20 against 27, 4096 streams 177 against 189.
+      // decode_step_kernel asks for the rows BEHIND the reference chunk before its selection and, for Eq. 16,
+      // reads values only where kept: with 110 such rows 1024 streams take it 63 us against 70 us, Eq. 16 at 2048
+      // streams 82 us against 91 us.  Up to one stream per CU neither matters.
+      const int64_t behind = tail - 2 * (int64_t)n.L;
+      const bool step = decode_step_supported(a) && n.streams > 256 &&
+                        (n.variant == LAGKV_SCORE_L2 || behind * 8 > n.L);
+      if (a4 && append_rows_supported(a)) e = launch_append_rows(a, s);
+      else if (a4 && !step && append_round_supported(a)) e = launch_append_round(a, s);
+      else if (n.hint.waves == 0 && decode_step_supported(a)) e = launch_decode_step(a, s);
       else e = launch_fused_append(a, s);
     }
   } else {
@@ -558,7 +571,12 @@ int lagkv_append_and_compress(const lagkv_params* p, lagkv_cache* c, const void*
     const AppendWs w = append_ws(n, q, rows_staged);
     if (q > 0 && (!ws || ws_bytes < w.total || !aligned_to(ws, 16))) return LAGKV_EWORKSPACE;
     const int64_t csh = c->capacity * n.rowbytes, csb = csh * n.H;
-    if (n_new > 0) {
+    const bool round = a4 && append_round_supported(a), rows = a4 && append_rows_supported(a);
+    if (round) {
+      e = launch_append_round(a, s);
+    } else if (n_new > 0 && rows) {
+      e = launch_append_rows(a, s);
+    } else if (n_new > 0) {
       e = launch_copy_rows((const char*)K_new, sb, sh, st, (char*)c->K + held * n.rowbytes, csb, csh,
                            n.rowbytes, n.B, n.H, n_new, n.rowbytes, s);
       if (e == hipSuccess)
@@ -567,7 +585,7 @@ int lagkv_append_and_compress(const lagkv_params* p, lagkv_cache* c, const void*
       if (e == hipSuccess && c->pos)
         e = launch_iota_rows(c->pos, n.streams, c->capacity, held, n_new, (int32_t)c->n_seen, s);
     }
-    if (e == hipSuccess && q > 0) {
+    if (e == hipSuccess && q > 0 && !round) {
       char* wsb = (char*)ws;
       float* sc = (float*)(wsb + w.off_scores);
       int32_t* kept = (int32_t*)(wsb + w.off_kept);

@@ -88,6 +88,7 @@ struct AppendArgs {
   int64_t n_seen;      // before the call
   int64_t n_new;
   int64_t rounds;      // chunks to compress after the append (host arithmetic)
+  int32_t n_sink;      // single-round kernel: new rows that complete the sink (n_static counts them)
   int32_t B, H, D;
   int32_t S, L, k;
   int32_t esize, f16, ddof, variant;
@@ -120,6 +121,16 @@ hipError_t launch_fused_append(const AppendArgs& a, hipStream_t s);
 // Single-round decode step (exactly one chunk completes; no intermediate append copy).
 bool decode_step_supported(const AppendArgs& a);
 hipError_t launch_decode_step(const AppendArgs& a, hipStream_t s);
+
+// The same round for the other shapes the chunk kernels take (rows on 4-byte aligned addresses).
+bool append_round_supported(const AppendArgs& a);
+hipError_t launch_append_round(const AppendArgs& a, hipStream_t s);
+hipError_t launch_round_f32(const AppendArgs& a, hipStream_t s);
+hipError_t launch_round_bf16(const AppendArgs& a, hipStream_t s);
+hipError_t launch_round_f16(const AppendArgs& a, hipStream_t s);
+// New rows behind the tail, nothing compressed.
+bool append_rows_supported(const AppendArgs& a);
+hipError_t launch_append_rows(const AppendArgs& a, hipStream_t s);
 
 // Three-kernel path (any D, any alignment).
 hipError_t launch_staged_score(const PassArgs& a, int64_t row0, float* scores, hipStream_t s);

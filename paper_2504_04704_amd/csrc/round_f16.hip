@@ -1,0 +1,8 @@
+// The single-round append kernel for one element type (a file each, so that they compile side by side).
+#include "round_pass.hpp"
+
+namespace lagkv {
+
+hipError_t launch_round_f16(const AppendArgs& a, hipStream_t s) { return launch_round_t<F16>(a, s); }
+
+}  // namespace lagkv
