@@ -9,8 +9,10 @@ missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from dataclasses import dataclass
+from operator import index
 from typing import Optional, Tuple
 
 import torch
@@ -181,21 +183,39 @@ def workspace_bytes(p: Params, T: int) -> int:
 
 
 def _stream_ptr(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    if device.type != "cuda" or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream  # (which refuses other devices)
+    return torch._C._cuda_getCurrentRawStream(device.index)  # (the raw handle: no Stream object built for it)
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-def _workspace(p: Params, T: int, device) -> Optional[torch.Tensor]:
-    n = workspace_bytes(p, T)
-    return torch.empty(n, dtype=torch.uint8, device=device) if n else None
-
-
 def _same_layout(K: torch.Tensor, V: torch.Tensor):
     if V.shape != K.shape or V.stride() != K.stride() or V.dtype != K.dtype or V.device != K.device:
         raise ValueError("K and V must share shape, strides, dtype and device")
+
+
+@functools.lru_cache(maxsize=512)
+def _prepared(shape, strides, dtype, S: int, L: int, r: float, variant: int, std_ddof: int, launch: int):
+    """What a one-shot call works out from values alone (never from a tensor's address): parameters, a
+    reference to them, the plan and the workspace size.  A serving loop repeats the same few shapes, and
+    building the structures and asking the library twice is a third of the time of a short call.  The
+    entries are only read; callers get copies of the plan."""
+    p = make_params(shape[0], shape[1], shape[3], S, L, r, _DTYPES[dtype], variant, std_ddof, strides[:3], launch)
+    T = shape[2]
+    return p, C.byref(p), plan(p, T), workspace_bytes(p, T)
+
+
+def _prepare(K: torch.Tensor, S, L, r, variant, std_ddof, launch):
+    strides = K.stride()
+    if K.dim() != 4 or strides[3] != 1:
+        raise ValueError("expected a [B,H,T,D] tensor with contiguous channels")
+    if K.dtype not in _DTYPES:
+        raise TypeError(f"unsupported dtype {K.dtype}")
+    return _prepared(K.shape, strides, K.dtype, index(S), index(L), float(r), index(variant), index(std_ddof),
+                     index(launch))
 
 
 def score(K: torch.Tensor, V: Optional[torch.Tensor], S: int, L: int, r: float, variant=SCORE_LAG,
@@ -205,11 +225,10 @@ def score(K: torch.Tensor, V: Optional[torch.Tensor], S: int, L: int, r: float, 
         raise RuntimeError("lagkv.score needs device tensors; there is no CPU path")
     if V is not None:
         _same_layout(K, V)
-    p = params_for(K, S, L, r, variant, std_ddof, launch)
+    p, ref, pl, _ = _prepare(K, S, L, r, variant, std_ddof, launch)
     T = K.shape[2]
-    pl = plan(p, T)
     out = torch.empty((p.B, p.H, pl.n_scored * L), dtype=torch.float32, device=K.device)
-    _check(load().lagkv_score(C.byref(p), K.data_ptr(), _ptr(V), T, out.data_ptr(), _ptr(ws),
+    _check(load().lagkv_score(ref, K.data_ptr(), _ptr(V), T, out.data_ptr(), _ptr(ws),
                               0 if ws is None else ws.numel(), _stream_ptr(K.device)), "lagkv_score")
     return out
 
@@ -221,12 +240,11 @@ def select(scores: torch.Tensor, T: int, S: int, L: int, r: float) -> torch.Tens
     if scores.dim() != 3 or not scores.is_contiguous() or scores.dtype != torch.float32:
         raise ValueError("scores must be a dense fp32 [B,H,n_scored*L] tensor")
     B, H, _ = scores.shape
-    p = make_params(B, H, 2, S, L, r, F32)
-    pl = plan(p, T)
+    _, ref, pl, _ = _prepared((B, H, index(T), 2), (0, 0, 0), torch.float32, index(S), index(L), float(r), SCORE_LAG, 1, 0)
     if scores.shape[2] != pl.n_scored * L:
         raise ValueError("scores do not match the partition of T")
     kept = torch.empty((B, H, pl.n_scored, pl.k), dtype=torch.int32, device=scores.device)
-    _check(load().lagkv_select(C.byref(p), scores.data_ptr(), T, kept.data_ptr(),
+    _check(load().lagkv_select(ref, scores.data_ptr(), T, kept.data_ptr(),
                                _stream_ptr(scores.device)), "lagkv_select")
     return kept
 
@@ -249,28 +267,28 @@ def compress(K: torch.Tensor, V: torch.Tensor, S: int, L: int, r: float, variant
     if not K.is_cuda:
         raise RuntimeError("lagkv.compress needs device tensors; there is no CPU path")
     _same_layout(K, V)
-    p = params_for(K, S, L, r, variant, std_ddof, launch)
+    p, ref, pl, need = _prepare(K, S, L, r, variant, std_ddof, launch)
     B, H, T, D = K.shape
-    pl = plan(p, T)
+    device = K.device
     if out is None:
-        Ko = torch.empty((B, H, pl.T_out, D), dtype=K.dtype, device=K.device)
-        Vo = torch.empty_like(Ko)
+        Ko = torch.empty((B, H, pl.T_out, D), dtype=K.dtype, device=device)
+        Vo = torch.empty((B, H, pl.T_out, D), dtype=K.dtype, device=device)
     else:
         Ko, Vo = out
         if tuple(Ko.shape) != (B, H, pl.T_out, D) or not Ko.is_contiguous() or not Vo.is_contiguous() \
                 or Vo.shape != Ko.shape or Ko.dtype != K.dtype or Vo.dtype != K.dtype:
             raise ValueError("output buffers must be dense [B,H,T_out,D] of the input dtype")
     if idx_out is None and want_idx:
-        idx_out = torch.empty((B, H, pl.T_out), dtype=torch.int32, device=K.device)
+        idx_out = torch.empty((B, H, pl.T_out), dtype=torch.int32, device=device)
     if scores_out is None and want_scores:
-        scores_out = torch.empty((B, H, pl.n_scored * L), dtype=torch.float32, device=K.device)
-    if ws is None:
-        ws = _workspace(p, T, K.device)
-    _check(load().lagkv_compress(C.byref(p), K.data_ptr(), V.data_ptr(), T, Ko.data_ptr(),
+        scores_out = torch.empty((B, H, pl.n_scored * L), dtype=torch.float32, device=device)
+    if ws is None and need:
+        ws = torch.empty(need, dtype=torch.uint8, device=device)
+    _check(load().lagkv_compress(ref, K.data_ptr(), V.data_ptr(), T, Ko.data_ptr(),
                                  Vo.data_ptr(), _ptr(idx_out), _ptr(scores_out), _ptr(ws),
-                                 0 if ws is None else ws.numel(), _stream_ptr(K.device)),
+                                 0 if ws is None else ws.numel(), _stream_ptr(device)),
            "lagkv_compress")
-    return Compressed(Ko, Vo, idx_out, scores_out, pl)
+    return Compressed(Ko, Vo, idx_out, scores_out, PlanT.from_buffer_copy(pl))
 
 
 STATIC_SCRATCH_BYTES = 16 << 20
@@ -312,6 +330,7 @@ class Cache:
             if track_positions else None
         self.c = CacheT(self.K.data_ptr(), self.V.data_ptr(), _ptr(self.pos), capacity, 0, 0, 0)
         self._ws = None
+        self._prepared = {}
 
     @classmethod
     def from_compressed(cls, comp: Compressed, T: int, capacity: int, S: int, L: int, r: float,
@@ -353,26 +372,37 @@ class Cache:
     def length(self) -> int:
         return self.c.n_static + self.c.n_tail
 
+    def _prepare(self, strides):
+        """Parameters and workspace size of a call whose new rows have these strides (0: dense).  They depend on
+        values only - the cache's own, which are part of the key, and the strides; the last few are kept."""
+        key = (strides, self.K.shape, self.K.dtype, self.S, self.L, self.r, self.variant, self.std_ddof, self.launch)
+        got = self._prepared.get(key)
+        if got is None:
+            if len(self._prepared) >= 64:
+                self._prepared = {}
+            p = self._params(strides)
+            got = self._prepared[key] = (p, C.byref(p), workspace_bytes(p, self.K.shape[2]))
+        return got
+
     def append_and_compress(self, K_new: Optional[torch.Tensor], V_new: Optional[torch.Tensor]) -> None:
-        B, H, cap, D = self.K.shape
+        K = self.K
         if K_new is None:
-            n_new, strides, dev = 0, (0, 0, 0), self.K.device
+            n_new, strides = 0, (0, 0, 0)
         else:
             _same_layout(K_new, V_new)
-            if K_new.dim() != 4 or K_new.stride(3) != 1 or K_new.shape[:2] != (B, H) \
-                    or K_new.shape[3] != D or K_new.dtype != self.K.dtype:
+            shape, have, strides = K_new.shape, K.shape, K_new.stride()
+            if len(shape) != 4 or strides[3] != 1 or shape[0] != have[0] or shape[1] != have[1] \
+                    or shape[3] != have[3] or K_new.dtype != K.dtype:
                 raise ValueError("K_new must be [B,H,n_new,D] of the cache dtype")
-            n_new = K_new.shape[2]
-            strides = (K_new.stride(0), K_new.stride(1), K_new.stride(2))
-        p = self._params(strides)
-        need = workspace_bytes(p, cap)
-        if need and (self._ws is None or self._ws.numel() < need):
-            self._ws = torch.empty(need, dtype=torch.uint8, device=self.K.device)
+            n_new, strides = shape[2], strides[:3]
+        p, ref, need = self._prepare(strides)
+        ws = self._ws
+        if need and (ws is None or ws.numel() < need):
+            ws = self._ws = torch.empty(need, dtype=torch.uint8, device=K.device)
         _check(load().lagkv_append_and_compress(
-            C.byref(p), C.byref(self.c), _ptr(K_new), _ptr(V_new), n_new, _ptr(self._ws),
-            0 if self._ws is None else self._ws.numel(), _stream_ptr(self.K.device)),
+            ref, C.byref(self.c), _ptr(K_new), _ptr(V_new), n_new, _ptr(ws),
+            0 if ws is None else ws.numel(), _stream_ptr(K.device)),
             "lagkv_append_and_compress")
-
 
     def prefill_chunked(self, K: torch.Tensor, V: torch.Tensor) -> int:
         """Chunk-by-chunk compression during prefill (Ablation, subsection on the prefill
