@@ -224,7 +224,8 @@ int lagkv_append_and_compress(const lagkv_params* p, lagkv_cache* cache, const v
  * nothing.  0 in any argument means "choose automatically" (and launch = 0 is the same as
  * lagkv_launch_hint(0, 0, 0)).
  *   path      LAGKV_PATH_AUTO (the register-resident kernel where it applies, else the
- *             streaming fused kernel, else the three-kernel path); LAGKV_PATH_FUSED (the
+ *             streaming fused kernel, else the three-kernel path; the chunk-at-a-time kernel
+ *             in place of the last two where it is faster); LAGKV_PATH_FUSED (the
  *             streaming fused kernel; error LAGKV_ESHAPE when the fused kernels do not
  *             cover the shape); LAGKV_PATH_STAGED (three-kernel path); or
  *             LAGKV_PATH_RESIDENT (the one-shot kernel that keeps a batch of rows in
@@ -259,8 +260,9 @@ int32_t lagkv_launch_hint_ex(int path, int waves, int segments, int order, int s
 /*
  * Which kernels lagkv_compress runs for these parameters (launch override included) on a
  * cache of T rows held in 16-byte aligned buffers: LAGKV_PATH_RESIDENT, LAGKV_PATH_FUSED
- * (the streaming one-shot kernel) or LAGKV_PATH_STAGED (the three-kernel path, which needs
- * the workspace); for benchmarks and profiles that have to name the kernel they time.
+ * (the streaming one-shot kernel, or for short calls the chunk-at-a-time kernel in its place)
+ * or LAGKV_PATH_STAGED (the shapes that need the workspace: the three-kernel path, or the
+ * chunk-at-a-time kernel where rows are multiples of 4 bytes); for benchmarks and profiles that have to name the kernel they time.
  * Host only.  Returns minus the lagkv_status the call itself would return for parameters
  * it rejects.
  */

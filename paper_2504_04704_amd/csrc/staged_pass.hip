@@ -2,7 +2,7 @@
 // dimension, element alignment and stride, reads every chunk twice (once as the
 // reference of its predecessor) and stages scores and kept positions in global
 // memory.  lagkv_select is always served from here; lagkv_score / lagkv_compress /
-// lagkv_append_and_compress use it for shapes the fused kernels do not cover.
+// lagkv_append_and_compress use it for shapes the fused and the chunk kernels do not cover.
 #include "lagkv_internal.hpp"
 #include "row_ops.hpp"
 #include "wave_ops.hpp"
