@@ -107,7 +107,7 @@ struct ChunkLane {
   int D, L;
   float inv_D, inv_dof;
   TStats<VEC> acc;
-  float mn[VEC], iv[VEC], bias;
+  float mn[VEC], iv[VEC];
 
   __device__ __forceinline__ void init(int D_, int L_, int ddof) {
     tid = threadIdx.x;
@@ -124,7 +124,6 @@ struct ChunkLane {
     ch0 = coff / ESIZE;
     inv_D = 1.0f / (float)D;
     inv_dof = 1.0f / (float)(D - ddof);
-    bias = 0.f;
   }
   // steps of R rows, in pairs (a step past the end repeats the chunk's last row), at most NSL
   __device__ __forceinline__ int steps() const { return ((L + R - 1) / R + 1) & ~1; }
@@ -160,12 +159,10 @@ struct ChunkLane {
   // the published statistics of the lane's channels, behind another barrier
   __device__ __forceinline__ void take_ref(const float* refbuf) {
     const float* rd = refbuf + tensor * 2 * D + ch0;
-    bias = 0.f;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
       mn[i] = rd[i];
       iv[i] = PART && i < dead ? 0.f : rd[D + i];
-      bias -= mn[i] * iv[i];
     }
   }
   // out[r] (LDS, chunk_pad(L) floats): channel variance of the lane's rows (Eq. 9-10), or minus the key
@@ -185,12 +182,9 @@ struct ChunkLane {
         if (l2) {
           v0 = -sqrtf(group_sum<LPR>(sum_squares<PART>(x0, dead)));
           v1 = -sqrtf(group_sum<LPR>(sum_squares<PART>(x1, dead)));
-        } else if constexpr (PART) {
-          v0 = token_var_part<LPR, VEC>(x0, mn, iv, bias, inv_D, inv_dof, dead);
-          v1 = token_var_part<LPR, VEC>(x1, mn, iv, bias, inv_D, inv_dof, dead);
         } else {
-          v0 = token_var<LPR, VEC>(x0, mn, iv, bias, inv_D, inv_dof);
-          v1 = token_var<LPR, VEC>(x1, mn, iv, bias, inv_D, inv_dof);
+          v0 = token_var_sub<LPR, VEC, PART>(x0, mn, iv, inv_D, inv_dof, dead);
+          v1 = token_var_sub<LPR, VEC, PART>(x1, mn, iv, inv_D, inv_dof, dead);
         }
         if (cl == 0) {
           out[j * R] = v0;

@@ -108,21 +108,25 @@ __device__ __forceinline__ float token_var(const float (&x)[VEC], const float (&
   return ss * inv_dof;
 }
 
-// The same in a lane whose first `dead` channels belong to its neighbour (a row that is not a whole number
-// of 16-byte slices, see chunk_pass.hpp): their iv is 0, and their centred squares are left out.
-template <int LPR, int VEC>
-__device__ __forceinline__ float token_var_part(const float (&x)[VEC], const float (&mn)[VEC],
-                                                const float (&iv)[VEC], float bias, float inv_D,
-                                                float inv_dof, int dead) {
-  float s = bias;
+// The same with the mean from the exactly subtracted (x - mn) as well: as many instructions, and no error that
+// grows with a channel's offset (fp32 rows at 4e6 with ranges of 8 put the seeded form 1e-4 off in a score).  For
+// the chunk kernels (chunk_ops.hpp), whose rows need not be whole 16-byte slices: the first `dead` channels of
+// the lane belong to its neighbour, their iv is 0, and their centred squares are left out.
+template <int LPR, int VEC, bool PART>
+__device__ __forceinline__ float token_var_sub(const float (&x)[VEC], const float (&mn)[VEC],
+                                               const float (&iv)[VEC], float inv_D, float inv_dof, int dead) {
+  float y[VEC], s = 0.f;
 #pragma unroll
-  for (int j = 0; j < VEC; ++j) s = fmaf(x[j], iv[j], s);
+  for (int j = 0; j < VEC; ++j) {
+    y[j] = x[j] - mn[j];
+    s = fmaf(y[j], iv[j], s);
+  }
   s = group_sum<LPR>(s);
   const float mean = s * inv_D;
   float ss[2] = {0.f, 0.f};  // (two short sums: half the rounding of one long one)
 #pragma unroll
   for (int j = 0; j < VEC; ++j) {
-    const float d = fmaf(x[j] - mn[j], iv[j], j < dead ? 0.f : -mean);
+    const float d = fmaf(y[j], iv[j], PART && j < dead ? 0.f : -mean);
     ss[j & 1] = fmaf(d, d, ss[j & 1]);
   }
   return group_sum<LPR>(ss[0] + ss[1]) * inv_dof;

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2504_04704_amd import lagkv
-from tests.test_gpu_parity import gen, run_and_check, say
+from tests.test_gpu_parity import VARIANT_NAME, gen, oracle_history_check, run_and_check, say
 
 pytestmark = pytest.mark.gpu
 
@@ -74,3 +74,21 @@ def test_row_strides_that_are_not_whole_slices():
         V2[:, :, 16:16 + 2 * L] = V[:, :, 16:17]
         K2[:, :, 16 + 2 * L:16 + 2 * L + 5] = K[:, :, 300:305]
         run_and_check(K2[..., :62], V2[..., :62], 16, L, 0.3)
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL])
+@pytest.mark.parametrize("D,L", [(50, 64), (33, 200), (50, 300), (126, 128), (48, 100)])
+def test_channel_offsets_far_above_the_ranges(D, L, variant):
+    """fp32 channels at a million times their range: x - min is exact there (the two are within a factor of two of
+    each other), so the scores are as good as anywhere, and the bar against the oracle is the same 1e-5."""
+    say("channel offsets", D, L, "variant", variant)
+    S, T = 3, 3 + 6 * L + 11
+    g = torch.Generator(device="cuda").manual_seed(D + L)
+    K, V = (4e6 * (1 + torch.rand((1, 2, 1, D), generator=g, device="cuda"))
+            + 4 * torch.randn((1, 2, T, D), generator=g, device="cuda") for _ in range(2))
+    run_and_check(K, V, S, L, 0.25, variant=variant)
+    cache = lagkv.Cache(1, 2, D, T, S, L, 0.25, dtype=torch.float32, variant=variant)
+    for a, b in [(0, S + 2 * L - 1), (S + 2 * L - 1, S + 2 * L), (S + 2 * L, S + 3 * L)]:
+        cache.append_and_compress(K[:, :, a:b], V[:, :, a:b])
+    torch.cuda.synchronize()
+    oracle_history_check(cache, K[:, :, :b], V[:, :, :b], S, L, 0.25, VARIANT_NAME[variant])
