@@ -127,7 +127,8 @@ struct ChunkLane {
   }
   // steps of R rows, in pairs (a step past the end repeats the chunk's last row), at most NSL
   __device__ __forceinline__ int steps() const { return ((L + R - 1) / R + 1) & ~1; }
-  static __device__ __forceinline__ uint4 ld(const char* p) { return PART ? ld16_a4(p) : ld16(p); }
+  // (whole rows may lie on 4-byte addresses too, by their stride or base: one instruction either way)
+  static __device__ __forceinline__ uint4 ld(const char* p) { return ld16_a4(p); }
 
   __device__ __forceinline__ void fold_pair(const uint4& q0, const uint4& q1) {
     float x0[VEC], x1[VEC];

@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(512, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const
   const bool l2 = a.variant == 2, local = a.variant == 1;
 
   if (edge) {
-    copy_edge_rows<LPR, PART>(kin, vin, a.st, kout, vout, iout, rowbytes, S, S + a.n_s * L, S + a.n_s * k,
+    copy_edge_rows<LPR, true>(kin, vin, a.st, kout, vout, iout, rowbytes, S, S + a.n_s * L, S + a.n_s * k,
                               a.T - (S + a.n_s * L), (int)((blockIdx.x - n_score) % a.edge), a.edge, coff, tid,
                               kChunkWaves * kWave);
     return;

@@ -237,8 +237,8 @@ __device__ __forceinline__ void copy_rows_kv(const char* __restrict__ ks, const 
 
 // One workgroup's share of the rows a one-shot pass keeps without scoring them: the S sink rows and
 // the sliding window (last full chunk + remainder) of one stream, K and V, with their positions.
-// `part` of `nparts` equal shares; `coff` is the byte the thread's slice of a row starts at (a multiple of 4
-// if A4, else of 16).  Four rows per thread are in flight at a time: at the head of the
+// `part` of `nparts` equal shares; `coff` is the byte the thread's slice of a row starts at; rows
+// and outputs lie on 4-byte addresses if A4, else on 16-byte ones.  Four rows per thread are in flight at a time: at the head of the
 // workgroup that scores the stream's last chunks these copies were a serial chain of one memory
 // latency per 32 rows (7 us of a 28 us call on 8 streams of 8K tokens, 50 us at lag 1024), so they
 // run in workgroups of their own.

@@ -92,3 +92,33 @@ def test_channel_offsets_far_above_the_ranges(D, L, variant):
         cache.append_and_compress(K[:, :, a:b], V[:, :, a:b])
     torch.cuda.synchronize()
     oracle_history_check(cache, K[:, :, :b], V[:, :, :b], S, L, 0.25, VARIANT_NAME[variant])
+
+
+def on_odd_addresses(x, pad, shift):
+    """The same values with `pad` more channels from row to row, `shift` channels into the allocation."""
+    B, H, T, D = x.shape
+    flat = torch.full((B * H * T * (D + pad) + shift,), 7, dtype=x.dtype, device=x.device)
+    view = flat[shift:].as_strided((B, H, T, D), (H * T * (D + pad), T * (D + pad), D + pad, 1), shift)
+    view.copy_(x)
+    return view
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
+@pytest.mark.parametrize("D,dtype", [(32, torch.bfloat16), (64, torch.float16), (32, torch.float32), (128, torch.bfloat16), (256, torch.bfloat16)])
+def test_whole_rows_on_four_byte_addresses(D, dtype, variant):
+    """Rows of 64, 128, 256 and 512 bytes that start on any multiple of 4: one-shot and as the new rows of a cache."""
+    step = 4 // dtype.itemsize
+    for L, pad, shift in [(64, step, 0), (128, 3 * step, step), (130, 2 * step, 3 * step), (300, step, 2 * step)]:
+        say("four-byte addresses", D, dtype, "variant", variant, "L", L, "pad", pad, "shift", shift)
+        S, T = 5, 5 + 4 * L + 9
+        K0, V0 = gen(1, 3, T, D, dtype, seed=D + L)
+        K, V = on_odd_addresses(K0, pad, shift), on_odd_addresses(V0, pad, shift)
+        assert K.data_ptr() % 16 == 4 * (shift // step) and torch.equal(K, K0)
+        out, _ = run_and_check(K, V, S, L, 0.3, variant=variant)
+        want = lagkv.compress(K0, V0, S, L, 0.3, variant=variant)
+        cache = lagkv.Cache(1, 3, D, T, S, L, 0.3, dtype=dtype, variant=variant)
+        for a, b in [(0, S + 2 * L - 1), (S + 2 * L - 1, S + 2 * L), (S + 2 * L, T - L), (T - L, T)]:
+            cache.append_and_compress(K[:, :, a:b], V[:, :, a:b])
+        torch.cuda.synchronize()
+        oracle_history_check(cache, K, V, S, L, 0.3, VARIANT_NAME[variant])
+        assert torch.equal(out.K, want.K) and torch.equal(out.V, want.V) and torch.equal(out.idx, want.idx)
