@@ -16,6 +16,7 @@
 namespace lagkv {
 
 constexpr int kChunkWaves = 8;
+static_assert(kChunkWaves * kWave == kChunkThreads, "");
 
 struct ChunkLds {
   int off_vK, off_vV, off_slot, off_rank, off_sel, off_stat, off_ref, total;  // bytes

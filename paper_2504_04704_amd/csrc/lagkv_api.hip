@@ -198,31 +198,62 @@ bool use_resident(const Norm& n) {
 // go to the streaming kernel (32 streams of 2335 rows, lag 246: 26 us against 37 us; 40 streams of 1228
 // rows of 128 bytes, lag 128: 10 us against 16.5 us; with four rounds it is the slower one, 36 streams of 6948 rows
 // of 128 bytes 34.6 us against 33 us).  The register-resident kernel is as fast or faster at any size.
-bool use_chunk(const Norm& n, const PassArgs& a, bool whole_slices) {
+// Sets a.nseg where it says yes.
+bool use_chunk(const Norm& n, PassArgs& a, bool whole_slices) {
   if (n.hint.path != LAGKV_PATH_AUTO || n.hint.waves || n.hint.nseg || n.hint.order || n.hint.sel) return false;
   if (((a.sb | a.sh | a.st) & 3) || !chunk_supported(n.D, n.esize, n.L, a.st)) return false;
   if (!aligned_to(a.K, 4) || !aligned_to(a.V, 4) || !aligned_to(a.K_out, 4) || !aligned_to(a.V_out, 4)) return false;
-  return !whole_slices || (!use_resident(n) && n.streams * a.n_s <= 2 * 256 * chunk_places(n.D, n.esize, n.L));
+  const int64_t places = 256 * chunk_places(n.D, n.esize, n.L);
+  if (whole_slices && (use_resident(n) || n.streams * a.n_s > 2 * places)) return false;
+  const int nseg = pick_segments(n.streams, a.n_s, n.L, places, 64, 1, 32);
+  // its workgroups are twice the three-kernel path's
+  if (!grid_fits(n.streams * nseg + most_edge_workgroups(a), kChunkThreads)) return false;
+  a.nseg = nseg;
+  return true;
 }
-int launch_chunk(PassArgs& a, const Norm& n, hipStream_t s) {
-  a.nseg = pick_segments(n.streams, a.n_s, n.L, 256 * chunk_places(n.D, n.esize, n.L), 64, 1, 32);
-  return launch_chunk_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
+int launch_chunk(PassArgs& a, hipStream_t s) { return launch_chunk_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP; }
+
+// `launch` on the streams of `a`, in one launch unless the workgroups that copy sink and window rows (one per
+// stream at such counts) take it past the limit of a grid: then in as few ranges of streams as fit.
+template <typename F>
+int launch_in_parts(const PassArgs& a, int threads, F launch, hipStream_t s) {
+  const int64_t streams = (int64_t)a.B * a.H, score = streams * a.nseg;
+  if (grid_fits(score + most_edge_workgroups(a), threads) || !grid_fits(score, threads))
+    return launch(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
+  const int64_t most = (kMaxGridItems - 1) / threads / (a.nseg + 1), rowbytes = (int64_t)a.D * a.esize;
+  // a range is whole batches, or heads of one batch
+  const int64_t nb = a.H <= most ? most / a.H : 1, nh = a.H <= most ? a.H : most;
+  for (int64_t b = 0; b < a.B; b += nb)
+    for (int64_t h = 0; h < a.H; h += nh) {
+      const int64_t at = b * a.H + h;
+      PassArgs p = a;
+      p.B = (int32_t)(a.B - b < nb ? a.B - b : nb);
+      p.H = (int32_t)(a.H - h < nh ? a.H - h : nh);
+      p.K += b * a.sb + h * a.sh;
+      p.V += b * a.sb + h * a.sh;
+      p.K_out += at * a.T_out * rowbytes;
+      p.V_out += at * a.T_out * rowbytes;
+      if (a.idx_out) p.idx_out += at * a.T_out;
+      if (a.scores) p.scores += at * a.n_s * a.L;
+      if (launch(p, s) != hipSuccess) return LAGKV_EHIP;
+    }
+  return LAGKV_OK;
 }
 
 // Launch the one-shot fused kernel.
 int launch_fused_any(PassArgs& a, const Norm& n, hipStream_t s) {
-  if (use_chunk(n, a, true)) return launch_chunk(a, n, s);
+  if (use_chunk(n, a, true)) return launch_chunk(a, s);
   a.order = n.hint.order;
   a.sel = n.hint.sel;
   if (use_resident(n)) {
     a.nwaves = 8;
     a.nseg = pick_segments_hold(n, a.n_s);
-    return launch_hold_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
+    return launch_in_parts(a, 64 * a.nwaves, launch_hold_pass, s);
   }
   if (n.hint.path == LAGKV_PATH_RESIDENT) return LAGKV_ESHAPE;
   a.nwaves = split_nw(n);
   a.nseg = pick_segments_split(n, a.n_s, a.nwaves);
-  return launch_split_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
+  return launch_in_parts(a, 64 * a.nwaves, launch_split_pass, s);
 }
 
 // Workspace of the three-kernel path for one pass: [scores][kept]
@@ -363,7 +394,7 @@ int lagkv_score(const lagkv_params* p, const void* K, const void* V, int64_t T, 
   if ((force == LAGKV_PATH_FUSED || force == LAGKV_PATH_RESIDENT) && !fused_ok) return LAGKV_ESHAPE;
   if (fused_ok && force != LAGKV_PATH_STAGED) return launch_fused_any(a, n, s);
   if (!staged_fits(n)) return LAGKV_ESHAPE;
-  if (use_chunk(n, a, false)) return launch_chunk(a, n, s);
+  if (use_chunk(n, a, false)) return launch_chunk(a, s);
   return hip_status(launch_staged_score(a, n.S, scores, s));
 }
 
@@ -447,7 +478,7 @@ int lagkv::compress_with_workspace(const lagkv_params* p, const void* K, const v
   if (!staged_fits(n)) return LAGKV_ESHAPE;
   const StagedWs w = staged_ws(n, pl.n_scored, scores_out == nullptr);
   if (!ws || ws_bytes < w.total || !aligned_to(ws, 16)) return LAGKV_EWORKSPACE;
-  if (use_chunk(n, a, false)) return launch_chunk(a, n, s);
+  if (use_chunk(n, a, false)) return launch_chunk(a, s);
   float* sc = scores_out ? scores_out : (float*)((char*)ws + w.off_scores);
   int32_t* kept = (int32_t*)((char*)ws + w.off_kept);
   hipError_t e = launch_staged_score(a, n.S, sc, s);

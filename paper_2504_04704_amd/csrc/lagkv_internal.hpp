@@ -74,6 +74,16 @@ inline int edge_parts(const PassArgs& a, int64_t pass) {
   return (int)(want < most ? want : most);
 }
 
+// ... and no more than these in all.
+inline int64_t most_edge_workgroups(const PassArgs& a) {
+  const int64_t streams = (int64_t)a.B * a.H;
+  return !a.K_out ? 0 : streams < 512 ? 512 : streams;
+}
+
+// HIP takes fewer than 2^32 work items in a dimension of a grid.
+constexpr int64_t kMaxGridItems = 1LL << 32;
+inline bool grid_fits(int64_t blocks, int64_t threads) { return blocks < kMaxGridItems / threads; }
+
 // In-place append + recursive compression of [streams] dense caches.
 struct AppendArgs {
   char* K;             // [streams, capacity, D]
@@ -110,6 +120,7 @@ bool hold_supported(int D, int esize, int L, int k);
 hipError_t launch_hold_pass(const PassArgs& a, hipStream_t s);
 
 // One-shot chunk-at-a-time kernel: rows of 16 to 512 bytes, a multiple of 4, on 4-byte aligned addresses.
+constexpr int kChunkThreads = 512;           // of the chunk kernels
 bool chunk_supported(int D, int esize, int L, int64_t st);
 int chunk_places(int D, int esize, int L);   // workgroups a CU holds
 hipError_t launch_chunk_pass(const PassArgs& a, hipStream_t s);

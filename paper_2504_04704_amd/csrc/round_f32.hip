@@ -52,7 +52,7 @@ bool append_round_supported(const AppendArgs& a) {
   if (a.rounds != 1 || !chunk_supported(a.D, a.esize, a.L, (int64_t)a.D * a.esize)) return false;
   // a sink that is still filling has no tail behind it
   if (a.n_seen < a.S && (a.n_tail != 0 || a.n_static != a.n_seen)) return false;
-  return round_lds_bytes(a.D, a.L) <= kMaxLdsBytes;
+  return round_lds_bytes(a.D, a.L) <= kMaxLdsBytes && grid_fits((int64_t)a.B * a.H, kChunkThreads);
 }
 
 hipError_t launch_append_round(const AppendArgs& args, hipStream_t s) {
