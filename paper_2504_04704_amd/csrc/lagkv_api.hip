@@ -118,6 +118,11 @@ bool fused_fits(const Norm& n) {
          fused_lds_bytes(n.D, n.L, n.k, 1) <= (size_t)kMaxLdsBytes;
 }
 
+// lagkv_workspace_bytes, which does not see addresses, answers 0 for these.
+bool told_none(const Norm& n, int64_t sb, int64_t sh, int64_t st) {
+  return n.hint.path != LAGKV_PATH_STAGED && shape_fused(n, sb, sh, st) && fused_fits(n);
+}
+
 bool staged_fits(const Norm& n) {
   return staged_score_lds_bytes(n.D, n.L) <= (size_t)kMaxLdsBytes &&
          ((size_t)n.L + n.k) * 4 <= (size_t)kMaxLdsBytes;
@@ -357,8 +362,7 @@ size_t lagkv_workspace_bytes(const lagkv_params* p, int64_t T) {
   if (validate(p, &n) != LAGKV_OK || T < 1 || T > kMaxRows) return 0;
   int64_t sb, sh, st;
   if (strides_of(p, n, T, &sb, &sh, &st) != LAGKV_OK) return 0;
-  const bool fused = n.hint.path != LAGKV_PATH_STAGED && shape_fused(n, sb, sh, st) && fused_fits(n);
-  if (fused) return 0;
+  if (told_none(n, sb, sh, st)) return 0;
   // one pass over T rows, and an append into a cache of capacity T
   lagkv_plan_t pl;
   plan_of(n, T, n.S, &pl);
@@ -429,7 +433,7 @@ size_t lagkv::compress_workspace_need(const lagkv_params* p, int64_t T) {
   if (validate(p, &n) != LAGKV_OK || T < 1 || T > kMaxRows) return 0;
   int64_t sb, sh, st;
   if (strides_of(p, n, T, &sb, &sh, &st) != LAGKV_OK) return 0;
-  if (n.hint.path != LAGKV_PATH_STAGED && shape_fused(n, sb, sh, st) && fused_fits(n)) return 0;
+  if (told_none(n, sb, sh, st)) return 0;
   lagkv_plan_t pl;
   plan_of(n, T, n.S, &pl);
   return pl.n_scored > 0 ? staged_ws(n, pl.n_scored, true).total : 0;
@@ -477,8 +481,10 @@ int lagkv::compress_with_workspace(const lagkv_params* p, const void* K, const v
   if (fused_ok && force != LAGKV_PATH_STAGED) return launch_fused_any(a, n, s);
   if (!staged_fits(n)) return LAGKV_ESHAPE;
   const StagedWs w = staged_ws(n, pl.n_scored, scores_out == nullptr);
-  if (!ws || ws_bytes < w.total || !aligned_to(ws, 16)) return LAGKV_EWORKSPACE;
-  if (use_chunk(n, a, false)) return launch_chunk(a, s);
+  const bool chunk = use_chunk(n, a, false);
+  if (!(chunk && told_none(n, sb, sh, st)) && (!ws || ws_bytes < w.total || !aligned_to(ws, 16)))
+    return LAGKV_EWORKSPACE;
+  if (chunk) return launch_chunk(a, s);
   float* sc = scores_out ? scores_out : (float*)((char*)ws + w.off_scores);
   int32_t* kept = (int32_t*)((char*)ws + w.off_kept);
   hipError_t e = launch_staged_score(a, n.S, sc, s);
@@ -600,9 +606,10 @@ int lagkv_append_and_compress(const lagkv_params* p, lagkv_cache* c, const void*
     if (!staged_fits(n)) return LAGKV_ESHAPE;
     const int64_t rows_staged = q > 0 ? q * n.k + (tail - q * n.L) : 0;
     const AppendWs w = append_ws(n, q, rows_staged);
-    if (q > 0 && (!ws || ws_bytes < w.total || !aligned_to(ws, 16))) return LAGKV_EWORKSPACE;
-    const int64_t csh = c->capacity * n.rowbytes, csb = csh * n.H;
     const bool round = a4 && append_round_supported(a), rows = a4 && append_rows_supported(a);
+    if (q > 0 && !(round && told_none(n, sb, sh, st)) && (!ws || ws_bytes < w.total || !aligned_to(ws, 16)))
+      return LAGKV_EWORKSPACE;
+    const int64_t csh = c->capacity * n.rowbytes, csb = csh * n.H;
     if (round) {
       e = launch_append_round(a, s);
     } else if (n_new > 0 && rows) {

@@ -122,3 +122,25 @@ def test_whole_rows_on_four_byte_addresses(D, dtype, variant):
         torch.cuda.synchronize()
         oracle_history_check(cache, K, V, S, L, 0.3, VARIANT_NAME[variant])
         assert torch.equal(out.K, want.K) and torch.equal(out.V, want.V) and torch.equal(out.idx, want.idx)
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
+@pytest.mark.parametrize("D,dtype,pad,shift", [(128, torch.bfloat16, 0, 2), (128, torch.bfloat16, 8, 6), (96, torch.float16, 0, 4), (64, torch.float32, 4, 3)])
+def test_whole_strides_on_a_four_byte_base_need_no_workspace(D, dtype, pad, shift, variant):
+    """lagkv_workspace_bytes, which sees no addresses, answers 0: the pass, and a cache's rows up to and over the one that
+    completes a chunk, take tensors (the cache's own among them) that start 4, 8 or 12 bytes into a slice."""
+    say("four-byte base", D, dtype, pad, shift, "variant", variant)
+    S, L = 5, 100
+    T = S + 4 * L + 9
+    K, V = (on_odd_addresses(x, pad, shift) for x in gen(2, 3, T, D, dtype, seed=D + shift))
+    assert K.data_ptr() % 16 != 0 and lagkv.workspace_bytes(lagkv.params_for(K, S, L, 0.3, variant), T) == 0
+    run_and_check(K, V, S, L, 0.3, variant=variant)
+    for odd_cache in (False, True):
+        cache = lagkv.Cache(2, 3, D, T, S, L, 0.3, dtype=dtype, variant=variant)
+        if odd_cache:
+            cache.K, cache.V = (on_odd_addresses(x, 0, shift) for x in (cache.K, cache.V))
+            cache.c.K, cache.c.V = cache.K.data_ptr(), cache.V.data_ptr()
+        for a, b in [(0, S + 2 * L - 1), (S + 2 * L - 1, S + 2 * L), (S + 2 * L, S + 3 * L - 1), (S + 3 * L - 1, S + 4 * L - 2)]:
+            cache.append_and_compress(K[:, :, a:b], V[:, :, a:b])
+        torch.cuda.synchronize()
+        oracle_history_check(cache, K[:, :, :b], V[:, :, :b], S, L, 0.3, VARIANT_NAME[variant])
