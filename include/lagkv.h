@@ -103,7 +103,8 @@ int lagkv_keep_for_compression(int64_t T, int32_t S, int32_t L, double C, int64_
  * bound that holds for any single append).  0 when the fused kernels serve the shape: rows
  * of 48 to 512 bytes that are a multiple of 16 bytes, strides that are multiples of 16
  * bytes, a lag that fits the LDS budget.  The three-kernel path used for every other shape stages scores and kept
- * positions there.  The answer assumes 16-byte aligned K / V / output / cache pointers (any
+ * positions there, and for an append the rows it moves; where this is not 0, lagkv_compress alone needs
+ * 4*B*H*n_scored*L and 4*B*H*n_scored*k bytes, each rounded up to a multiple of 256.  The answer assumes 16-byte aligned K / V / output / cache pointers (any
  * hipMalloc'ed buffer is), or where it is 0 4-byte aligned ones for lags of up to 512 (one
  * round of an append); a caller whose pointers are only element-aligned must ask, and
  * call, with a launch hint of LAGKV_PATH_STAGED.  Returns 0 on invalid parameters as well.

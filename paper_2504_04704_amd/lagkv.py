@@ -205,7 +205,16 @@ def _prepared(shape, strides, dtype, S: int, L: int, r: float, variant: int, std
     entries are only read; callers get copies of the plan."""
     p = make_params(shape[0], shape[1], shape[3], S, L, r, _DTYPES[dtype], variant, std_ddof, strides[:3], launch)
     T = shape[2]
-    return p, C.byref(p), plan(p, T), workspace_bytes(p, T)
+    pl = plan(p, T)
+    return p, C.byref(p), pl, _compress_bytes(p, T, pl)
+
+
+def _compress_bytes(p: Params, T: int, pl: PlanT) -> int:
+    """Workspace of one lagkv_compress call (see lagkv_workspace_bytes in include/lagkv.h): its scores and kept
+    positions, without the two staged copies of a whole cache that an append may need."""
+    if workspace_bytes(p, T) == 0:
+        return 0
+    return sum((4 * p.B * p.H * pl.n_scored * n + 255) // 256 * 256 for n in (p.L, pl.k))
 
 
 def _prepare(K: torch.Tensor, S, L, r, variant, std_ddof, launch):

@@ -77,3 +77,28 @@ def test_static_scratch_rejects_sizes_beyond_its_limit():
     rc = lib.lagkv_compress_static(C.byref(p), fake, fake, T, fake, fake, None, None, None)
     assert rc == lagkv.EWORKSPACE
     assert "workspace" in lagkv.strerror(rc)
+
+
+@pytest.mark.parametrize("D,L,launch", [(100, 64, 0), (100, 700, 0), (41, 50, 0), (128, 128, lagkv.PATH_STAGED)])
+def test_one_pass_takes_a_workspace_for_itself_alone(D, L, launch):
+    """The binding's workspace of a compress call is what the library demands of one, to the byte, and not the size
+    for an append into a cache of that length."""
+    K, V = _gen(2, 3, 16 + 5 * L + 9, D, torch.bfloat16, seed=D)
+    T, launch = K.shape[2], lagkv.launch_hint(launch) if launch else 0
+    p, _, pl, need = lagkv._prepare(K, 16, L, 0.3, lagkv.SCORE_LAG, 1, launch)
+    assert 0 < need < lagkv.workspace_bytes(p, T)
+    want = lagkv.compress(K, V, 16, L, 0.3, launch=launch)
+    ws = torch.full((need + 4096,), 0x5a, dtype=torch.uint8, device=DEV)
+    got = lagkv.compress(K, V, 16, L, 0.3, ws=ws[:need], launch=launch)
+    torch.cuda.synchronize()
+    assert torch.equal(got.idx, want.idx) and torch.equal(got.K, want.K) and bool((ws[need:] == 0x5a).all())
+    with pytest.raises(lagkv.LagKVError) as e:
+        lagkv.compress(K, V, 16, L, 0.3, ws=ws[:need - 1], launch=launch)
+    assert e.value.status == lagkv.EWORKSPACE
+    # (the caching allocator's peak: both outputs, positions and the workspace)
+    free = torch.cuda.memory_allocated()
+    torch.cuda.reset_peak_memory_stats()
+    lagkv.compress(K, V, 16, L, 0.3, launch=launch)
+    rounded = sum((x + 511) // 512 * 512 for x in (need, K.element_size() * K[:, :, :pl.T_out].numel(),
+                                                   K.element_size() * K[:, :, :pl.T_out].numel(), 24 * pl.T_out))
+    assert torch.cuda.max_memory_allocated() - free <= rounded
