@@ -261,6 +261,28 @@ int launch_fused_any(PassArgs& a, const Norm& n, hipStream_t s) {
   return launch_in_parts(a, 64 * a.nwaves, launch_split_pass, s);
 }
 
+// A single round of whole-slice rows: append_round_kernel, or (where it says no) decode_step_kernel if the shape
+// is one of its own, else fused_append_kernel.  The first asks for everything at once and is the shortest per
+// stream; with more than 8 row slices a lane its registers leave room for one workgroup per CU, where the others
+// keep two and more.  Gains below are time of the others over its time, cache kernels alone.
+bool round_is_faster(const Norm& n, const AppendArgs& a, int64_t tail) {
+  if (!append_round_supported(a)) return false;
+  const int slices = append_round_slices(n.D, n.esize, n.L);
+  // up to one workgroup per CU: 1.1 to 1.8 (64, 128, 256 streams) at any number of slices up to 16; beyond 16, where
+  // the reference rows are read twice, 256 streams of Eq. 7-8 0.83 to 0.98 and 128 streams 1.0 to 1.2
+  if (n.streams <= (slices <= 16 || n.variant == LAGKV_SCORE_LOCAL ? 256 : 128)) return true;
+  const bool step = decode_step_supported(a);
+  // 8 slices: Eq. 14-15 1.14 to 1.86.  decode_step_kernel asks for the rows BEHIND the reference chunk before its
+  // selection and, for Eq. 16, reads values only where kept: lag 128, rows of 256 bytes, 110 such rows, 1024
+  // streams 63 us against 70 us, Eq. 16 at 2048 streams 82 us against 91 us; with fewer rows behind 1.0 to 1.4
+  if (slices <= 8) return !step || (n.variant != LAGKV_SCORE_L2 && (tail - 2 * (int64_t)n.L) * 8 <= n.L);
+  // 16 slices: against decode_step_kernel 0.70 to 0.94 (rows of 160 bytes, lag 200; 192 and 160; 80 and 300);
+  // against fused_append_kernel from 512 streams on 0.99 to 1.20 where three quarters of the slices hold
+  // rows (256 bytes, lag 256; 512 and 100; 128 and 500), 0.84 to 1.10 below that and below 512 streams, Eq. 16
+  // 0.77 to 1.09
+  return !step && slices <= 16 && n.variant != LAGKV_SCORE_L2 && n.streams >= 512 && n.rowbytes * n.L >= 48 * 1024;
+}
+
 // Workspace of the three-kernel path for one pass: [scores][kept]
 struct StagedWs {
   size_t off_scores, off_kept, total;
@@ -589,16 +611,8 @@ int lagkv_append_and_compress(const lagkv_params* p, lagkv_cache* c, const void*
   if (fused_ok && force != LAGKV_PATH_STAGED) {
     if (n_new > 0 || q > 0) {
       a.nwaves = pick_waves(n);
-      // One round.  append_round_kernel asks for everything at once and is shorter per stream: lag 128, rows of
-      // 256 bytes, 256 streams 14.6 us against 19.0 us, 512 streams 20 against 27, 4096 streams 177 against 189.
-      // decode_step_kernel asks for the rows BEHIND the reference chunk before its selection and, for Eq. 16,
-      // reads values only where kept: with 110 such rows 1024 streams take it 63 us against 70 us, Eq. 16 at 2048
-      // streams 82 us against 91 us.  Up to one stream per CU neither matters.
-      const int64_t behind = tail - 2 * (int64_t)n.L;
-      const bool step = decode_step_supported(a) && n.streams > 256 &&
-                        (n.variant == LAGKV_SCORE_L2 || behind * 8 > n.L);
       if (a4 && append_rows_supported(a)) e = launch_append_rows(a, s);
-      else if (a4 && !step && append_round_supported(a)) e = launch_append_round(a, s);
+      else if (a4 && round_is_faster(n, a, tail)) e = launch_append_round(a, s);
       else if (n.hint.waves == 0 && decode_step_supported(a)) e = launch_decode_step(a, s);
       else e = launch_fused_append(a, s);
     }

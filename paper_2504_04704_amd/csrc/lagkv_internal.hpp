@@ -135,6 +135,7 @@ hipError_t launch_decode_step(const AppendArgs& a, hipStream_t s);
 
 // The same round for the other shapes the chunk kernels take (rows on 4-byte aligned addresses).
 bool append_round_supported(const AppendArgs& a);
+int append_round_slices(int D, int esize, int L);  // 16-byte row slices a lane holds of a chunk: up to 8, 16 or 32
 hipError_t launch_append_round(const AppendArgs& a, hipStream_t s);
 hipError_t launch_round_f32(const AppendArgs& a, hipStream_t s);
 hipError_t launch_round_bf16(const AppendArgs& a, hipStream_t s);

@@ -85,3 +85,27 @@ def test_plain_append_keeps_what_lies_around_it(D, dtype):
     assert torch.equal(K, Kh) and torch.equal(V, Vh)
     assert torch.equal(pos, torch.arange(90, dtype=torch.int32, device=pos.device).expand(3, 5, 90))
     assert bool((cache.K[:, :, 90:] == 7).all()) and bool((cache.V[:, :, 90:] == 7).all()) and bool((cache.pos[:, :, 90:] == -7).all())
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
+@pytest.mark.parametrize("L,D,dtype", [(64, 128, torch.bfloat16), (160, 96, torch.bfloat16), (200, 128, torch.float16), (256, 128, torch.bfloat16),
+                                       (300, 256, torch.bfloat16), (130, 128, torch.float32), (200, 100, torch.bfloat16)])
+def test_single_round_on_either_side_of_its_stream_counts(L, D, dtype, variant):
+    """8, 16 and 32 slices a lane, at the stream counts where the choice of the kernel changes (up to a workgroup per
+    compute unit, half of that, two per unit), with nothing and with much behind the reference chunk."""
+    S = 2
+    for H, behind in [(128, 0), (136, 0), (256, L - 1), (264, 0), (264, L - 1), (512, 1)]:
+        say("append choice", L, D, dtype, "variant", variant, "streams", H, "behind", behind)
+        T = S + 2 * L + behind
+        Kh, Vh = gen(1, H, T, D, dtype, seed=L + H)
+        cache = lagkv.Cache(1, H, D, T, S, L, 0.25, dtype=dtype, variant=variant)
+        first = S + 2 * L - 1
+        cache.append_and_compress(Kh[:, :, :first], Vh[:, :, :first])
+        assert cache.n_static == S
+        cache.append_and_compress(Kh[:, :, first:], Vh[:, :, first:])
+        torch.cuda.synchronize()
+        few = [0, H // 2, H - 1]
+        sub = lagkv.Cache(1, 3, D, T, S, L, 0.25, dtype=dtype, variant=variant)
+        sub.K, sub.V, sub.pos = (x[:, few].contiguous() for x in (cache.K, cache.V, cache.pos))
+        sub.c = lagkv.CacheT(0, 0, None, T, cache.n_static, cache.n_tail, cache.n_seen)
+        oracle_history_check(sub, Kh[:, few], Vh[:, few], S, L, 0.25, VARIANT_NAME[variant])
