@@ -135,7 +135,8 @@ __global__ void __launch_bounds__(512, 2) hold_pass_kernel(const PassArgs a) {
   constexpr int64_t rowbytes = (int64_t)LPR * 16;
   const int64_t coff = (int64_t)cl * 16;
 
-  // the first streams * nseg workgroups score, the rest copy sink and window rows
+  // the first streams * nseg workgroups score, the rest copy sink and window rows; if there are none (see
+  // launch_hold_pass), the workgroup of a stream's last segment does, first of all
   const int64_t streams = (int64_t)a.B * a.H, n_score = streams * a.nseg;
   const bool edge = blockIdx.x >= n_score;
   const int64_t stream = edge ? (blockIdx.x - n_score) / a.edge : stream_of(blockIdx.x / a.nseg, streams, a.order);
@@ -154,11 +155,11 @@ __global__ void __launch_bounds__(512, 2) hold_pass_kernel(const PassArgs a) {
   const float inv_D = 1.0f / (float)a.D;
   const float inv_dof = 1.0f / (float)(a.D - a.ddof);
 
-  if (edge) {
+  if (edge || (a.edge == 0 && gather && seg == a.nseg - 1)) {
     copy_edge_rows<LPR>(kin, vin, a.st, kout, vout, iout, rowbytes, S, S + a.n_s * L, S + a.n_s * k,
-                        a.T - (S + a.n_s * L), (int)((blockIdx.x - n_score) % a.edge), a.edge, (int)coff, tid,
-                        nthreads);
-    return;
+                        a.T - (S + a.n_s * L), edge ? (int)((blockIdx.x - n_score) % a.edge) : 0, edge ? a.edge : 1,
+                        (int)coff, tid, nthreads);
+    if (edge) return;
   }
 
   const int64_t p0 = (int64_t)seg * a.n_s / a.nseg;
@@ -565,13 +566,30 @@ static hipError_t launch_hold_t(const PassArgs& a, int nsc, dim3 grid, size_t ld
                         : launch_hold_v<ET, false>(a, nsc, grid, lds, s);
 }
 
+// Sink and window rows copied by the scoring workgroups themselves, at their head, or by workgroups of their own.
+// One workgroup fills a CU, so the latter run on the CUs that the last round of scoring leaves free, or else make a
+// round of their own: 256 streams (a CU each), one scored chunk of 128 rows 18.6 us against 15.8 us in line, two
+// 23.3 us against 20.7 us, six to ten equal, 254 of 512 rows 4142 us against 4169 us in line; 480 streams, one
+// chunk 33.0 us against 31.1 us.  With room they hide: 128 streams, one chunk of 512 rows, 1.27 times the speed in
+// line; 224 streams, four of 128, 1.05 times; 700 streams, four of 256, 1.07 times.  So in line up to eight scored
+// chunks where the rows to copy are more than twice (in a launch of several rounds, which feels one more the less,
+// four times) what the free CUs would score in a round; but never where a stream is cut into segments, the last
+// of which would then be the longest (128 streams in two, two chunks of 512 rows: 1.18 times the old speed with
+// workgroups of their own, 1.11 in line).
+static bool edges_in_line(const PassArgs& a) {
+  const int64_t streams = (int64_t)a.B * a.H, rounds = (streams + 255) / 256;
+  const int64_t rows = streams * (a.T - a.n_s * a.L);
+  return a.nseg == 1 && a.n_s <= 8 && rows > (rounds > 1 ? 4 : 2) * (rounds * 256 - streams) * (a.n_s + 1) * a.L;
+}
+
 hipError_t launch_hold_pass(const PassArgs& args, hipStream_t s) {
   PassArgs a = args;
   if (!hold_supported(a.D, a.esize, a.L, a.k) || a.variant == 2) return hipErrorInvalidValue;
   const int lpr = 16, nsc = hold_nsc(a.L, lpr), R = (kHoldWaves / 2) * (kWave / lpr);
-  a.edge = edge_parts(a, 4 * kHoldWaves * (kWave / lpr));
+  if (a.nseg < 1 || a.nseg > a.n_s) return hipErrorInvalidValue;
+  a.edge = edges_in_line(a) ? 0 : edge_parts(a, 4 * kHoldWaves * (kWave / lpr));
   const int64_t nblocks = (int64_t)a.B * a.H * (a.nseg + a.edge);
-  if (nblocks <= 0 || nblocks > 0x7fffffffLL || a.nseg < 1 || a.nseg > a.n_s) return hipErrorInvalidValue;
+  if (nblocks <= 0 || nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
   // per-lane offsets inside a step are 32 bit, and so are the step offsets of the first loads
   if (a.st * (int64_t)R * kHoldSteps >= (1LL << 31)) return hipErrorInvalidValue;
   const size_t lds = (size_t)hold_lds(a.D, kHoldSteps * R, a.k, kHoldSteps / nsc, a.variant == 1).total;

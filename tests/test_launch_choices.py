@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2504_04704_amd import lagkv
+from tests import parity_util as PU
 from tests.test_gpu_parity import VARIANT_NAME, gen, oracle_history_check, run_and_check, say
 
 pytestmark = pytest.mark.gpu
@@ -92,6 +93,21 @@ def test_channel_offsets_far_above_the_ranges(D, L, variant):
         cache.append_and_compress(K[:, :, a:b], V[:, :, a:b])
     torch.cuda.synchronize()
     oracle_history_check(cache, K[:, :, :b], V[:, :, :b], S, L, 0.25, VARIANT_NAME[variant])
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL])
+@pytest.mark.parametrize("B,H,n,m,L,S", [(2, 128, 2, 0, 128, 16), (2, 128, 5, 127, 128, 0), (1, 200, 2, 100, 128, 700), (1, 224, 3, 255, 256, 1),
+                                         (2, 256, 2, 3, 512, 16), (1, 700, 2, 77, 128, 3), (1, 96, 9, 20, 128, 5)])
+def test_sink_and_window_rows_copied_in_line(B, H, n, m, L, S, variant):
+    """Streams that fill the compute units, or nearly: the resident kernel's scoring workgroups copy these rows themselves
+    (the last case, with room, and the positions of every stream, beside it)."""
+    say("edge rows in line", B, H, n, m, L, S, "variant", variant)
+    T = S + n * L + m
+    K, V = gen(B, H, T, 128, torch.bfloat16, seed=H + n)
+    out, _ = run_and_check(K, V, S, L, 0.25, variant=variant, streams=[(0, 0), (B - 1, H // 2), (B - 1, H - 1)])
+    PU.check_index_invariants(out.idx, T, S, L, L // 4, n - 1)
+    rows = out.idx.long().unsqueeze(-1).expand(-1, -1, -1, 128)
+    assert torch.equal(out.K, K.gather(2, rows)) and torch.equal(out.V, V.gather(2, rows))
 
 
 def on_odd_addresses(x, pad, shift):
