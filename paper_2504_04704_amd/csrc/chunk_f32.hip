@@ -7,15 +7,16 @@ namespace lagkv {
 bool chunk_supported(int D, int esize, int L, int64_t st) {
   const int64_t rowbytes = (int64_t)D * esize;
   if (rowbytes < 16 || rowbytes > 512 || rowbytes % 4 != 0 || L > 512) return false;
-  const int lpr = chunk_lpr((int)rowbytes);
-  if ((L + chunk_step(lpr) - 1) / chunk_step(lpr) > 32) return false;
+  if (chunk_slices(D, esize, L) > 32) return false;
   return st * (int64_t)L < (1LL << 31);  // lane offsets inside a chunk are 32 bit
 }
 
-int chunk_places(int D, int esize, int L) {
+int chunk_slices(int D, int esize, int L) {
   const int R = chunk_step(chunk_lpr(D * esize));
-  return (L + R - 1) / R <= 8 ? 2 : 1;
+  return (L + R - 1) / R;
 }
+
+int chunk_places(int D, int esize, int L) { return chunk_slices(D, esize, L) <= 8 ? 2 : 1; }
 
 hipError_t launch_chunk_pass(const PassArgs& args, hipStream_t s) {
   PassArgs a = args;

@@ -196,21 +196,33 @@ bool use_resident(const Norm& n) {
   return n.hint.path == LAGKV_PATH_RESIDENT || n.hint.path == LAGKV_PATH_AUTO;
 }
 
-// The chunk-at-a-time kernel.  It reads a reference chunk beside every chunk and overlaps nothing but the
-// workgroups that share a CU, so it takes (a) every call whose rows or addresses are not whole 16-byte slices -
-// the walking kernels cannot, and the three-kernel path reads such rows 2 or 4 bytes at a time (64 streams of
-// 8K rows of 200 bytes: 86 us against 570 us); and (b) calls of at most two rounds of workgroups that would
-// go to the streaming kernel (32 streams of 2335 rows, lag 246: 26 us against 37 us; 40 streams of 1228
-// rows of 128 bytes, lag 128: 10 us against 16.5 us; with four rounds it is the slower one, 36 streams of 6948 rows
-// of 128 bytes 34.6 us against 33 us).  The register-resident kernel is as fast or faster at any size.
+// The chunk-at-a-time kernel.  It reads a reference chunk beside every chunk, and for Eq. 16 the values of rows that
+// are not kept (in a scores-only call the keys a second time), and overlaps nothing but the workgroups that share
+// a CU.  So it takes (a) the calls with a workspace, or on 4-byte addresses, whose rows are multiples of 4 bytes - the
+// walking kernels cannot, and the three-kernel path reads such rows 2 or 4 bytes at a time (64 streams of 8K rows of
+// 200 bytes: 109 us against 570 us); and (b) short calls that would go to the streaming kernel.  Those are counted in
+// scored chunks against the places of its workgroups, two a CU with up to 8 row slices a lane, else one.  Its gain
+// over the streaming kernel, launches of 1 to 10 chunks per stream, 15 shapes:
+//   up to 8 slices      half the places 1.36 to 1.81, all 0.99 to 1.68, twice 0.90 to 1.51 (32 streams of 2335 rows, lag
+//                       246: 26 us against 37 us; lag 128, rows of 128 bytes: 10 us against 16.5 us)
+//   9 to 16 slices      half 1.40 to 2.34, all 1.05 to 2.00, twice 0.79 to 1.28 (as many above 1 as below)
+//   17 to 32 slices     half 1.17 to 1.58, all 0.88 to 1.49, 1.25 times 0.74 to 1.07
+//   Eq. 16              half 0.83 to 1.55, three quarters 0.76 to 1.42, all 0.64 to 1.27
+//   Eq. 16, scores      all 1.08 to 1.77 (17 to 32 slices: half 1.00 to 1.28, all 0.85 to 1.21), 1.25 times 0.54 to 1.43
+// The register-resident kernel is as fast or faster at any size.
+int64_t chunk_most(const Norm& n, bool gather) {
+  const int slices = chunk_slices(n.D, n.esize, n.L);
+  const int64_t places = 256 * chunk_places(n.D, n.esize, n.L);
+  if (n.variant == LAGKV_SCORE_L2) return gather || slices > 16 ? places / 2 : places;
+  return slices <= 16 ? 2 * places : places;
+}
 // Sets a.nseg where it says yes.
 bool use_chunk(const Norm& n, PassArgs& a, bool whole_slices) {
   if (n.hint.path != LAGKV_PATH_AUTO || n.hint.waves || n.hint.nseg || n.hint.order || n.hint.sel) return false;
   if (((a.sb | a.sh | a.st) & 3) || !chunk_supported(n.D, n.esize, n.L, a.st)) return false;
   if (!aligned_to(a.K, 4) || !aligned_to(a.V, 4) || !aligned_to(a.K_out, 4) || !aligned_to(a.V_out, 4)) return false;
-  const int64_t places = 256 * chunk_places(n.D, n.esize, n.L);
-  if (whole_slices && (use_resident(n) || n.streams * a.n_s > 2 * places)) return false;
-  const int nseg = pick_segments(n.streams, a.n_s, n.L, places, 64, 1, 32);
+  if (whole_slices && (use_resident(n) || n.streams * a.n_s > chunk_most(n, a.K_out != nullptr))) return false;
+  const int nseg = pick_segments(n.streams, a.n_s, n.L, 256 * chunk_places(n.D, n.esize, n.L), 64, 1, 32);
   // its workgroups are twice the three-kernel path's
   if (!grid_fits(n.streams * nseg + most_edge_workgroups(a), kChunkThreads)) return false;
   a.nseg = nseg;
@@ -267,7 +279,7 @@ int launch_fused_any(PassArgs& a, const Norm& n, hipStream_t s) {
 // keep two and more.  Gains below are time of the others over its time, cache kernels alone.
 bool round_is_faster(const Norm& n, const AppendArgs& a, int64_t tail) {
   if (!append_round_supported(a)) return false;
-  const int slices = append_round_slices(n.D, n.esize, n.L);
+  const int slices = chunk_slices(n.D, n.esize, n.L);
   // up to one workgroup per CU: 1.1 to 1.8 (64, 128, 256 streams) at any number of slices up to 16; beyond 16, where
   // the reference rows are read twice, 256 streams of Eq. 7-8 0.83 to 0.98 and 128 streams 1.0 to 1.2
   if (n.streams <= (slices <= 16 || n.variant == LAGKV_SCORE_LOCAL ? 256 : 128)) return true;

@@ -122,6 +122,7 @@ hipError_t launch_hold_pass(const PassArgs& a, hipStream_t s);
 // One-shot chunk-at-a-time kernel: rows of 16 to 512 bytes, a multiple of 4, on 4-byte aligned addresses.
 constexpr int kChunkThreads = 512;           // of the chunk kernels
 bool chunk_supported(int D, int esize, int L, int64_t st);
+int chunk_slices(int D, int esize, int L);   // 16-byte row slices a lane holds of a chunk: up to 8, 16 or 32
 int chunk_places(int D, int esize, int L);   // workgroups a CU holds
 hipError_t launch_chunk_pass(const PassArgs& a, hipStream_t s);
 hipError_t launch_chunk_f32(const PassArgs& a, hipStream_t s);
@@ -135,7 +136,6 @@ hipError_t launch_decode_step(const AppendArgs& a, hipStream_t s);
 
 // The same round for the other shapes the chunk kernels take (rows on 4-byte aligned addresses).
 bool append_round_supported(const AppendArgs& a);
-int append_round_slices(int D, int esize, int L);  // 16-byte row slices a lane holds of a chunk: up to 8, 16 or 32
 hipError_t launch_append_round(const AppendArgs& a, hipStream_t s);
 hipError_t launch_round_f32(const AppendArgs& a, hipStream_t s);
 hipError_t launch_round_bf16(const AppendArgs& a, hipStream_t s);

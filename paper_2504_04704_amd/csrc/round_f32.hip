@@ -55,11 +55,6 @@ bool append_round_supported(const AppendArgs& a) {
   return round_lds_bytes(a.D, a.L) <= kMaxLdsBytes && grid_fits((int64_t)a.B * a.H, kChunkThreads);
 }
 
-int append_round_slices(int D, int esize, int L) {
-  const int R = chunk_step(chunk_lpr(D * esize));
-  return (L + R - 1) / R;
-}
-
 hipError_t launch_append_round(const AppendArgs& args, hipStream_t s) {
   AppendArgs a = args;
   if (!append_round_supported(a)) return hipErrorInvalidValue;
