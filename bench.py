@@ -148,13 +148,6 @@ def copy_rate_gbs(src, dst, n=3):
     return 2 * cnt * src.element_size() / (s.elapsed_time(e) / n * 1e-3) / 1e9
 
 
-def kernel_name(path: int) -> str:
-    """Name of the kernel a one-shot pass runs, from the path the library reports for it."""
-    from paper_2504_04704_amd import lagkv
-    return {lagkv.PATH_RESIDENT: "hold_pass_kernel", lagkv.PATH_FUSED: "split_pass_kernel",
-            lagkv.PATH_STAGED: "staged_score_kernel"}[path]
-
-
 def bench_compress(args, cfg_name=None, steps=None, warmup=None, placements=None, cpu_streams=None,
                    cpu_single=None, with_copy=True, with_ablations=False):
     import torch
@@ -225,7 +218,7 @@ def bench_compress(args, cfg_name=None, steps=None, warmup=None, placements=None
         # Eq. 16 scores from K alone: V is read only where it is kept
         alg = cfg.streams * (K.element_size() * cfg.D * (cfg.T + 3 * pl.T_out) + 4 * pl.T_out)
     gbs = lambda ms: alg / (ms * 1e-3) / 1e9
-    kernel = kernel_name(lagkv.path_for(p, cfg.T))
+    kernel = lagkv.kernel_for(p, cfg.T)
     traffic = read_traffic(f"{kernel.replace('_kernel', '')}_{cfg.name}_traffic.txt") if args.variant == "lag" else None
     tq = quantiles(trials)
     roof = {"bound": "hbm", "achieved": gbs(q["mean"]), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -267,7 +260,7 @@ def bench_compress(args, cfg_name=None, steps=None, warmup=None, placements=None
             valg = alg if vname == "local" else \
                 cfg.streams * (K.element_size() * cfg.D * (cfg.T + 3 * pl.T_out) + 4 * pl.T_out)
             vp = lagkv.params_for(K, cfg.S, cfg.L, cfg.r, variant=vid, launch=launch)
-            abl.append({"variant": vname, "kernel": kernel_name(lagkv.path_for(vp, cfg.T)), "steps": 5,
+            abl.append({"variant": vname, "kernel": lagkv.kernel_for(vp, cfg.T), "steps": 5,
                         "ms": vq["mean"], "ms_median": vq["median"], "algorithmic_bytes": valg,
                         "achieved_gbs": valg / (vq["mean"] * 1e-3) / 1e9,
                         "frac": valg / (vq["mean"] * 1e-3) / 1e9 / HBM_PEAK_GBS})

@@ -260,15 +260,23 @@ enum { LAGKV_SELECT_AUTO = 0, LAGKV_SELECT_WAVE = 1, LAGKV_SELECT_GROUP = 2 };
 int32_t lagkv_launch_hint_ex(int path, int waves, int segments, int order, int select);
 
 /*
- * Which kernels lagkv_compress runs for these parameters (launch override included) on a
+ * The path lagkv_compress takes for these parameters (launch override included) on a
  * cache of T rows held in 16-byte aligned buffers: LAGKV_PATH_RESIDENT, LAGKV_PATH_FUSED
  * (the streaming one-shot kernel, or for short calls the chunk-at-a-time kernel in its place)
  * or LAGKV_PATH_STAGED (the shapes that need the workspace: the three-kernel path, or the
- * chunk-at-a-time kernel where rows are multiples of 4 bytes); for benchmarks and profiles that have to name the kernel they time.
+ * chunk-at-a-time kernel where rows are multiples of 4 bytes).
  * Host only.  Returns minus the lagkv_status the call itself would return for parameters
  * it rejects.
  */
 int lagkv_path_for(const lagkv_params* p, int64_t T);
+
+/*
+ * Name of the kernel that scores in that call, for benchmarks and profiles that have to name
+ * what they time: "hold_pass_kernel", "split_pass_kernel", "chunk_pass_kernel" or
+ * "staged_score_kernel" ("copy_rows_kernel" where nothing is compressed).  Host only; NULL
+ * for parameters the call rejects.
+ */
+const char* lagkv_kernel_for(const lagkv_params* p, int64_t T);
 
 /* Static, human readable text for a lagkv_status. */
 const char* lagkv_strerror(int status);

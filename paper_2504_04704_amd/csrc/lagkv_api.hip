@@ -731,6 +731,23 @@ int lagkv_path_for(const lagkv_params* p, int64_t T) {
   return staged_fits(n) ? LAGKV_PATH_STAGED : -LAGKV_ESHAPE;
 }
 
+const char* lagkv_kernel_for(const lagkv_params* p, int64_t T) {
+  const int path = lagkv_path_for(p, T);
+  if (path < 0) return nullptr;
+  Norm n;
+  int64_t sb, sh, st;
+  if (validate(p, &n) != LAGKV_OK || strides_of(p, n, T, &sb, &sh, &st) != LAGKV_OK) return nullptr;
+  lagkv_plan_t pl;
+  plan_of(n, T, n.S, &pl);
+  if (pl.n_scored == 0) return "copy_rows_kernel";
+  PassArgs a;
+  fill_pass(&a, n, nullptr, nullptr, T, pl, sb, sh, st);
+  alignas(16) char out[16];  // (a call with outputs; nothing is stored)
+  a.K_out = a.V_out = out;
+  if (use_chunk(n, a, path != LAGKV_PATH_STAGED)) return "chunk_pass_kernel";
+  return path == LAGKV_PATH_RESIDENT ? "hold_pass_kernel" : path == LAGKV_PATH_FUSED ? "split_pass_kernel" : "staged_score_kernel";
+}
+
 const char* lagkv_strerror(int status) {
   switch (status) {
     case LAGKV_OK: return "ok";

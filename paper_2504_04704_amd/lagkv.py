@@ -31,7 +31,7 @@ EXPORTS = ("lagkv_plan", "lagkv_keep_for_compression", "lagkv_workspace_bytes", 
            "lagkv_select", "lagkv_compress", "lagkv_compress_static", "lagkv_cache_after_compress",
            "lagkv_prefill_rows",
            "lagkv_append_and_compress", "lagkv_launch_hint", "lagkv_launch_hint_ex", "lagkv_path_for",
-           "lagkv_strerror",
+           "lagkv_kernel_for", "lagkv_strerror",
            "lagkv_version")
 
 
@@ -103,6 +103,8 @@ def load():
     lib.lagkv_launch_hint_ex.restype = C.c_int32
     lib.lagkv_path_for.argtypes = [C.POINTER(Params), C.c_int64]
     lib.lagkv_path_for.restype = C.c_int
+    lib.lagkv_kernel_for.argtypes = [C.POINTER(Params), C.c_int64]
+    lib.lagkv_kernel_for.restype = C.c_char_p
     lib.lagkv_strerror.argtypes = [C.c_int]
     lib.lagkv_strerror.restype = C.c_char_p
     lib.lagkv_version.argtypes = []
@@ -133,6 +135,15 @@ def path_for(p: "Params", T: int) -> int:
     if v < 0:
         raise LagKVError(-v, "lagkv_path_for")
     return v
+
+
+def kernel_for(p: "Params", T: int) -> str:
+    """lagkv_kernel_for: name of the kernel that scores in a lagkv_compress call with these parameters."""
+    name = load().lagkv_kernel_for(C.byref(p), T)
+    if name is None:
+        path_for(p, T)  # (raises with the status)
+        raise LagKVError(EINVAL, "lagkv_kernel_for")
+    return name.decode()
 
 
 def launch_hint(path: int = PATH_AUTO, waves: int = 0, segments: int = 0, order: int = 0,
