@@ -109,3 +109,52 @@ def test_single_round_on_either_side_of_its_stream_counts(L, D, dtype, variant):
         sub.K, sub.V, sub.pos = (x[:, few].contiguous() for x in (cache.K, cache.V, cache.pos))
         sub.c = lagkv.CacheT(0, 0, None, T, cache.n_static, cache.n_tail, cache.n_seen)
         oracle_history_check(sub, Kh[:, few], Vh[:, few], S, L, 0.25, VARIANT_NAME[variant])
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
+@pytest.mark.parametrize("D,dtype,L", [(128, torch.bfloat16, 128), (128, torch.bfloat16, 300), (100, torch.float16, 50)])
+def test_an_append_captured_and_replayed(D, dtype, L, variant):
+    """The kernels of two calls - rows that complete nothing, then the row that completes a chunk - replayed on the same
+    buffers three times, the cache put back and eager work done in between."""
+    S, T = 5, 5 + 2 * L
+    Kh, Vh = gen(2, 4, T, D, dtype, seed=L + D)
+    first = T - 4
+
+    def start():
+        cache = lagkv.Cache(2, 4, D, T, S, L, 0.25, dtype=dtype, variant=variant)
+        cache.append_and_compress(Kh[:, :, :first].contiguous(), Vh[:, :, :first].contiguous())
+        return cache
+
+    parts = [tuple(x[:, :, a:b].contiguous() for x in (Kh, Vh)) for a, b in ((first, T - 1), (T - 1, T))]
+    eager, cache = start(), start()
+    for part in parts:
+        eager.append_and_compress(*part)
+    held = [x.clone() for x in (cache.K, cache.V, cache.pos)]
+    counters = (cache.c.n_static, cache.c.n_tail, cache.c.n_seen)
+
+    def put_back():
+        for x, y in zip((cache.K, cache.V, cache.pos), held):
+            x.copy_(y)
+        cache.c.n_static, cache.c.n_tail, cache.c.n_seen = counters
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for part in parts:
+            cache.append_and_compress(*part)
+    torch.cuda.current_stream().wait_stream(side)
+    put_back()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for part in parts:
+            cache.append_and_compress(*part)
+    after = (cache.c.n_static, cache.c.n_tail, cache.c.n_seen)
+    for rep in range(3):
+        put_back()
+        _ = (cache.K.float().sum() + rep).item()
+        g.replay()
+        torch.cuda.synchronize()
+        say("append graph replay", D, L, "variant", variant, rep)
+        cache.c.n_static, cache.c.n_tail, cache.c.n_seen = after
+        assert all(torch.equal(x, y) for x, y in zip(cache.view(), eager.view()))
+    oracle_history_check(cache, Kh, Vh, S, L, 0.25, VARIANT_NAME[variant])

@@ -102,11 +102,15 @@ def test_shapes_against_oracle(shape, path):
 
 @pytest.mark.parametrize("D,dtype", [(42, torch.float32), (100, torch.bfloat16), (5, torch.float32), (300, torch.bfloat16),
                                      (13, torch.float16)])
-def test_unaligned_head_dims_use_the_staged_path(D, dtype):
+def test_unaligned_head_dims_on_the_staged_path_and_as_chosen(D, dtype):
     say("unaligned D", D, dtype)
     K, V = gen(1, 2, 8 + 4 * 50 + 7, D, dtype, seed=D)
-    assert lagkv.workspace_bytes(lagkv.params_for(K, 8, 50, 0.3), K.shape[2]) > 0
-    run_and_check(K, V, 8, 50, 0.3)
+    for path in (lagkv.PATH_STAGED, lagkv.PATH_AUTO):
+        p = lagkv.params_for(K, 8, 50, 0.3, launch=hint(path))
+        assert lagkv.workspace_bytes(p, K.shape[2]) > 0
+        chunk = path == lagkv.PATH_AUTO and D in (42, 100, 5)   # rows of 16 to 512 bytes, a multiple of 4
+        assert lagkv.kernel_for(p, K.shape[2]) == ("chunk_pass_kernel" if chunk else "staged_score_kernel")
+        run_and_check(K, V, 8, 50, 0.3, launch=hint(path))
 
 
 # rows of 3, 5, 7, 9, 10, 12, 17, 25 and 31 16-byte slices: fewer than the 4, 8, 16 or 32 lanes that hold a row

@@ -1,6 +1,6 @@
 """GPU: the one-shot pass under its own launch choices (nothing hinted), at the sizes where the split of
-the work can go wrong: one chunk per segment and several, sink and window rows in one share and in many,
-shares of one row, no sink, a window of one lag exactly."""
+the work can go wrong: one chunk per segment and several in each kernel, sink and window rows in one share and in
+many, shares of one row, no sink, a window of one lag exactly."""
 import pytest
 import torch
 
@@ -160,3 +160,102 @@ def test_whole_strides_on_a_four_byte_base_need_no_workspace(D, dtype, pad, shif
             cache.append_and_compress(K[:, :, a:b], V[:, :, a:b])
         torch.cuda.synchronize()
         oracle_history_check(cache, K[:, :, :b], V[:, :, :b], S, L, 0.3, VARIANT_NAME[variant])
+
+
+# streams, scored chunks, D, dtype, L: several chunks per workgroup of the chunk kernel (512 places up to 8 slices a
+# lane, else 256), in each range of its selection, on partial and on whole rows
+LONG_RUNS = [
+    (64, 21, 100, torch.bfloat16, 128), (40, 40, 100, torch.bfloat16, 64), (64, 13, 100, torch.bfloat16, 200), (64, 9, 100, torch.float16, 300),
+    (300, 3, 126, torch.float32, 128), (70, 19, 34, torch.bfloat16, 512), (7, 160, 33, torch.float32, 60),
+    (72, 12, 80, torch.bfloat16, 100), (90, 5, 64, torch.bfloat16, 500), (1, 1000, 96, torch.float16, 40), (120, 4, 96, torch.float32, 128),
+]
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
+@pytest.mark.parametrize("streams,n_s,D,dtype,L", LONG_RUNS)
+def test_several_chunks_per_workgroup_of_the_chunk_kernel(streams, n_s, D, dtype, L, variant):
+    """A workgroup that walks a run of chunks: the statistics handed from one to the next, rows loaded behind the stores
+    of the one before, the chunk's own statistics (Eq. 14-15), scores alone."""
+    whole = D * dtype.itemsize % 16 == 0
+    if whole and variant == lagkv.SCORE_L2:  # half the places at most go to it: a scores-only call takes more
+        n_s = max(1, 120 // streams)
+    S, T = 3, 3 + (n_s + 1) * L + 5
+    say("long runs", streams, n_s, D, dtype, L, "variant", variant)
+    K, V = gen(1, streams, T, D, dtype, seed=streams + L)
+    p = lagkv.params_for(K, S, L, 0.3, variant)
+    assert lagkv.kernel_for(p, T) == "chunk_pass_kernel"
+    assert n_s * streams > 256 * (2 if L * D * dtype.itemsize <= 32 * 1024 else 1) or (whole and variant == lagkv.SCORE_L2)
+    out, _ = run_and_check(K, V, S, L, 0.3, variant=variant, streams=[(0, s) for s in sorted({0, streams // 2, streams - 1})])
+    PU.check_index_invariants(out.idx, T, S, L, out.plan.k, n_s)
+    rows = out.idx.long().unsqueeze(-1).expand(-1, -1, -1, D)
+    assert torch.equal(out.K, K.gather(2, rows)) and torch.equal(out.V, V.gather(2, rows))
+    assert torch.equal(lagkv.score(K, V, S, L, 0.3, variant=variant), out.scores)
+    if streams * n_s < 1500:
+        ref = lagkv.score(K, V, S, L, 0.3, variant=variant, launch=lagkv.launch_hint(lagkv.PATH_STAGED))
+        assert torch.allclose(out.scores, ref, rtol=4e-6, atol=0)     # (as for partial slices above)
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
+@pytest.mark.parametrize("D,dtype,L", [(100, torch.bfloat16, 60), (100, torch.float16, 128), (33, torch.float32, 250), (66, torch.bfloat16, 400), (80, torch.bfloat16, 300)])
+def test_infinities_and_nan_stay_in_their_streams(D, dtype, L, variant):
+    """Scores of such rows are unspecified, but every chunk keeps k rows of its own, in order and bit for bit, and the
+    streams beside them are what they are without: one-shot and in a cache whose chunk completes."""
+    S, n = 5, 4
+    T = S + n * L + 7
+    say("inf and nan", D, dtype, L, "variant", variant)
+    K, V = gen(1, 6, T, D, dtype, seed=D + L)
+    want = lagkv.compress(K, V, S, L, 0.3, variant=variant, want_scores=True)
+    bad = torch.randperm(T, generator=torch.Generator().manual_seed(L))[: T // 3].cuda()
+    K[:, 1, bad, 3], V[:, 2, bad, D - 1] = float("nan"), float("inf")
+    K[:, 3], V[:, 3] = float("nan"), -float("inf")
+    K[:, 4, ::2, 0], K[:, 4, 1::2, D - 1] = float("inf"), -float("inf")
+    out = lagkv.compress(K, V, S, L, 0.3, variant=variant, want_scores=True)
+    cache = lagkv.Cache(1, 6, D, T, S, L, 0.3, dtype=dtype, variant=variant)
+    for a, b in [(0, S + 2 * L - 2), (S + 2 * L - 2, S + 2 * L + 1), (S + 2 * L + 1, S + 3 * L + 1), (S + 3 * L + 1, T)]:
+        cache.append_and_compress(K[:, :, a:b], V[:, :, a:b])
+    torch.cuda.synchronize()
+    bits = {2: torch.int16, 4: torch.int32}[dtype.itemsize]
+    ck, cv, cpos = cache.view()
+    for gk, gv, idx in ((out.K, out.V, out.idx), (ck.contiguous(), cv.contiguous(), cpos.contiguous())):
+        PU.check_index_invariants(idx, T, S, L, out.plan.k, n - 1)
+        rows = idx.long().unsqueeze(-1).expand(-1, -1, -1, D)
+        assert torch.equal(gk.view(bits), K.gather(2, rows).view(bits)) and torch.equal(gv.view(bits), V.gather(2, rows).view(bits))
+    for s in (0, 5):
+        assert torch.equal(out.scores[:, s], want.scores[:, s]) and torch.equal(out.idx[:, s], want.idx[:, s])
+        assert torch.equal(cpos[:, s], want.idx[:, s])
+
+
+@pytest.mark.parametrize("D,dtype,L", [(100, torch.bfloat16, 128), (80, torch.bfloat16, 100), (66, torch.float16, 300)])
+def test_chunk_kernel_in_a_captured_graph(D, dtype, L):
+    """... and replayed three times, with eager work between, on other bytes in the same buffers too."""
+    S, T = 16, 16 + 5 * L + 17
+    K, V = gen(2, 4, T, D, dtype, seed=404)
+    p = lagkv.params_for(K, S, L, 0.25)
+    assert lagkv.kernel_for(p, T) == "chunk_pass_kernel"
+    want = lagkv.compress(K, V, S, L, 0.25, want_scores=True)
+    out = [torch.zeros_like(x) for x in (want.K, want.V, want.idx, want.scores)]
+    ws = torch.empty(max(lagkv.workspace_bytes(p, T), 16), dtype=torch.uint8, device="cuda")
+
+    def call():
+        lagkv.compress(K, V, S, L, 0.25, out=(out[0], out[1]), idx_out=out[2], scores_out=out[3], ws=ws)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for rep in range(4):
+        if rep == 3:
+            for x, y in zip((K, V), gen(2, 4, T, D, dtype, seed=405)):
+                x.copy_(y)
+            want = lagkv.compress(K, V, S, L, 0.25, want_scores=True)
+        for x in out:
+            x.zero_()
+        _ = (K.float().sum() + rep).item()
+        g.replay()
+        torch.cuda.synchronize()
+        say("chunk graph replay", D, L, rep)
+        assert all(torch.equal(x, y) for x, y in zip(out, (want.K, want.V, want.idx, want.scores)))

@@ -43,18 +43,23 @@ def _both(K, V, S, L, r, variant, launch=0):
     assert torch.equal(Ko, want.K) and torch.equal(Vo, want.V)
 
 
+@pytest.mark.parametrize("path", [lagkv.PATH_STAGED, lagkv.PATH_AUTO])
 @pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
-def test_static_scratch_two_calls_in_a_row_second_one_smaller(variant):
+def test_static_scratch_two_calls_in_a_row_second_one_smaller(variant, path):
     lagkv.load()
-    # 200-byte rows (D = 100 bf16): only the three-kernel path serves them, so the scratch is used
+    # 200-byte rows (D = 100 bf16): on the three-kernel path, asked for by hint, the scratch is used; left to itself the
+    # call goes to the chunk kernel, which touches none of it
+    launch = lagkv.launch_hint(path)
     K, V = _gen(3, 4, 16 + 9 * 64 + 21, 100, torch.bfloat16, seed=7)
-    assert lagkv.workspace_bytes(lagkv.params_for(K, 16, 64, 0.25), K.shape[2]) > 0
-    _both(K, V, 16, 64, 0.25, variant)
+    p = lagkv.params_for(K, 16, 64, 0.25, variant, launch=launch)
+    assert lagkv.workspace_bytes(p, K.shape[2]) > 0
+    assert lagkv.kernel_for(p, K.shape[2]) == ("staged_score_kernel" if path == lagkv.PATH_STAGED else "chunk_pass_kernel")
+    _both(K, V, 16, 64, 0.25, variant, launch)
     # second call: fewer streams, shorter, another lag; the array still holds the first call's data
     K2, V2 = _gen(1, 2, 8 + 4 * 50 + 3, 100, torch.bfloat16, seed=8)
-    _both(K2, V2, 8, 50, 0.3, variant)
+    _both(K2, V2, 8, 50, 0.3, variant, launch)
     # and a larger one again
-    _both(K, V, 16, 64, 0.25, variant)
+    _both(K, V, 16, 64, 0.25, variant, launch)
 
 
 def test_static_scratch_staged_by_hint_and_fused_shapes():
