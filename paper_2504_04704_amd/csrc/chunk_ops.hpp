@@ -37,9 +37,6 @@ __host__ __device__ inline ChunkLds chunk_lds(int D, int L) {
   return l;
 }
 
-// Workgroup barrier for LDS traffic only (see hold_pass.hip): rows still in flight are not waited for.
-__device__ __forceinline__ void lds_only_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // min(a, b) where lanes [0,32) receive the minimum of `a` over both halves of the wavefront and lanes
 // [32,64) that of `b`; the same over the even and odd rows of 16 lanes.
 __device__ __forceinline__ float fold_min32(float a, float b) {

@@ -95,9 +95,9 @@ __global__ void __launch_bounds__(512, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const
           if (j0 + u < n) g.fold_pair(q[u], q[u + 1]);
       }
       g.park(statbuf);
-      lds_only_barrier();
+      lds_barrier();
       g.publish(statbuf, refbuf);
-      lds_only_barrier();
+      lds_barrier();
       g.take_ref(refbuf);
     } else {
 #pragma unroll
@@ -119,9 +119,9 @@ __global__ void __launch_bounds__(512, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const
           __builtin_amdgcn_sched_barrier(0);
         }
       g.park(statbuf);
-      lds_only_barrier();
+      lds_barrier();
       g.publish(statbuf, refbuf);
-      lds_only_barrier();
+      lds_barrier();
       g.take_ref(refbuf);
     }
     // 1. channel variance of every row (Eq. 9-10), or minus the key norm (Eq. 16); the running
@@ -131,13 +131,13 @@ __global__ void __launch_bounds__(512, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const
     g.variances(hold, here_s(n_iter), myvar + here_v(row0), l2, stats);
     if (stats) g.park(statbuf);
     if (L > kRankSelMax) group_sel_clear(selbuf, tid, kChunkWaves * kWave);
-    lds_only_barrier();
+    lds_barrier();
     if (stats) g.publish(statbuf, refbuf);
     // 2. chunk softmax, K+V sum and top-k (Eq. 10-11)
     float* gs = sout ? sout + p * L : nullptr;
     int32_t* gp = iout ? iout + S + p * k : nullptr;
     chunk_select(vK, vV, l2, L, k, gather, gs, rank, selbuf, slotmap, tid, gp, (uint32_t)(S + p * L));
-    lds_only_barrier();
+    lds_barrier();
     // 3. kept rows out of the registers, the next chunk's rows in
     const char* nb = cb - (int64_t)L * a.st;
     {

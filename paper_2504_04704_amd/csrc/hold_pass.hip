@@ -82,12 +82,6 @@ __device__ __forceinline__ uint4 buf_ld16(const char* base, uint32_t lane_off, u
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// Workgroup barrier for LDS traffic only: waits for this wavefront's LDS operations, not for
-// its vector-memory operations (a __syncthreads() carries a fence that may wait for those).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // f(integral_constant<int, I>) for I = BEGIN, BEGIN + STEP, ... < END
 template <int BEGIN, int END, int STEP, typename F>
 __device__ __forceinline__ void static_for(F&& f) {

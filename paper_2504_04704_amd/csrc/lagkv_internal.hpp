@@ -1,5 +1,5 @@
-// Internal interface between the C-ABI host layer (lagkv_api.hip) and the kernel
-// launchers (split_pass.hip, append_pass.hip, staged_pass.hip).  Not part of the public ABI.
+// Internal interface between the C-ABI host layer (lagkv_api.hip) and the kernel launchers
+// (split_pass.hip, hold_pass.hip, append_pass.hip, chunk_f32.hip, round_f32.hip, staged_pass.hip).  Not part of the public ABI.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>

@@ -15,6 +15,12 @@
 
 namespace lagkv {
 
+// Workgroup barrier for LDS traffic only: waits for this wavefront's LDS operations, not for
+// its vector-memory operations (a __syncthreads() carries a fence that may wait for those).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // 16-byte store of an output row slice.  The compacted cache is written once and not read
 // again by this pass: non-temporal, workgroup scope ("sc0 nt").  Measured on the 128K
 // workload: plain 17.4x ms, nt 17.35 ms, sc0 nt 17.26 ms, any sc1 form 17.4-17.9 ms.  The

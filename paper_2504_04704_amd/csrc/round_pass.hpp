@@ -1,7 +1,7 @@
 // One compression round of a decode cache (gfx950), in place, one workgroup per stream: the call in which
-// the appended rows complete exactly one more chunk, for up to a few streams per CU and for every shape
-// decode_step_kernel does not take (a reference chunk beyond its LDS share, Eq. 14-15, a sink that still
-// fills, rows that are not whole 16-byte slices).
+// the appended rows complete exactly one more chunk, for up to one stream per CU at any shape that the chunk
+// kernels take, for rows that are not whole 16-byte slices at any stream count, and above that for chunks of
+// up to 8 row slices a lane and some of up to 16 (the rule and the figures stand at round_is_faster, lagkv_api.hip).
 //
 // Such calls come a lag at a time while a prompt is prefilled, on few streams: a stream's chain of
 // dependent steps is what bounds them, not bandwidth.  As in chunk_pass.hpp everything is asked for at
@@ -119,17 +119,17 @@ __global__ void __launch_bounds__(512, 2) append_round_kernel(const AppendArgs a
   }
   if (!l2) {
     g.park(statbuf);
-    lds_only_barrier();
+    lds_barrier();
     g.publish(statbuf, refbuf);
-    lds_only_barrier();
+    lds_barrier();
     g.take_ref(refbuf);
   }
   // 2. variances, scores, selection (Eq. 9-11, Eq. 16)
   g.variances(hold, here_s(n_iter), (g.tensor ? vV : vK) + here_v(row0), l2, false);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // whatever was asked for above has been read
-  lds_only_barrier();
+  lds_barrier();
   chunk_select(vK, vV, l2, L, k, true, nullptr, rank, selbuf, slotmap, tid, nullptr, 0);
-  lds_only_barrier();
+  lds_barrier();
   // 3. kept rows -> [0, k)
   {
     const int row = here_v(row0), n = here_s(n_iter);
@@ -155,7 +155,7 @@ __global__ void __launch_bounds__(512, 2) append_round_kernel(const AppendArgs a
   auto put = [&](int to, int rows) __attribute__((always_inline)) {
     const int row = here_v(row0), n = here_s(n_iter);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    lds_only_barrier();
+    lds_barrier();
 #pragma unroll
     for (int j = 0; j < NSL; ++j)
       if (j < n && row + j * R < rows) store(to + row + j * R, hold[j]);
