@@ -104,7 +104,8 @@ int lagkv_keep_for_compression(int64_t T, int32_t S, int32_t L, double C, int64_
  * of 48 to 512 bytes that are a multiple of 16 bytes, strides that are multiples of 16
  * bytes, a lag that fits the LDS budget.  The three-kernel path used for every other shape stages scores and kept
  * positions there, and for an append the rows it moves; where this is not 0, lagkv_compress alone needs
- * 4*B*H*n_scored*L and 4*B*H*n_scored*k bytes, each rounded up to a multiple of 256.  The answer assumes 16-byte aligned K / V / output / cache pointers (any
+ * 4*B*H*n_scored*L and 4*B*H*n_scored*k bytes, each rounded up to a multiple of 256.  (The chunk kernels, which
+ * serve most of these shapes in its place, stage nothing; the workspace is demanded all the same.)  The answer assumes 16-byte aligned K / V / output / cache pointers (any
  * hipMalloc'ed buffer is), or where it is 0 4-byte aligned ones for lags of up to 512 (one
  * round of an append); a caller whose pointers are only element-aligned must ask, and
  * call, with a launch hint of LAGKV_PATH_STAGED.  Returns 0 on invalid parameters as well.
@@ -176,8 +177,9 @@ typedef struct {
  * is taken, its scores and kept positions are staged in a fixed device array inside the
  * library (LAGKV_STATIC_SCRATCH_BYTES per GPU, held from the first call on that GPU until
  * the process ends) instead.  The call allocates and frees nothing.
- *   - LAGKV_EWORKSPACE when the pass would need more than LAGKV_STATIC_SCRATCH_BYTES
- *     (use lagkv_compress with a workspace then); nothing is enqueued.
+ *   - LAGKV_EWORKSPACE when the three-kernel path would need more than
+ *     LAGKV_STATIC_SCRATCH_BYTES for a shape that is its own (use lagkv_compress with a
+ *     workspace then), whichever kernel would serve the call; nothing is enqueued.
  *   - The device that is current when the call is made must be the stream's device.
  *   - All calls on one GPU share that GPU's array: two calls that may run at the same time
  *     (different streams, different threads) race on it and must be serialised by the

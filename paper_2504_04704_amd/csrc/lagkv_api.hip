@@ -149,7 +149,10 @@ int split_nw(const Norm& n) {
 // one more round doubles the time (112 streams of 32K tokens at lag 1024: 560 workgroups on 512 places
 // 750 us, 448 workgroups 589 us).  A segment of c chunks costs c chunks of rows, one more that is only read
 // for the first reference, and `fixed` rows' worth of start-up and drain, plus `per_batch` rows per batch of
-// `batch` chunks.
+// `batch` chunks.  (Eq. 16 reads no such chunk, nor does Eq. 14-15 in the resident kernel; not charging them for it
+// made 6 of 600 shapes 4 to 13 % faster and 4 of them 4 to 7 % slower.  Nor does the cost know of a memory that is
+// saturated already, where one more segment is only one more chunk to read: 456 streams of 9 chunks of 128 rows of
+// 512 bytes, scores alone, three segments 146 us, two 130 us.)
 int pick_segments(int64_t streams, int64_t n_s, int64_t L, int64_t cap, int64_t fixed, int64_t batch,
                   int64_t per_batch) {
   int64_t best = 1, best_cost = INT64_MAX;
@@ -203,9 +206,10 @@ bool use_resident(const Norm& n) {
 // 200 bytes: 109 us against 570 us); and (b) short calls that would go to the streaming kernel.  Those are counted in
 // scored chunks against the places of its workgroups, two a CU with up to 8 row slices a lane, else one.  Its gain
 // over the streaming kernel, launches of 1 to 10 chunks per stream, 15 shapes:
-//   up to 8 slices      half the places 1.36 to 1.81, all 0.99 to 1.68, twice 0.90 to 1.51 (32 streams of 2335 rows, lag
-//                       246: 26 us against 37 us; lag 128, rows of 128 bytes: 10 us against 16.5 us)
-//   9 to 16 slices      half 1.40 to 2.34, all 1.05 to 2.00, twice 0.79 to 1.28 (as many above 1 as below)
+//   up to 8 slices      half the places 1.36 to 1.81, all 0.99 to 1.68, twice 0.90 to 1.51 (40 streams of 1228 rows of
+//                       128 bytes, lag 128: 12.0 us against 18.3 us)
+//   9 to 16 slices      half 1.40 to 2.34, all 1.05 to 2.00, twice 0.79 to 1.28 (as many above 1 as below; 32 streams of
+//                       2335 rows of 256 bytes, lag 246: 25.7 us against 44.4 us)
 //   17 to 32 slices     half 1.17 to 1.58, all 0.88 to 1.49, 1.25 times 0.74 to 1.07
 //   Eq. 16              half 0.83 to 1.55, three quarters 0.76 to 1.42, all 0.64 to 1.27
 //   Eq. 16, scores      all 1.08 to 1.77 (17 to 32 slices: half 1.00 to 1.28, all 0.85 to 1.21), 1.25 times 0.54 to 1.43
@@ -276,7 +280,7 @@ int launch_fused_any(PassArgs& a, const Norm& n, hipStream_t s) {
 // A single round of whole-slice rows: append_round_kernel, or (where it says no) decode_step_kernel if the shape
 // is one of its own, else fused_append_kernel.  The first asks for everything at once and is the shortest per
 // stream; with more than 8 row slices a lane its registers leave room for one workgroup per CU, where the others
-// keep two and more.  Gains below are time of the others over its time, cache kernels alone.
+// keep two and more.  The gains below are the others' kernel time over its own.
 bool round_is_faster(const Norm& n, const AppendArgs& a, int64_t tail) {
   if (!append_round_supported(a)) return false;
   const int slices = chunk_slices(n.D, n.esize, n.L);
@@ -284,9 +288,11 @@ bool round_is_faster(const Norm& n, const AppendArgs& a, int64_t tail) {
   // the reference rows are read twice, 256 streams of Eq. 7-8 0.83 to 0.98 and 128 streams 1.0 to 1.2
   if (n.streams <= (slices <= 16 || n.variant == LAGKV_SCORE_LOCAL ? 256 : 128)) return true;
   const bool step = decode_step_supported(a);
-  // 8 slices: Eq. 14-15 1.14 to 1.86.  decode_step_kernel asks for the rows BEHIND the reference chunk before its
-  // selection and, for Eq. 16, reads values only where kept: lag 128, rows of 256 bytes, 110 such rows, 1024
-  // streams 63 us against 70 us, Eq. 16 at 2048 streams 82 us against 91 us; with fewer rows behind 1.0 to 1.4
+  // 8 slices: Eq. 14-15 1.14 to 2.0.  decode_step_kernel asks for the rows BEHIND the reference chunk before its
+  // selection and, for Eq. 16, reads values only where kept, and its lead grows with the streams: lag 128, rows
+  // of 256 bytes, caches of 8448 rows, 110 rows behind, 4096 streams 231 us against 268 us, Eq. 16 209 us against
+  // 265 us (2048 streams equal, 512 streams 32 us against 29 us).  With an eighth of a lag behind or less, the
+  // single-round kernel 1.2 to 1.4 at 512 to 2048 streams, as long at 4096
   if (slices <= 8) return !step || (n.variant != LAGKV_SCORE_L2 && (tail - 2 * (int64_t)n.L) * 8 <= n.L);
   // 16 slices: against decode_step_kernel 0.70 to 0.94 (rows of 160 bytes, lag 200; 192 and 160; 80 and 300);
   // against fused_append_kernel from 512 streams on 0.99 to 1.20 where three quarters of the slices hold
