@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(512, 2) hold_pass_kernel(const PassArgs a) {
   const int64_t coff = (int64_t)cl * 16;
 
   // the first streams * nseg workgroups score, the rest copy sink and window rows; if there are none (see
-  // launch_hold_pass), the workgroup of a stream's last segment does, first of all
+  // edges_in_line), the workgroup of a stream does, first of all
   const int64_t streams = (int64_t)a.B * a.H, n_score = streams * a.nseg;
   const bool edge = blockIdx.x >= n_score;
   const int64_t stream = edge ? (blockIdx.x - n_score) / a.edge : stream_of(blockIdx.x / a.nseg, streams, a.order);
@@ -149,12 +149,15 @@ __global__ void __launch_bounds__(512, 2) hold_pass_kernel(const PassArgs a) {
   const float inv_D = 1.0f / (float)a.D;
   const float inv_dof = 1.0f / (float)(a.D - a.ddof);
 
-  if (edge || (a.edge == 0 && gather && seg == a.nseg - 1)) {
+  if (edge) {
     copy_edge_rows<LPR>(kin, vin, a.st, kout, vout, iout, rowbytes, S, S + a.n_s * L, S + a.n_s * k,
-                        a.T - (S + a.n_s * L), edge ? (int)((blockIdx.x - n_score) % a.edge) : 0, edge ? a.edge : 1,
-                        (int)coff, tid, nthreads);
-    if (edge) return;
+                        a.T - (S + a.n_s * L), (int)((blockIdx.x - n_score) % a.edge), a.edge, (int)coff, tid,
+                        nthreads);
+    return;
   }
+  if (__builtin_expect(a.edge == 0 && gather, 0))  // (a stream is one segment then)
+    copy_edge_rows<LPR>(kin, vin, a.st, kout, vout, iout, rowbytes, S, S + a.n_s * L, S + a.n_s * k,
+                        a.T - (S + a.n_s * L), 0, 1, (int)coff, tid, nthreads);
 
   const int64_t p0 = (int64_t)seg * a.n_s / a.nseg;
   const int64_t p1 = (int64_t)(seg + 1) * a.n_s / a.nseg;
