@@ -101,7 +101,7 @@ __device__ __forceinline__ uint32_t ordered_key(float s) {
 //   list     receives the k kept token positions, ascending (LDS)
 //   slotmap  optional [L]: output slot of a kept token, -1 otherwise (LDS)
 // Order: score descending, position ascending.  The k-th largest key is found bit by
-// bit with ballots, starting below the bits all keys share; all larger keys are kept
+// bit with ballots, starting below the bits all keys share, until exactly k keys lie above; all larger keys are kept
 // and ties with it are admitted from the lowest position up.  A prefix count over
 // (element, lane) is position order.
 template <int E, typename F>
@@ -135,6 +135,7 @@ __device__ __forceinline__ void wave_topk(KeyFn key, int L, int k, uint32_t* lis
       int cnt = 0;
       for_each_slab<E>(ne, [&](int e) { cnt += __popcll(__ballot(key(e) >= cand)); });
       if (cnt >= k) theta = cand;
+      if (cnt == k) break;  // it parts exactly k keys from the rest: no lower bit changes which
     }
   }
   int n_gt = 0;
