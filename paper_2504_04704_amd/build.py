@@ -14,6 +14,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "liblagkv.so")
 SOURCES = ["lagkv_api.hip", "split_pass.hip", "hold_pass.hip", "append_pass.hip", "staged_pass.hip",
            "chunk_f32.hip", "chunk_bf16.hip", "chunk_f16.hip",
+           "ring_f32.hip", "ring_bf16.hip", "ring_f16.hip",
            "round_f32.hip", "round_bf16.hip", "round_f16.hip", "static_scratch.hip"]
 
 HIPCC_FLAGS = [

@@ -232,6 +232,23 @@ bool use_chunk(const Norm& n, PassArgs& a, bool whole_slices) {
   a.nseg = nseg;
   return true;
 }
+// The ring kernel, in place of the streaming kernel, of the chunk kernel (`brief`) and of the register-resident
+// kernel.  The last for lags of 128 with 2-byte elements and more scored chunks than it has places, in less than a stream
+// per place: 1.02 to 1.17 up to 1.5 chunks a place (8 streams of 63 chunks, 8269 rows of 256 bytes, 19.6 us against
+// 16.8 us), above 0.93 to 1.14, the better the less evenly whole segments fill the chip; by Eq. 14-15, where that
+// kernel goes over its rows twice with nothing else on the compute unit, 1.05 to 1.15.  Other lags 0.82 to 1.0, fp32
+// 0.89 to 0.95.  Sets a.walks and a.brief where it says yes.
+bool use_ring(const Norm& n, PassArgs& a, bool brief) {
+  if (n.hint.path != LAGKV_PATH_AUTO || n.hint.waves || n.hint.nseg || n.hint.order || n.hint.sel) return false;
+  const int64_t chunks = n.streams * a.n_s;
+  if (n.variant == LAGKV_SCORE_L2 || !ring_supported(n.D, n.esize, n.L, a.st) || chunks >= (1LL << 31)) return false;
+  if (use_resident(n) && (n.L != 128 || n.esize != 2 || chunks <= 256 || n.streams >= 256)) return false;
+  const int64_t places = ring_places(n.D, n.esize, n.L);
+  if (!places || !grid_fits(places + most_edge_workgroups(a), ring_threads(n.D, n.esize, n.L))) return false;
+  a.walks = chunks < places ? chunks : places;
+  a.brief = brief;
+  return true;
+}
 int launch_chunk(PassArgs& a, hipStream_t s) { return launch_chunk_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP; }
 
 // `launch` on the streams of `a`, in one launch unless the workgroups that copy sink and window rows (one per
@@ -263,7 +280,9 @@ int launch_in_parts(const PassArgs& a, int threads, F launch, hipStream_t s) {
 
 // Launch the one-shot fused kernel.
 int launch_fused_any(PassArgs& a, const Norm& n, hipStream_t s) {
-  if (use_chunk(n, a, true)) return launch_chunk(a, s);
+  const bool brief = use_chunk(n, a, true);
+  if (use_ring(n, a, brief)) return launch_ring_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
+  if (brief) return launch_chunk(a, s);
   a.order = n.hint.order;
   a.sel = n.hint.sel;
   if (use_resident(n)) {
@@ -750,7 +769,9 @@ const char* lagkv_kernel_for(const lagkv_params* p, int64_t T) {
   fill_pass(&a, n, nullptr, nullptr, T, pl, sb, sh, st);
   alignas(16) char out[16];  // (a call with outputs; nothing is stored)
   a.K_out = a.V_out = out;
-  if (use_chunk(n, a, path != LAGKV_PATH_STAGED)) return "chunk_pass_kernel";
+  const bool whole = path != LAGKV_PATH_STAGED;
+  if (use_chunk(n, a, whole)) return "chunk_pass_kernel";
+  if (whole && use_ring(n, a, false)) return "split_pass_kernel";
   return path == LAGKV_PATH_RESIDENT ? "hold_pass_kernel" : path == LAGKV_PATH_FUSED ? "split_pass_kernel" : "staged_score_kernel";
 }
 

@@ -34,6 +34,8 @@ struct PassArgs {
   int32_t f16;         // 2-byte elements are IEEE binary16 (else bfloat16)
   int32_t ddof;
   int32_t variant;
+  int64_t walks;       // ring kernel: workgroups that share the scored chunks
+  int32_t brief;       // ... by the name it has in short calls
   int32_t nseg;        // segments each stream is cut into (one-shot kernels)
   int32_t edge;        // workgroups per stream that copy its sink and window rows, after all the others
   int32_t nwaves;      // wavefronts per workgroup (one-shot kernels)
@@ -128,6 +130,17 @@ hipError_t launch_chunk_pass(const PassArgs& a, hipStream_t s);
 hipError_t launch_chunk_f32(const PassArgs& a, hipStream_t s);
 hipError_t launch_chunk_bf16(const PassArgs& a, hipStream_t s);
 hipError_t launch_chunk_f16(const PassArgs& a, hipStream_t s);
+
+// One-shot ring kernel: rows of whole 16-byte slices on 16-byte aligned addresses, not Eq. 16.
+constexpr int kRingMaxLds = 160 * 1024;
+bool ring_supported(int D, int esize, int L, int64_t st);
+// 0: there is a faster kernel for rows of D elements and chunks of L, else the workgroups that the chip holds
+int ring_places(int D, int esize, int L);
+int ring_threads(int D, int esize, int L);
+hipError_t launch_ring_pass(const PassArgs& a, hipStream_t s);
+hipError_t launch_ring_f32(const PassArgs& a, hipStream_t s);
+hipError_t launch_ring_bf16(const PassArgs& a, hipStream_t s);
+hipError_t launch_ring_f16(const PassArgs& a, hipStream_t s);
 
 hipError_t launch_fused_append(const AppendArgs& a, hipStream_t s);
 // Single-round decode step (exactly one chunk completes; no intermediate append copy).

@@ -1,0 +1,8 @@
+// The ring kernel for bf16 (see ring_pass.hpp).
+#include "ring_pass.hpp"
+
+namespace lagkv {
+
+hipError_t launch_ring_bf16(const PassArgs& a, hipStream_t s) { return launch_ring_t<BF16>(a, s); }
+
+}  // namespace lagkv

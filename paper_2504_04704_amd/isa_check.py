@@ -30,6 +30,7 @@ from . import build as B
 WAIT_STATES = 5
 KERNEL_SOURCES = ["split_pass.hip", "hold_pass.hip", "append_pass.hip", "staged_pass.hip",
                   "chunk_f32.hip", "chunk_bf16.hip", "chunk_f16.hip",
+                  "ring_f32.hip", "ring_bf16.hip", "ring_f16.hip",
                   "round_f32.hip", "round_bf16.hip", "round_f16.hip"]
 _VMEM = re.compile(r"^(global_|buffer_|scratch_|flat_)")
 _LABEL = re.compile(r"^(_Z\w+):")
