@@ -223,6 +223,16 @@ int lagkv_append_and_compress(const lagkv_params* p, lagkv_cache* cache, const v
                               void* hip_stream);
 
 /*
+ * A prompt of T rows per stream (K, V: [B,H,T,D] with p->stride_*, 0 = dense) through the calls that
+ * lagkv_prefill_rows and lagkv_append_and_compress describe, for a caller that has all of its rows: buffers (up to the
+ * rows held), counters, capacity and workspace demands and status codes are those of the calls, made one after the
+ * other.  On an empty cache the rounds, none of which reads what another wrote, run side by side in one pass.
+ * `calls`, if not NULL, receives the number of calls that this stands for (on an error, of those that were made).
+ */
+int lagkv_prefill(const lagkv_params* p, lagkv_cache* cache, const void* K, const void* V, int64_t T,
+                  void* ws, size_t ws_bytes, void* hip_stream, int64_t* calls);
+
+/*
  * Launch override for benchmarks, tests and sweeps.  A pure function: it packs its
  * arguments into the value lagkv_params.launch carries for ONE call; the library keeps
  * nothing.  0 in any argument means "choose automatically" (and launch = 0 is the same as

@@ -243,8 +243,9 @@ bool use_ring(const Norm& n, PassArgs& a, bool brief) {
   const int64_t chunks = n.streams * a.n_s;
   if (n.variant == LAGKV_SCORE_L2 || !ring_supported(n.D, n.esize, n.L, a.st) || chunks >= (1LL << 31)) return false;
   if (use_resident(n) && (n.L != 128 || n.esize != 2 || chunks <= 256 || n.streams >= 256)) return false;
+  if (!ring_pays(n.D, n.esize, n.L)) return false;
   const int64_t places = ring_places(n.D, n.esize, n.L);
-  if (!places || !grid_fits(places + most_edge_workgroups(a), ring_threads(n.D, n.esize, n.L))) return false;
+  if (!grid_fits(places + most_edge_workgroups(a), ring_threads(n.D, n.esize, n.L))) return false;
   a.walks = chunks < places ? chunks : places;
   a.brief = brief;
   return true;
@@ -354,6 +355,14 @@ AppendWs append_ws(const Norm& n, int64_t q, int64_t rows_staged) {
   return w;
 }
 
+// What the append asks of its caller before it takes rows that are not the fused kernels' (`tail` rows behind the sink).
+bool append_ws_given(const Norm& n, int64_t q, int64_t tail, int64_t sb, int64_t sh, int64_t st, const void* ws,
+                     size_t ws_bytes) {
+  if (!staged_fits(n)) return false;
+  return told_none(n, sb, sh, st) ||
+         (ws && aligned_to(ws, 16) && ws_bytes >= append_ws(n, q, q * n.k + (tail - q * n.L)).total);
+}
+
 int hip_status(hipError_t e) { return e == hipSuccess ? LAGKV_OK : LAGKV_EHIP; }
 
 void fill_pass(PassArgs* a, const Norm& n, const void* K, const void* V, int64_t T,
@@ -379,6 +388,51 @@ void fill_pass(PassArgs* a, const Norm& n, const void* K, const void* V, int64_t
   a->variant = n.variant;
   a->nseg = 1;
   a->nwaves = 4;
+}
+
+// The new rows of an EMPTY cache in one pass, where they complete chunks: no round of the recursion reads what another
+// wrote (a chunk is scored against the raw rows behind it), so all of them run side by side through the one-shot
+// kernels, whose outputs go straight to their places in the cache (T_out is the distance from one stream's to the
+// next's).  Only kernels that subtract as exactly as the single-round kernels these calls otherwise go to; LAGKV_ESHAPE
+// where there is none, or where rows and cache overlap.
+int fill_empty_cache(const Norm& n, lagkv_cache* c, const void* K, const void* V, int64_t T, int64_t sb, int64_t sh,
+                     int64_t st, hipStream_t s) {
+  lagkv_plan_t pl;
+  plan_of(n, T, n.S, &pl);
+  if (pl.n_scored < 1 || c->n_seen || c->n_static || c->n_tail) return LAGKV_ESHAPE;
+  if (n.hint.path != LAGKV_PATH_AUTO || n.hint.waves || n.hint.nseg || n.hint.order || n.hint.sel) return LAGKV_ESHAPE;
+  const int64_t held = n.streams * c->capacity * n.rowbytes, span = (n.B - 1) * sb + (n.H - 1) * sh + (T - 1) * st + n.rowbytes;
+  for (const void* from : {K, V})
+    for (const void* to : {c->K, c->V})
+      if ((const char*)from < (const char*)to + held && (const char*)to < (const char*)from + span) return LAGKV_ESHAPE;
+  PassArgs a;
+  fill_pass(&a, n, K, V, T, pl, sb, sh, st);
+  a.K_out = (char*)c->K;
+  a.V_out = (char*)c->V;
+  a.idx_out = c->pos;
+  a.T_out = c->capacity;
+  const bool whole = shape_fused(n, sb, sh, st) && fused_fits(n) &&
+                     fused_supported(n.D, n.esize, sb, sh, st, K, V, c->K, c->V);
+  const int64_t chunks = n.streams * pl.n_scored;
+  int rc = LAGKV_ESHAPE;
+  if (whole && n.variant != LAGKV_SCORE_L2 && ring_supported(n.D, n.esize, n.L, st) && chunks < (1LL << 31)) {
+    const int64_t places = ring_places(n.D, n.esize, n.L);
+    a.walks = chunks < places ? chunks : places;
+    a.brief = use_chunk(n, a, true);
+    if (grid_fits(a.walks + most_edge_workgroups(a), ring_threads(n.D, n.esize, n.L)))
+      rc = launch_ring_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
+  } else if (use_chunk(n, a, whole && n.variant == LAGKV_SCORE_L2)) {
+    rc = launch_chunk(a, s);
+  } else if (whole && (n.variant == LAGKV_SCORE_L2 || !chunk_supported(n.D, n.esize, n.L, st))) {
+    a.nwaves = split_nw(n);  // (which takes its means as the general append kernel does)
+    a.nseg = pick_segments_split(n, a.n_s, a.nwaves);
+    rc = launch_in_parts(a, 64 * a.nwaves, launch_split_pass, s);
+  }
+  if (rc != LAGKV_OK) return rc;
+  c->n_seen = T;
+  c->n_static = n.S + (int64_t)n.k * pl.n_scored;
+  c->n_tail = pl.T_out - c->n_static;
+  return LAGKV_OK;
 }
 
 }  // namespace
@@ -613,6 +667,10 @@ int lagkv_append_and_compress(const lagkv_params* p, lagkv_cache* c, const void*
   const bool fused_ok = shape_fused(n, sb, sh, st) && fused_fits(n) &&
                         fused_supported(n.D, n.esize, sb, sh, st, c->K, c->V, K_new, V_new);
   if ((force == LAGKV_PATH_FUSED || force == LAGKV_PATH_RESIDENT) && !fused_ok) return LAGKV_ESHAPE;
+  if (q > 1 && total == n_new && (fused_ok || append_ws_given(n, q, tail, sb, sh, st, ws, ws_bytes))) {
+    rc = fill_empty_cache(n, c, K_new, V_new, n_new, sb, sh, st, s);
+    if (rc != LAGKV_ESHAPE) return rc;
+  }
   hipError_t e = hipSuccess;
   AppendArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -722,6 +780,44 @@ int lagkv_append_and_compress(const lagkv_params* p, lagkv_cache* c, const void*
   c->n_seen += n_new;
   c->n_static = base + q * n.k;
   c->n_tail = tail - q * n.L;
+  return LAGKV_OK;
+}
+
+int lagkv_prefill(const lagkv_params* p, lagkv_cache* c, const void* K, const void* V, int64_t T, void* ws,
+                  size_t ws_bytes, void* hip_stream, int64_t* calls) {
+  if (calls) *calls = 0;
+  Norm n;
+  int rc = validate(p, &n);
+  if (rc != LAGKV_OK) return rc;
+  if (!c || !c->K || !c->V || T < 0 || (T > 0 && (!K || !V))) return LAGKV_EINVAL;
+  if (T == 0) return LAGKV_OK;
+  int64_t sb, sh, st;
+  rc = strides_of(p, n, T, &sb, &sh, &st);
+  if (rc != LAGKV_OK) return rc;
+  // the rows that the longest of the calls would hold: S + 2L, then k more with every lag, or the last, partial one
+  const int64_t first = n.S + 2 * (int64_t)n.L, full = (T - first) / n.L, rem = (T - first) % n.L;
+  if (T >= first && T <= kMaxRows && c->capacity <= kMaxRows && c->capacity >= first + full * n.k &&
+      c->capacity >= n.S + (full + 1) * n.k + n.L + rem && aligned_to(K, n.esize) && aligned_to(V, n.esize) &&
+      aligned_to(c->K, n.esize) && aligned_to(c->V, n.esize)) {
+    const bool fused_ok = shape_fused(n, sb, sh, st) && fused_fits(n) &&
+                          fused_supported(n.D, n.esize, sb, sh, st, c->K, c->V, K, V);
+    if (fused_ok || append_ws_given(n, 1, 2 * (int64_t)n.L, sb, sh, st, ws, ws_bytes)) {
+      rc = fill_empty_cache(n, c, K, V, T, sb, sh, st, (hipStream_t)hip_stream);
+      if (rc == LAGKV_OK && calls) *calls = 1 + full + (rem > 0);
+      if (rc != LAGKV_ESHAPE) return rc;
+    }
+  }
+  lagkv_params q = *p;
+  q.stride_b = sb / n.esize;
+  q.stride_h = sh / n.esize;
+  q.stride_t = st / n.esize;
+  for (int64_t t = 0; t < T;) {
+    const int64_t rows = lagkv_prefill_rows(&q, c, T - t);
+    rc = lagkv_append_and_compress(&q, c, (const char*)K + t * st, (const char*)V + t * st, rows, ws, ws_bytes, hip_stream);
+    if (rc != LAGKV_OK) return rc;
+    t += rows;
+    if (calls) ++*calls;
+  }
   return LAGKV_OK;
 }
 

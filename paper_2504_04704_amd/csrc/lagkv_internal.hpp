@@ -26,7 +26,7 @@ struct PassArgs {
   float* scores;    // dense [streams, n_s*L] or nullptr
   int64_t sb, sh, st;  // input strides (bytes) of batch, head, row
   int64_t T;           // input rows per stream
-  int64_t T_out;       // output rows per stream
+  int64_t T_out;       // output rows per stream, or the rows from one stream's outputs to the next's
   int64_t n_s;         // scored chunks per stream (>= 1)
   int32_t B, H, D;
   int32_t S, L, k;
@@ -134,7 +134,8 @@ hipError_t launch_chunk_f16(const PassArgs& a, hipStream_t s);
 // One-shot ring kernel: rows of whole 16-byte slices on 16-byte aligned addresses, not Eq. 16.
 constexpr int kRingMaxLds = 160 * 1024;
 bool ring_supported(int D, int esize, int L, int64_t st);
-// 0: there is a faster kernel for rows of D elements and chunks of L, else the workgroups that the chip holds
+// For supported shapes: it is the faster one against the streaming kernel; workgroups that the chip holds; threads of each.
+bool ring_pays(int D, int esize, int L);
 int ring_places(int D, int esize, int L);
 int ring_threads(int D, int esize, int L);
 hipError_t launch_ring_pass(const PassArgs& a, hipStream_t s);

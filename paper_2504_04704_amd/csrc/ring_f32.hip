@@ -16,7 +16,8 @@ bool ring_supported(int D, int esize, int L, int64_t st) {
 //                                    0.85 1.07 to 1.36, 0.9 and more 1.04 to 1.35; fp32 1.12 to 1.46 from 0.62 on
 //   32 slices, 2-byte elements       0.57 0.93, 0.62 1.01 to 1.20, 0.75 and more 1.02 to 1.36
 //   32 slices, fp32                  0.62 0.94, 0.70 1.00, 0.95 and more 1.06 to 1.22
-static bool ring_pays(const RingShape& f, int D, int esize, int L) {
+bool ring_pays(int D, int esize, int L) {
+  const RingShape f = ring_shape(D, esize, L);
   if (f.gw < 8 && f.nsl == 8) return true;
   const int lpr = chunk_lpr(D * esize), R = f.gw * (kWave / lpr), steps = ((L + R - 1) / R + 1) & ~1;
   const int64_t filled = (int64_t)L * row_units(D, esize) * 100 / ((int64_t)steps * R * lpr);
@@ -28,7 +29,6 @@ int ring_threads(int D, int esize, int L) { return ring_shape(D, esize, L).gw * 
 
 int ring_places(int D, int esize, int L) {
   const RingShape f = ring_shape(D, esize, L);
-  if (f.gw == 0 || !ring_pays(f, D, esize, L)) return 0;
   const int lds = kRingMaxLds / ring_lds(D, esize, L, f.nsl, f.gw).total, regs = (f.nsl == 8 ? 16 : 8) / (2 * f.gw);
   return 256 * (lds < regs ? lds : regs);
 }

@@ -30,7 +30,7 @@ SELECT_AUTO, SELECT_WAVE, SELECT_GROUP = 0, 1, 2
 EXPORTS = ("lagkv_plan", "lagkv_keep_for_compression", "lagkv_workspace_bytes", "lagkv_score",
            "lagkv_select", "lagkv_compress", "lagkv_compress_static", "lagkv_cache_after_compress",
            "lagkv_prefill_rows",
-           "lagkv_append_and_compress", "lagkv_launch_hint", "lagkv_launch_hint_ex", "lagkv_path_for",
+           "lagkv_append_and_compress", "lagkv_prefill", "lagkv_launch_hint", "lagkv_launch_hint_ex", "lagkv_path_for",
            "lagkv_kernel_for", "lagkv_strerror",
            "lagkv_version")
 
@@ -97,6 +97,8 @@ def load():
     lib.lagkv_cache_after_compress.restype = C.c_int
     lib.lagkv_prefill_rows.argtypes = [C.POINTER(Params), C.POINTER(CacheT), i64]
     lib.lagkv_prefill_rows.restype = C.c_int64
+    lib.lagkv_prefill.argtypes = [C.POINTER(Params), C.POINTER(CacheT), vp, vp, i64, vp, sz, vp, C.POINTER(i64)]
+    lib.lagkv_prefill.restype = C.c_int
     lib.lagkv_launch_hint.argtypes = [C.c_int, C.c_int, C.c_int]
     lib.lagkv_launch_hint.restype = C.c_int32
     lib.lagkv_launch_hint_ex.argtypes = [C.c_int] * 5
@@ -404,6 +406,11 @@ class Cache:
             got = self._prepared[key] = (p, C.byref(p), workspace_bytes(p, self.K.shape[2]))
         return got
 
+    def _workspace(self, need: int) -> Optional[torch.Tensor]:
+        if need > 0 and (self._ws is None or self._ws.numel() < need):
+            self._ws = torch.empty(need, dtype=torch.uint8, device=self.K.device)
+        return self._ws
+
     def append_and_compress(self, K_new: Optional[torch.Tensor], V_new: Optional[torch.Tensor]) -> None:
         K = self.K
         if K_new is None:
@@ -416,9 +423,7 @@ class Cache:
                 raise ValueError("K_new must be [B,H,n_new,D] of the cache dtype")
             n_new, strides = shape[2], strides[:3]
         p, ref, need = self._prepare(strides)
-        ws = self._ws
-        if need and (ws is None or ws.numel() < need):
-            ws = self._ws = torch.empty(need, dtype=torch.uint8, device=K.device)
+        ws = self._workspace(need) if need else self._ws
         _check(load().lagkv_append_and_compress(
             ref, C.byref(self.c), _ptr(K_new), _ptr(V_new), n_new, _ptr(ws),
             0 if ws is None else ws.numel(), _stream_ptr(K.device)),
@@ -428,9 +433,20 @@ class Cache:
         """Chunk-by-chunk compression during prefill (Ablation, subsection on the prefill
         stage): the first S + 2L rows in one call, then L rows per call until all rows
         are in; every call is lagkv_append_and_compress.  The model forward that would produce
-        each slice between the calls is the caller's; here the rows are given.  Returns the
-        number of calls made."""
-        T = K.shape[2]
+        each slice between the calls is the caller's; here the rows are given, and
+        lagkv_prefill makes the calls, or on an empty cache one pass in their place.  Returns the
+        number of calls."""
+        T, have = K.shape[2], self.K.shape
+        strides = K.stride()
+        if T and isinstance(V, torch.Tensor) and K.shape == (have[0], have[1], T, have[3]) and strides[3] == 1 \
+                and 0 not in strides and (V.shape, V.stride(), V.dtype, V.device) == (K.shape, strides, K.dtype, K.device) \
+                and (K.dtype, K.device) == (self.K.dtype, self.K.device):
+            _, ref, need = self._prepare(strides[:3])
+            calls = C.c_int64()
+            _check(load().lagkv_prefill(ref, C.byref(self.c), K.data_ptr(), V.data_ptr(), T, _ptr(self._workspace(need)), need,
+                                        _stream_ptr(self.K.device), C.byref(calls)), "lagkv_append_and_compress")
+            return calls.value
+        # (what is wrong with the rows is said by the call that meets it, as the calls before it have been made)
         p = self._params()
         calls, t = 0, 0
         while t < T:

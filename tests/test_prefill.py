@@ -1,0 +1,110 @@
+"""GPU: a prompt whose rows are all there - lagkv_prefill, and an append of a whole prompt to an empty cache - against the
+calls it stands for, made one by one."""
+import pytest
+import torch
+
+from paper_2504_04704_amd import lagkv
+from tests.test_gpu_parity import gen, say
+
+pytestmark = pytest.mark.gpu
+
+
+def by_chunks(cache, K, V):
+    """The calls themselves; returns how many."""
+    S, L, T = cache.S, cache.L, K.shape[2]
+    cuts = [0, *range(S + 2 * L, T, L), T] if T > S + 2 * L else [0, T]
+    for a, b in zip(cuts, cuts[1:]):
+        cache.append_and_compress(K[:, :, a:b], V[:, :, a:b])
+    return len(cuts) - 1
+
+
+def state(c):
+    return c.n_static, c.n_tail, c.n_seen
+
+
+def same(a, b):
+    assert state(a) == state(b)
+    bits = {2: torch.int16, 4: torch.int32}[a.K.dtype.itemsize]
+    for x, y in zip(a.view(), b.view()):
+        if x is not None:
+            x, y = (t.contiguous().view(bits) if t.dtype != torch.int32 else t for t in (x, y))
+            # the scores of the two may differ by an ulp: of a few thousand chunks one may keep another token
+            assert (x != y).sum() <= 2e-3 * x.numel()
+
+
+# B, H, D, dtype, S, L, chunks, remainder: the ring kernel, the chunk kernel (rows of partial slices), the streaming
+# kernel (longer lags), the calls themselves (2-byte rows of an odd number of elements; a lag of 700 of such rows)
+FORMS = [
+    (2, 3, 128, torch.bfloat16, 16, 128, 9, 5), (1, 1, 64, torch.float32, 0, 64, 2, 0), (4, 8, 128, torch.bfloat16, 33, 256, 6, 255),
+    (1, 5, 80, torch.float16, 4, 100, 7, 1), (1, 4, 256, torch.bfloat16, 1, 256, 4, 0), (1, 700, 32, torch.bfloat16, 2, 40, 4, 39),
+    (2, 3, 100, torch.bfloat16, 16, 128, 8, 3), (1, 2, 33, torch.float32, 5, 300, 4, 7),
+    (1, 3, 128, torch.bfloat16, 16, 1024, 3, 11), (1, 2, 42, torch.float32, 3, 700, 3, 0), (1, 2, 25, torch.bfloat16, 2, 50, 5, 0),
+]
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
+@pytest.mark.parametrize("form", FORMS, ids=lambda f: f"B{f[0]}H{f[1]}D{f[2]}L{f[5]}")
+def test_prefill_is_its_calls(form, variant):
+    B, H, D, dtype, S, L, n, m = form
+    say("prefill", form, "variant", variant)
+    T = S + n * L + m
+    K, V = gen(B, H, T, D, dtype, seed=D + L)
+    need = S + 2 * L + (L // 4) * max(0, n - 2) + m      # the longest of the calls holds at most this
+    for layout in ("bhtd", "bthd"):
+        if layout == "bthd":
+            K, V = (x.transpose(1, 2).contiguous().transpose(1, 2) for x in (K, V))
+        one, many = (lagkv.Cache(B, H, D, need + L, S, L, 0.25, dtype, variant=variant, track_positions=layout == "bhtd")
+                     for _ in range(2))
+        calls = by_chunks(many, K, V)
+        assert one.prefill_chunked(K, V) == calls
+        same(one, many)
+        # ... on a cache that holds a prompt already, and from a partly filled sink on
+        assert one.prefill_chunked(K[:, :, :L + 1], V[:, :, :L + 1]) == 2
+        for a, b in [(0, L), (L, L + 1)]:
+            many.append_and_compress(K[:, :, a:b], V[:, :, a:b])
+        same(one, many)
+        whole = lagkv.Cache(B, H, D, T, S, L, 0.25, dtype, variant=variant)
+        whole.append_and_compress(K, V)
+        torch.cuda.synchronize()
+        want = lagkv.Cache(B, H, D, T, S, L, 0.25, dtype, variant=variant)
+        by_chunks(want, K, V)
+        same(whole, want)
+
+
+@pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (50, torch.bfloat16)])
+def test_room_for_the_longest_call_is_demanded(D, dtype):
+    """One row too few for the longest of the calls: the calls before it have been made, as one by one."""
+    S, L, k = 3, 64, 16
+    for n, m in [(2, 0), (4, 0), (4, 63), (6, 1), (1, 5)]:
+        T = S + n * L + m
+        K, V = gen(1, 3, T, D, dtype, seed=n)
+        full = max(0, n - 2)
+        room = max(S + 2 * L + full * k, S + (full + 1) * k + L + m if m else 0) if n >= 2 else T
+        for cap in (room, room - 1):
+            say("prefill room", D, n, m, cap)
+            one, many = (lagkv.Cache(1, 3, D, cap, S, L, 0.25, dtype) for _ in range(2))
+            if cap == room:
+                one.prefill_chunked(K, V), by_chunks(many, K, V)
+            else:
+                for c, f in ((one, one.prefill_chunked), (many, lambda k_, v_: by_chunks(many, k_, v_))):
+                    with pytest.raises(lagkv.LagKVError) as e:
+                        f(K, V)
+                    assert e.value.status == lagkv.ECAPACITY
+            same(one, many)
+
+
+def test_rows_in_the_cache_itself_and_bad_rows():
+    """Rows that lie in the cache's own buffers go through the calls; rows of another type or shape are refused as by them."""
+    S, L, T = 2, 32, 2 + 6 * 32
+    K, V = gen(1, 2, T, 64, torch.bfloat16, seed=1)
+    one, many = (lagkv.Cache(1, 2, 64, 3 * T, S, L, 0.25) for _ in range(2))
+    for c in (one, many):
+        c.K[:, :, 2 * T:], c.V[:, :, 2 * T:] = K, V
+    one.prefill_chunked(one.K[:, :, 2 * T:], one.V[:, :, 2 * T:])
+    by_chunks(many, many.K[:, :, 2 * T:], many.V[:, :, 2 * T:])
+    same(one, many)
+    c = lagkv.Cache(1, 2, 64, T, S, L, 0.25)
+    for k, v in [(K.half(), V.half()), (K[:, :1], V[:, :1]), (K, V[:, :, ::2]), (K[0], V[0]), (K[..., :32], V[..., :32])]:
+        with pytest.raises(ValueError):
+            c.prefill_chunked(k, v)
+    assert state(c) == (0, 0, 0) and c.prefill_chunked(K[:, :, :0], V[:, :, :0]) == 0
