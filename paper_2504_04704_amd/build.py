@@ -12,6 +12,7 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "liblagkv.so")
+BINDING_PATH = os.path.join(PKG_DIR, "_lagkv_native.so")
 SOURCES = ["lagkv_api.hip", "split_pass.hip", "hold_pass.hip", "append_pass.hip", "staged_pass.hip",
            "chunk_f32.hip", "chunk_bf16.hip", "chunk_f16.hip",
            "ring_f32.hip", "ring_bf16.hip", "ring_f16.hip",
@@ -61,5 +62,25 @@ def build_library(verbose: bool = True, extra_flags=(), out_path: str = LIB_PATH
     return out_path
 
 
+def build_binding(verbose: bool = True, out_path: str = BINDING_PATH) -> str:
+    """Compile csrc/binding.cpp (host code only, against torch's headers) into
+    paper_2504_04704_amd/_lagkv_native.so; returns its path."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        raise RuntimeError("g++ not found")
+    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    _run([cxx, "-O2", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+          *(x for i in inc for x in ("-isystem", i)), os.path.join(CSRC, "binding.cpp"), "-o", out_path + ".tmp",
+          "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python", f"-Wl,-rpath,{lib}"], verbose)
+    os.replace(out_path + ".tmp", out_path)
+    return out_path
+
+
 if __name__ == "__main__":
     build_library(extra_flags=sys.argv[1:])
+    build_binding()

@@ -19,6 +19,7 @@ import torch
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "liblagkv.so")
 _lib = None
+_native = None  # csrc/binding.cpp, once the library is loaded (None where it is not built: the ctypes calls below do the same)
 
 OK, EINVAL, ESHAPE, EDTYPE, ECAPACITY, EWORKSPACE, EHIP = range(7)
 F32, BF16, F16 = 0, 1, 2
@@ -67,7 +68,7 @@ def lib_path() -> str:
 
 def load():
     """Load liblagkv.so (built by paper_2504_04704_amd.build / __graft_entry__.build)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -112,7 +113,19 @@ def load():
     lib.lagkv_version.argtypes = []
     lib.lagkv_version.restype = C.c_int
     _lib = lib
+    _native = _load_native(lib)
     return lib
+
+
+def _load_native(lib):
+    try:
+        from . import _lagkv_native
+    except ImportError:
+        return None
+    _lagkv_native.init(*(C.cast(f, C.c_void_p).value for f in (lib.lagkv_plan, lib.lagkv_workspace_bytes, lib.lagkv_compress,
+                                                              lib.lagkv_append_and_compress)),
+                       torch._C._cuda_getCurrentRawStream)
+    return _lagkv_native
 
 
 def strerror(status: int) -> str:
@@ -286,6 +299,10 @@ def compress(K: torch.Tensor, V: torch.Tensor, S: int, L: int, r: float, variant
              idx_out: Optional[torch.Tensor] = None, scores_out: Optional[torch.Tensor] = None,
              ws: Optional[torch.Tensor] = None, launch: int = 0) -> Compressed:
     """lagkv_compress: one whole pass.  Output buffers may be passed in (benchmarks)."""
+    if _native is not None and out is None and idx_out is None and scores_out is None and ws is None:
+        got = _native.compress(K, V, S, L, r, variant, std_ddof, launch, want_idx, want_scores)
+        if got is not None:
+            return Compressed(got[0], got[1], got[2], got[3], PlanT.from_buffer_copy(got[4]))
     if not K.is_cuda:
         raise RuntimeError("lagkv.compress needs device tensors; there is no CPU path")
     _same_layout(K, V)
@@ -413,6 +430,12 @@ class Cache:
 
     def append_and_compress(self, K_new: Optional[torch.Tensor], V_new: Optional[torch.Tensor]) -> None:
         K = self.K
+        if _native is not None:
+            rc = _native.append(self.c, K, self.S, self.L, self.r, self.variant, self.std_ddof, self.launch, self._ws, K_new, V_new)
+            if rc == OK:
+                return
+            if rc > 0:
+                raise LagKVError(rc, "lagkv_append_and_compress")
         if K_new is None:
             n_new, strides = 0, (0, 0, 0)
         else:
