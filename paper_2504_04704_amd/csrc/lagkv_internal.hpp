@@ -134,8 +134,10 @@ hipError_t launch_chunk_f16(const PassArgs& a, hipStream_t s);
 // One-shot ring kernel: rows of whole 16-byte slices on 16-byte aligned addresses, not Eq. 16.
 constexpr int kRingMaxLds = 160 * 1024;
 bool ring_supported(int D, int esize, int L, int64_t st);
-// For supported shapes: it is the faster one against the streaming kernel; workgroups that the chip holds; threads of each.
+// For supported shapes: it is the faster one against the streaming kernel; it reads every row once; workgroups that
+// the chip holds; threads of each.
 bool ring_pays(int D, int esize, int L);
+bool ring_holds(int D, int esize, int L);
 int ring_places(int D, int esize, int L);
 int ring_threads(int D, int esize, int L);
 hipError_t launch_ring_pass(const PassArgs& a, hipStream_t s);

@@ -111,15 +111,25 @@ __device__ __forceinline__ void lds_drain() { asm volatile("s_waitcnt lgkmcnt(0)
 #ifndef LAGKV_DMA16_FLAGS
 #define LAGKV_DMA16_FLAGS "nt"
 #endif
+template <bool NT = true>  // false: the rows are read again
 __device__ __forceinline__ void dma_rows16(uint32_t lane_off, const char* sbase, uint32_t lds_addr) {
   uint64_t base;  // (see sgpr_base_note below; the copy is also the wait state after the write of M0)
-  asm volatile(
-      "s_mov_b32 m0, %3\n\t"
-      "s_mov_b64 %0, %2\n\t"
-      "global_load_lds_dwordx4 %1, %0 " LAGKV_DMA16_FLAGS
-      : "=&s"(base)
-      : "v"(lane_off), "s"(sbase), "s"(lds_addr)
-      : "memory");
+  if constexpr (NT)
+    asm volatile(
+        "s_mov_b32 m0, %3\n\t"
+        "s_mov_b64 %0, %2\n\t"
+        "global_load_lds_dwordx4 %1, %0 " LAGKV_DMA16_FLAGS
+        : "=&s"(base)
+        : "v"(lane_off), "s"(sbase), "s"(lds_addr)
+        : "memory");
+  else
+    asm volatile(
+        "s_mov_b32 m0, %3\n\t"
+        "s_mov_b64 %0, %2\n\t"
+        "global_load_lds_dwordx4 %1, %0"
+        : "=&s"(base)
+        : "v"(lane_off), "s"(sbase), "s"(lds_addr)
+        : "memory");
 }
 // ... at a compile-time byte offset from lds_addr
 template <int OFF>

@@ -30,8 +30,9 @@
 
 namespace lagkv {
 
-// Ring slots (1 KiB steps) per wavefront: a whole chunk, or half of one where a lane holds more than 16 slices.
-__host__ __device__ constexpr int ring_slots(int nsl) { return nsl < 16 ? nsl : 16; }
+// Ring slots (1 KiB steps) per wavefront: a whole chunk, or half of one where a lane holds 32 slices; six or
+// eight where it holds none (nsl = 0: chunks that do not fit).
+__host__ __device__ constexpr int ring_slots(int nsl, int gw) { return nsl == 32 ? 16 : nsl == 0 && gw == 4 ? 6 : 8; }
 
 struct RingLds {
   int off_vK, off_vV, off_slot, off_ref, off_stat, off_ring, total;  // bytes
@@ -42,11 +43,12 @@ __host__ __device__ inline RingLds ring_lds(int D, int esize, int L, int nsl, in
   const int lp = chunk_pad(L);
   l.off_vK = 0;
   l.off_vV = lp * 4;
-  l.off_slot = 2 * lp * 4;                     // int32 [L]: where the row goes, in bytes from the first kept row of its chunk, or -1
-  l.off_ref = 3 * lp * 4;                      // float [K|V][mn|iv][D], then zeros for lanes without channels
-  l.off_stat = l.off_ref + (4 * D + 8) * 4;    // elements as in the rows: [wave][mn|mx][D]
+  l.off_slot = 2 * lp * 4;                     // nsl = 0: uint32 [k]: the kept rows; else int32 [L]: where the row goes, in bytes from the first kept row of its chunk, or -1
+  l.off_ref = 3 * lp * 4;                      // float [K|V][mn|iv][D], then eight zeros for lanes without channels
+  const int full = (D * esize & (D * esize - 1)) == 0 && D * esize >= 64;  // no lane without channels
+  l.off_stat = l.off_ref + (4 * D + (full ? 0 : 8)) * 4;  // elements as in the rows: [wave][mn|mx][D]
   l.off_ring = (l.off_stat + 2 * gw * 2 * D * esize + 127) & ~127;
-  l.total = l.off_ring + 2 * gw * ring_slots(nsl) * 1024;
+  l.total = l.off_ring + 2 * gw * ring_slots(nsl, gw) * 1024;
   return l;
 }
 
@@ -163,7 +165,8 @@ __device__ __forceinline__ float token_var_pair(const float (&x0)[VEC], const fl
 
 // Chunk softmax, K+V sum and top-k (Eq. 10-11) by one wavefront, L <= 64 * E tokens in registers; arguments as
 // group_rank_select's (wg_select.hpp), but the slot map receives byte offsets of rows.
-template <int E>
+// LIST: it receives the k kept rows instead.
+template <int E, bool LIST>
 __device__ __forceinline__ void wave_pick(const float* vK, const float* vV, int L, int k, bool do_select, float* gout,
                                           int32_t* slotmap, int lane, int32_t* pos_out, uint32_t pos0, uint32_t rowbytes) {
   float eK[E], eV[E];
@@ -227,7 +230,11 @@ __device__ __forceinline__ void wave_pick(const float* vK, const float* vV, int 
     const bool keep = key[e] > theta || (key[e] == theta && t < L && prefix_popc(eq) < need);
     const uint64_t km = __ballot(keep);
     const int slot = base + prefix_popc(km);
-    if (t < L) slotmap[t] = keep ? (int)__umul24((uint32_t)slot, rowbytes) : -1;
+    if constexpr (LIST) {
+      if (keep) slotmap[slot] = t;
+    } else if (t < L) {
+      slotmap[t] = keep ? (int)__umul24((uint32_t)slot, rowbytes) : -1;
+    }
     if (keep && pos_out) st4_out_at(pos_out, (uint32_t)slot * 4u, pos0 + (uint32_t)t);
     base += __popcll(km);
     need -= __popcll(eq);
@@ -239,8 +246,9 @@ __device__ __forceinline__ void wave_pick(const float* vK, const float* vV, int 
 // the highest number down.
 template <typename ET, int LPR, int NSL, int GW>
 __device__ __forceinline__ void ring_pass(const PassArgs& a) {
-  constexpr int VEC = ET::VEC, ESIZE = 16 / VEC, RPW = kWave / LPR, R = GW * RPW, NR = ring_slots(NSL);
+  constexpr int VEC = ET::VEC, ESIZE = 16 / VEC, RPW = kWave / LPR, R = GW * RPW, NR = ring_slots(NSL, GW);
   constexpr int THREADS = GW * 2 * kWave;
+  constexpr bool HOLD = NSL > 0;  // else a chunk passes through the ring only
   typedef Stat<ET> ST;
   extern __shared__ float4 lds_raw[];
   char* lds = reinterpret_cast<char*>(lds_raw);
@@ -297,20 +305,24 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
     return tbase + (int64_t)b * a.sb + (int64_t)h * a.sh + (S + (int64_t)q * L) * a.st;
   };
   // An item is a chunk to be scored, or (Eq. 7-8) the first reference of a share or of a stream in it.
-  bool ref = !local;
-  const char* cur = chunk_at(stream, p + (ref ? 1 : 0));
+  // Where the chunk does not stay in registers, its own statistics (Eq. 14-15) are an item before it.
+  bool ref = !HOLD || !local;
+  const char* cur = chunk_at(stream, p + (local ? 0 : 1));
   auto dma = [&](const char* base, auto tag) __attribute__((always_inline)) {
     constexpr int j = decltype(tag)::value;
     const uint32_t off = lane_off + (uint32_t)(j * R) * st;
-    dma_rows16_at<(j % NR) * 1024>(off < lane_max ? off : lane_max, base, ring_base);
+    if constexpr (HOLD) dma_rows16_at<(j % NR) * 1024>(off < lane_max ? off : lane_max, base, ring_base);
+    else dma_rows16<false>(off < lane_max ? off : lane_max, base, ring_base + (j % NR) * 1024u);
   };
   ring_for<0, NR, 1>([&](auto tag) __attribute__((always_inline)) {
     if (decltype(tag)::value < n) dma(cur, tag);
   });
-  if (tid < 8) refbuf[4 * D + tid] = 0.f;
-  for (int t = L + tid; t < chunk_pad(L); t += THREADS) slotmap[t] = -1;  // rows past the end are never stored
+  if (tid < 8 && rowbytes < LPR * 16) refbuf[4 * D + tid] = 0.f;
+  if constexpr (HOLD)
+    for (int t = L + tid; t < chunk_pad(L); t += THREADS) slotmap[t] = -1;  // rows past the end are never stored
+  uint32_t at = 0;  // !HOLD: byte offset of the next step's slot
 
-  uint4 hold[NSL];
+  uint4 hold[HOLD ? NSL : 1];
   TStats<VEC> acc;
   float mn[VEC], iv[VEC];
   // the wavefront's minima and maxima -> statbuf
@@ -370,20 +382,51 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
     const bool more = ref || left > 1;
     const bool turn = !ref && p == 0;  // this stream's share ends
     int nstream = stream, np = p - (ref ? 0 : 1);
-    bool nref = false;
-    const char* next = cur - (int64_t)L * a.st;
+    const bool split_item = !HOLD && local;  // every chunk is two items
+    bool nref = split_item && !ref;
+    const char* next = split_item && ref ? cur : cur - (int64_t)L * a.st;
     if (turn && more) {
       nstream = stream - 1;
       np = (int)n_s - 1;
-      nref = !local;
-      next = chunk_at(nstream, np + (nref ? 1 : 0));
+      nref = !HOLD || !local;
+      next = chunk_at(nstream, np + (local ? 0 : 1));
     }
-    const bool stats = ref || local || (more && !turn);  // its minima and maxima are wanted
-    const bool score = !ref && !local;
+    const bool score = !ref && !(HOLD && local);
+    // its minima and maxima are wanted
+    const bool stats = ref || (HOLD && local) || (!local && more && !turn);
     acc.reset();
     // Steps j and j + 1 have landed once no more operations are outstanding than loads were issued behind them: the
     // rest of the item's and, if there is one, the next item's as far as it has been asked for.
-    if (!more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (HOLD && !more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (!HOLD) {
+      for (int j = 0; j < n; j += 2) {
+        // as many loads as slots are under way, until nothing is left to ask for
+        if (more || j + NR <= n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NR - 2) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        u32x4 qa, qb;
+        lds_read_pair_at<0, 1024>(qa, qb, ring_lane + at);
+        const int ja = j + NR;  // (no wavefront with rows has fewer than NR steps)
+        if (more || ja < n) {
+          const char* base = ja < n ? cur : next;
+          const uint32_t step = (uint32_t)((ja < n ? ja : ja - n) * R) * st;
+          const uint32_t o0 = lane_off + step, o1 = o0 + (uint32_t)R * st;
+          dma_rows16<false>(o0 < lane_max ? o0 : lane_max, base, ring_base + at);
+          dma_rows16<false>(o1 < lane_max ? o1 : lane_max, base, ring_base + at + 1024u);
+        }
+        at = at == (NR - 2) * 1024u ? 0u : at + 2048u;
+        float x0[VEC], x1[VEC];
+        unpack<ET>(make_uint4(qa.x, qa.y, qa.z, qa.w), x0);
+        unpack<ET>(make_uint4(qb.x, qb.y, qb.z, qb.w), x1);
+        if (stats) {
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) {
+            acc.mn[i] = fminf(fminf(acc.mn[i], x0[i]), x1[i]);
+            acc.mx[i] = fmaxf(fmaxf(acc.mx[i], x0[i]), x1[i]);
+          }
+        }
+        if (score) score_pair(x0, x1, j);
+      }
+    }
     ring_for<0, NSL, 2>([&](auto tag) __attribute__((always_inline)) {
       constexpr int j = decltype(tag)::value;
       if (j < n) {
@@ -426,14 +469,14 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
       __builtin_amdgcn_sched_barrier(0);
     });
     if (stats) park();
-    if (ref || local) {
+    if (ref || (HOLD && local)) {
       lds_barrier();
       publish();
       lds_barrier();
       take_ref();
     }
     if (!ref) {
-      if (local) {
+      if (HOLD && local) {
 #pragma unroll
         for (int j = 0; j < NSL; j += 2) {
           if (j < n) {
@@ -458,14 +501,31 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
         int32_t* gp = gather && a.idx_out ? a.idx_out + out : nullptr;
         const int ln = here_v(lane), Ls = here_s(L), ks = here_s(k);
         const uint32_t pos0 = (uint32_t)(S + p * L), rb = (uint32_t)rowbytes;
-        if (Ls <= 64) wave_pick<1>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
-        else if (Ls <= 128) wave_pick<2>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
-        else if (Ls <= 256) wave_pick<4>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
-        else wave_pick<8>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
+        if constexpr (HOLD) {
+          if (Ls <= 64) wave_pick<1, false>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
+          else if (Ls <= 128) wave_pick<2, false>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
+          else if (Ls <= 256) wave_pick<4, false>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
+          else wave_pick<8, false>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
+        } else {
+          if (Ls <= 512) wave_pick<8, true>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
+          else wave_pick<16, true>(vK, vV, Ls, ks, gather, gs, slotmap, ln, gp, pos0, rb);
+        }
       }
       lds_barrier();
       if (gather) {
         char* dst = (tensor ? a.V_out : a.K_out) + out * rowbytes;
+        if constexpr (!HOLD) {  // kept rows are read again
+          constexpr int UG = 8;
+          const char* src = cur + here_v(coff);
+          for (int s0 = here_v(row0); s0 < k; s0 += UG * R) {
+            uint4 q[UG];
+#pragma unroll
+            for (int u = 0; u < UG; ++u) q[u] = ld16_last(src + (int64_t)slotmap[s0 + u * R < k ? s0 + u * R : s0] * a.st);
+#pragma unroll
+            for (int u = 0; u < UG; ++u)
+              if (s0 + u * R < k) st16_out_at(dst, (uint32_t)(s0 + u * R) * (uint32_t)rowbytes + (uint32_t)coff, q[u]);
+          }
+        }
         const int row = here_v(row0), nn = here_s(n);
 #pragma unroll
         for (int j = 0; j < NSL; ++j) {
@@ -517,12 +577,48 @@ hipError_t launch_ring_one(K kernel, const PassArgs& a, dim3 grid, int threads, 
 struct RingShape {
   int gw, nsl;  // (0, 0: no shape holds the chunk)
 };
-inline RingShape ring_shape(int D, int esize, int L) {
+inline RingShape ring_hold_shape(int D, int esize, int L) {
   const int lpr = chunk_lpr(D * esize), rpw = kWave / lpr;
   for (int gw = 1; gw <= 8; gw *= 2)
     if (L <= 8 * gw * rpw && 2 * gw * rpw <= 128 && ring_lds(D, esize, L, 8, gw).total <= kRingMaxLds) return {gw, 8};
   if (L > 16 * 4 * rpw && L <= 32 * 4 * rpw && L <= 512 && ring_lds(D, esize, L, 32, 4).total <= kRingMaxLds) return {4, 32};
   return {0, 0};
+}
+// ... and the wavefronts through whose ring other chunks pass.
+inline RingShape ring_stream_shape(int D, int esize, int L) {
+  const int lpr = chunk_lpr(D * esize), rpw = kWave / lpr;
+  const int gw = lpr == 4 || (int64_t)L * D * esize < 256 * 1024 ? 4 : 8, nr = ring_slots(0, gw);
+  const bool deep = L - (gw - 1) * rpw > (nr - 2) * gw * rpw;  // its last wavefront has rows in as many steps as slots, in pairs
+  return deep && L <= 1024 && ring_lds(D, esize, L, 0, gw).total <= kRingMaxLds ? RingShape{gw, 0} : RingShape{0, 0};
+}
+// Where a chunk in registers takes a compute unit to itself, nothing runs beside its selection, and lanes without rows
+// of their own - rows of fewer slices than lanes, steps past the end of the chunk - count.  Two workgroups that stream
+// and read the kept rows again (mostly out of the memory-side cache) do better there from some share of such lanes
+// on, the earlier the more arithmetic a byte costs.  Held | streamed, us, 600 MB on 96 streams, lag and own reference:
+//   16 wavefronts, bf16   rows of 128 bytes, lag 512 (all slices hold rows) 200, 234 | 186, 218; 450 (0.88) 206, 241 | 182, 211
+//                         rows of 256 bytes, lag 180 (0.94) 187, 215 | 191, 219; of 192, 256 (0.75) 207, 240 | 197, 232
+//                 fp32    rows of 256 bytes, lag 130 (0.68) 194, 218 | 199, 231; 200 (0.78) 169, 182 | 183, 210
+//   32 slices, bf16       rows of 256 bytes, lag 300 (0.94) 212, 243 | 190, 224; 400 (0.96) 188, 216 | 193, 229
+//                         rows of 512 bytes, lag 152 (0.95) 207, 240 | 194, 230; 200 (0.96) 180, 215 | 195, 232
+//              fp32       rows of 384 bytes, lag 152 (0.71) 211, 233 | 182, 212; 200 (0.72) 189, 216 | 190, 223
+inline bool ring_hold_pays(const RingShape& f, int D, int esize, int L) {
+  if (f.gw == 0) return false;
+  if (f.gw < 8 && f.nsl == 8) return true;
+  const int lpr = chunk_lpr(D * esize), R = f.gw * (kWave / lpr), steps = ((L + R - 1) / R + 1) & ~1;
+  const int64_t filled = (int64_t)L * row_units(D, esize) * 100 / ((int64_t)steps * R * lpr);
+  if (f.nsl == 8) return esize == 4 || (lpr >= 16 && filled >= 90);
+  return filled >= (esize == 4 ? 72 : 96);
+}
+// Where neither does: lanes without channels and chunks too short for the steps that the selection costs (2-byte
+// elements; streaming kernel, us): rows of 160 bytes, lag 180 239, 272 | 251, 301; 256 228, 260 | 226, 272; 300 265, 295 | 213,
+// 259; rows of 192 bytes, lag 152 215, 242 | 230, 275; 180 217, 245 | 211, 252; 256 216, 246 | 197, 232.
+inline bool ring_stream_pays(int D, int esize, int L) {
+  const int units = row_units(D, esize), lpr = chunk_lpr(D * esize);
+  return esize == 4 || units == lpr || L > (4 * units < 3 * lpr ? 256 : 179);
+}
+inline RingShape ring_shape(int D, int esize, int L) {
+  const RingShape h = ring_hold_shape(D, esize, L), t = ring_stream_shape(D, esize, L);
+  return ring_hold_pays(h, D, esize, L) || t.gw == 0 ? h : t;
 }
 
 template <typename ET, int LPR, int NSL, int GW>
@@ -538,6 +634,10 @@ hipError_t launch_ring_l(const PassArgs& a, const RingShape& f, dim3 grid, size_
     case 4 * 64 + 8: return launch_ring_n<ET, LPR, 8, 4>(a, grid, lds, s);
     case 8 * 64 + 8:
       if constexpr (LPR >= 8) return launch_ring_n<ET, LPR, 8, 8>(a, grid, lds, s);
+      break;
+    case 4 * 64: return launch_ring_n<ET, LPR, 0, 4>(a, grid, lds, s);
+    case 8 * 64:
+      if constexpr (LPR >= 8) return launch_ring_n<ET, LPR, 0, 8>(a, grid, lds, s);
       break;
     case 4 * 64 + 32:
       if constexpr (LPR >= 16) return launch_ring_n<ET, LPR, 32, 4>(a, grid, lds, s);

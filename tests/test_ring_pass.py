@@ -20,8 +20,12 @@ SHAPES = [
     (1, 1300, 80, torch.float16, 100), (520, 3, 256, torch.bfloat16, 57), (150, 7, 64, torch.bfloat16, 129), (17, 70, 128, torch.float32, 64),
     # sixteen: just over eight, full
     (100, 6, 128, torch.float32, 65), (37, 15, 64, torch.float32, 225), (29, 20, 256, torch.bfloat16, 128), (40, 13, 64, torch.float16, 512),
-    # 32 slices: 17 and a row more, all; 31 and an odd number of steps
-    (40, 8, 128, torch.bfloat16, 257), (12, 23, 256, torch.float16, 256), (23, 12, 128, torch.float32, 249), (16, 18, 96, torch.bfloat16, 500),
+    # 32 slices: 26 and an odd number of steps, all, nearly all
+    (40, 8, 128, torch.bfloat16, 409), (12, 23, 256, torch.float16, 256), (23, 12, 128, torch.float32, 249), (300, 2, 128, torch.float16, 500),
+    # chunks that pass through the ring only: eight wavefronts, six slots - the fewest steps, an odd number, rows of 64 bytes, the
+    # longest chunk of 2-byte rows below 512 KiB - and sixteen, eight slots
+    (60, 9, 128, torch.float16, 129), (30, 20, 80, torch.bfloat16, 300), (7, 31, 64, torch.bfloat16, 450), (5, 9, 24, torch.bfloat16, 513),
+    (31, 9, 128, torch.bfloat16, 1023), (300, 2, 96, torch.float16, 700), (11, 9, 128, torch.bfloat16, 1024), (3, 12, 128, torch.float32, 513), (9, 5, 256, torch.float16, 1000),
 ]
 
 
@@ -48,7 +52,7 @@ def test_shapes_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, va
     assert torch.equal(kept.flatten(2), out.idx[:, :, S:S + n_s * out.plan.k])
 
 
-@pytest.mark.parametrize("D,dtype,L", [(64, torch.bfloat16, 64), (128, torch.bfloat16, 100), (128, torch.float32, 128), (128, torch.float16, 300)])
+@pytest.mark.parametrize("D,dtype,L", [(64, torch.bfloat16, 64), (128, torch.bfloat16, 100), (128, torch.float32, 128), (128, torch.float16, 300), (64, torch.bfloat16, 900)])
 def test_equal_scores_infinities_and_nan(D, dtype, L):
     """Equal tokens across the edge of the kept set go to the lower positions; a stream with infinities or NaN keeps k
     rows of every chunk, in order, and leaves the streams in the same workgroup what they are."""
@@ -67,7 +71,7 @@ def test_equal_scores_infinities_and_nan(D, dtype, L):
         assert torch.equal(getattr(out, x)[:, same], getattr(want, x)[:, same])
 
 
-@pytest.mark.parametrize("D,dtype,L,streams", [(64, torch.bfloat16, 64, 90), (80, torch.float16, 100, 300), (128, torch.float32, 250, 40)])
+@pytest.mark.parametrize("D,dtype,L,streams", [(64, torch.bfloat16, 64, 90), (80, torch.float16, 100, 300), (128, torch.float32, 250, 40), (96, torch.bfloat16, 600, 70)])
 def test_in_a_captured_graph(D, dtype, L, streams):
     """... replayed three times with eager work between, then on other bytes in the same buffers."""
     S, T = 16, 16 + 9 * L + 17
