@@ -144,6 +144,14 @@ hipError_t launch_ring_pass(const PassArgs& a, hipStream_t s);
 hipError_t launch_ring_f32(const PassArgs& a, hipStream_t s);
 hipError_t launch_ring_bf16(const PassArgs& a, hipStream_t s);
 hipError_t launch_ring_f16(const PassArgs& a, hipStream_t s);
+// Its form for rows of a multiple of 4 bytes on 4-byte aligned addresses.
+bool direct_supported(int D, int esize, int L, int64_t st);
+int direct_places(int D, int esize, int L);
+int direct_threads(int D, int esize, int L);
+hipError_t launch_direct_pass(const PassArgs& a, hipStream_t s);
+hipError_t launch_direct_f32(const PassArgs& a, hipStream_t s);
+hipError_t launch_direct_bf16(const PassArgs& a, hipStream_t s);
+hipError_t launch_direct_f16(const PassArgs& a, hipStream_t s);
 
 hipError_t launch_fused_append(const AppendArgs& a, hipStream_t s);
 // Single-round decode step (exactly one chunk completes; no intermediate append copy).

@@ -139,9 +139,10 @@ __device__ __forceinline__ float pair_sum(float s0, float s1, bool odd) {
   }
 }
 // Channel variances (Eq. 9-10, as token_var_sub) of two rows: the first in even lanes, the second in odd ones.
-template <int LPR, int VEC>
+// PART: the first `dead` channels of the lane belong to its neighbour and are left out (their iv is 0).
+template <int LPR, int VEC, bool PART>
 __device__ __forceinline__ float token_var_pair(const float (&x0)[VEC], const float (&x1)[VEC], const float (&mn)[VEC],
-                                                const float (&iv)[VEC], float inv_D, float inv_dof, bool odd) {
+                                                const float (&iv)[VEC], float inv_D, float inv_dof, bool odd, int dead) {
   float y0[VEC], y1[VEC], s0 = 0.f, s1 = 0.f;
 #pragma unroll
   for (int j = 0; j < VEC; ++j) {
@@ -156,7 +157,8 @@ __device__ __forceinline__ float token_var_pair(const float (&x0)[VEC], const fl
   float q0[2] = {0.f, 0.f}, q1[2] = {0.f, 0.f};  // (two short sums: half the rounding of one long one)
 #pragma unroll
   for (int j = 0; j < VEC; ++j) {
-    const float d0 = fmaf(y0[j], iv[j], -m0), d1 = fmaf(y1[j], iv[j], -m1);
+    const bool out = PART && j < dead;
+    const float d0 = fmaf(y0[j], iv[j], out ? 0.f : -m0), d1 = fmaf(y1[j], iv[j], out ? 0.f : -m1);
     q0[j & 1] = fmaf(d0, d0, q0[j & 1]);
     q1[j & 1] = fmaf(d1, d1, q1[j & 1]);
   }
@@ -244,7 +246,9 @@ __device__ __forceinline__ void wave_pick(const float* vK, const float* vV, int 
 // GW wavefronts on K rows, as many on V rows; a lane holds up to NSL 16-byte slices of its chunk.
 // Scored chunks are numbered stream * n_s + p; workgroup i of `walks` takes the i-th equal share of them, from
 // the highest number down.
-template <typename ET, int LPR, int NSL, int GW>
+// DIRECT: rows of any multiple of 4 bytes on 4-byte addresses, which the asynchronous loads do not take: the next
+// chunk's rows are loaded into registers of their own while this one is selected (NSL = 8).
+template <typename ET, int LPR, int NSL, int GW, bool DIRECT>
 __device__ __forceinline__ void ring_pass(const PassArgs& a) {
   constexpr int VEC = ET::VEC, ESIZE = 16 / VEC, RPW = kWave / LPR, R = GW * RPW, NR = ring_slots(NSL, GW);
   constexpr int THREADS = GW * 2 * kWave;
@@ -259,9 +263,11 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
   const int slot0 = tensor ? (wave + GW / 2) % GW : wave;
   const int cl = lane % LPR, row0 = slot0 * RPW + lane / LPR;
   const int D = a.D, L = a.L, k = a.k, S = a.S, rowbytes = D * ESIZE;
-  // a lane beyond the row's slices repeats the last one; it has no channels of its own
+  // A lane beyond the row's slices repeats its last 16 bytes; it has no channels of its own.  (Where the row ends
+  // inside a lane's slice, that lane does too, and its first `part` channels are its neighbour's.)
   const bool dead = cl * 16 >= rowbytes;
-  const int coff = dead ? rowbytes - 16 : cl * 16, ch0 = coff / ESIZE;
+  const int coff = cl * 16 > rowbytes - 16 ? rowbytes - 16 : cl * 16, ch0 = coff / ESIZE;
+  const int part = dead ? VEC : (cl * 16 - coff) / ESIZE;
   const RingLds lay = ring_lds(D, ESIZE, L, NSL, GW);
   float* vK = reinterpret_cast<float*>(lds + lay.off_vK);
   float* vV = reinterpret_cast<float*>(lds + lay.off_vV);
@@ -277,7 +283,7 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
   if (blockIdx.x >= a.walks) {
     const int64_t e = blockIdx.x - a.walks, stream = e / a.edge, b = stream / a.H, h = stream % a.H;
     const int64_t out = stream * a.T_out;
-    copy_edge_rows<LPR>(a.K + b * a.sb + h * a.sh, a.V + b * a.sb + h * a.sh, a.st, a.K_out + out * rowbytes,
+    copy_edge_rows<LPR, DIRECT>(a.K + b * a.sb + h * a.sh, a.V + b * a.sb + h * a.sh, a.st, a.K_out + out * rowbytes,
                         a.V_out + out * rowbytes, a.idx_out ? a.idx_out + out : nullptr, rowbytes, S,
                         S + a.n_s * L, S + a.n_s * k, a.T - (S + a.n_s * L), (int)(e % a.edge), a.edge, coff, tid,
                         THREADS);
@@ -314,15 +320,28 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
     if constexpr (HOLD) dma_rows16_at<(j % NR) * 1024>(off < lane_max ? off : lane_max, base, ring_base);
     else dma_rows16<false>(off < lane_max ? off : lane_max, base, ring_base + (j % NR) * 1024u);
   };
-  ring_for<0, NR, 1>([&](auto tag) __attribute__((always_inline)) {
-    if (decltype(tag)::value < n) dma(cur, tag);
-  });
+  uint4 hold[HOLD ? NSL : 1], ahead[DIRECT ? NSL : 1];
+  // (All slices in one go, without a branch: behind one, the compiler waits for the loads before it.  Steps this
+  // wavefront does not have, and with `rows` 1 the whole of it, repeat one row.)
+  auto load = [&](uint4 (&to)[NSL ? NSL : 1], const char* base, int rows) __attribute__((always_inline)) {
+    const int row = here_v(row0);  // (offsets worked out here, not kept across everything)
+#pragma unroll
+    for (int j = 0; j < NSL; ++j)
+      to[j] = ld16_a4(base + ((uint32_t)(row + j * R < rows ? row + j * R : rows - 1) * st + (uint32_t)coff));
+  };
+  if constexpr (DIRECT) {  // the first reference and the first chunk at once
+    load(ahead, cur, L);
+    load(hold, ref ? cur - (int64_t)L * a.st : cur, L);
+  } else {
+    ring_for<0, NR, 1>([&](auto tag) __attribute__((always_inline)) {
+      if (decltype(tag)::value < n) dma(cur, tag);
+    });
+  }
   if (tid < 8 && rowbytes < LPR * 16) refbuf[4 * D + tid] = 0.f;
   if constexpr (HOLD)
     for (int t = L + tid; t < chunk_pad(L); t += THREADS) slotmap[t] = -1;  // rows past the end are never stored
   uint32_t at = 0;  // !HOLD: byte offset of the next step's slot
 
-  uint4 hold[HOLD ? NSL : 1];
   TStats<VEC> acc;
   float mn[VEC], iv[VEC];
   // the wavefront's minima and maxima -> statbuf
@@ -367,16 +386,44 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
       mn[i] = rd[i];
-      iv[i] = ri[i];
+      iv[i] = DIRECT && i < part ? 0.f : ri[i];
     }
   };
   // lanes 0 and 1 of a row hold the variances of its row of steps j and j + 1
   float* myvar = (tensor ? vV : vK) + row0 + (odd ? R : 0);
   auto score_pair = [&](const float (&x0)[VEC], const float (&x1)[VEC], int j) __attribute__((always_inline)) {
-    const float v = token_var_pair<LPR, VEC>(x0, x1, mn, iv, inv_D, inv_dof, odd);
+    const float v = token_var_pair<LPR, VEC, DIRECT>(x0, x1, mn, iv, inv_D, inv_dof, odd, part);
     if (cl < 2) myvar[j * R] = v;
   };
 
+  auto fold_pair = [&](const float (&x0)[VEC], const float (&x1)[VEC]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      acc.mn[i] = fminf(fminf(acc.mn[i], x0[i]), x1[i]);
+      acc.mx[i] = fmaxf(fmaxf(acc.mx[i], x0[i]), x1[i]);
+    }
+    pin(acc);
+  };
+
+  if (DIRECT && ref) {
+    acc.reset();
+#pragma unroll
+    for (int j = 0; j < NSL; j += 2)
+      if (j < n) {
+        float x0[VEC], x1[VEC];
+        unpack<ET>(ahead[DIRECT ? j : 0], x0);
+        unpack<ET>(ahead[DIRECT ? j + 1 : 0], x1);
+        fold_pair(x0, x1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    park();
+    lds_barrier();
+    publish();
+    lds_barrier();
+    take_ref();
+    ref = false;
+    cur -= (int64_t)L * a.st;
+  }
   while (true) {
     // the item after this one
     const bool more = ref || left > 1;
@@ -397,7 +444,7 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
     acc.reset();
     // Steps j and j + 1 have landed once no more operations are outstanding than loads were issued behind them: the
     // rest of the item's and, if there is one, the next item's as far as it has been asked for.
-    if (HOLD && !more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (HOLD && !DIRECT && !more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if constexpr (!HOLD) {
       for (int j = 0; j < n; j += 2) {
         // as many loads as slots are under way, until nothing is left to ask for
@@ -417,19 +464,13 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
         float x0[VEC], x1[VEC];
         unpack<ET>(make_uint4(qa.x, qa.y, qa.z, qa.w), x0);
         unpack<ET>(make_uint4(qb.x, qb.y, qb.z, qb.w), x1);
-        if (stats) {
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) {
-            acc.mn[i] = fminf(fminf(acc.mn[i], x0[i]), x1[i]);
-            acc.mx[i] = fmaxf(fmaxf(acc.mx[i], x0[i]), x1[i]);
-          }
-        }
+        if (stats) fold_pair(x0, x1);
         if (score) score_pair(x0, x1, j);
       }
     }
     ring_for<0, NSL, 2>([&](auto tag) __attribute__((always_inline)) {
       constexpr int j = decltype(tag)::value;
-      if (j < n) {
+      if (!DIRECT && j < n) {
         if constexpr (NSL == 8) wait_vm6(n - 2);
         else wait_vm14(j >= 16 && more ? n - 18 : n - 2 - j);
         u32x4 qa, qb;
@@ -438,7 +479,8 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
         hold[j + 1] = make_uint4(qb.x, qb.y, qb.z, qb.w);
       }
       // the two slots are free again
-      if constexpr (NSL == 8) {
+      if constexpr (DIRECT) {
+      } else if constexpr (NSL == 8) {
         if (j < n && more) {
           dma(next, tag);
           dma(next, std::integral_constant<int, j + 1>{});
@@ -456,18 +498,12 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
         float x0[VEC], x1[VEC];
         unpack<ET>(hold[j], x0);
         unpack<ET>(hold[j + 1], x1);
-        if (stats) {
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) {
-            acc.mn[i] = fminf(fminf(acc.mn[i], x0[i]), x1[i]);
-            acc.mx[i] = fmaxf(fmaxf(acc.mx[i], x0[i]), x1[i]);
-          }
-          pin(acc);
-        }
+        if (stats) fold_pair(x0, x1);
         if (score) score_pair(x0, x1, j);
       }
       __builtin_amdgcn_sched_barrier(0);
     });
+    if constexpr (DIRECT) load(ahead, more ? next : cur, more ? L : 1);
     if (stats) park();
     if (ref || (HOLD && local)) {
       lds_barrier();
@@ -540,6 +576,10 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
       --left;
     }
     if (!more) break;
+    if constexpr (DIRECT) {
+#pragma unroll
+      for (int j = 0; j < NSL; ++j) hold[j] = ahead[j];
+    }
     cur = next;
     stream = nstream;
     p = np;
@@ -547,16 +587,16 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
   }
 }
 
-// The same under two names, by which lagkv_kernel_for and profiles tell short calls (about a chunk per place) from
-// those that stream.
+// The same under two names, by which lagkv_kernel_for and profiles tell short calls (about a chunk per place) and rows
+// on 4-byte addresses from those that stream.
 namespace ring {
 template <typename ET, int LPR, int NSL, int GW>
 __global__ void __launch_bounds__(GW * 2 * kWave, NSL <= 8 ? 4 : 2) split_pass_kernel(const PassArgs a) {
-  ring_pass<ET, LPR, NSL, GW>(a);
+  ring_pass<ET, LPR, NSL, GW, false>(a);
 }
-template <typename ET, int LPR, int NSL, int GW>
+template <typename ET, int LPR, int NSL, int GW, bool DIRECT>
 __global__ void __launch_bounds__(GW * 2 * kWave, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const PassArgs a) {
-  ring_pass<ET, LPR, NSL, GW>(a);
+  ring_pass<ET, LPR, NSL, GW, DIRECT>(a);
 }
 }  // namespace ring
 
@@ -623,7 +663,7 @@ inline RingShape ring_shape(int D, int esize, int L) {
 
 template <typename ET, int LPR, int NSL, int GW>
 hipError_t launch_ring_n(const PassArgs& a, dim3 grid, size_t lds, hipStream_t s) {
-  return a.brief ? launch_ring_one(ring::chunk_pass_kernel<ET, LPR, NSL, GW>, a, grid, GW * 2 * kWave, lds, s)
+  return a.brief ? launch_ring_one(ring::chunk_pass_kernel<ET, LPR, NSL, GW, false>, a, grid, GW * 2 * kWave, lds, s)
                  : launch_ring_one(ring::split_pass_kernel<ET, LPR, NSL, GW>, a, grid, GW * 2 * kWave, lds, s);
 }
 template <typename ET, int LPR>
@@ -646,6 +686,44 @@ hipError_t launch_ring_l(const PassArgs& a, const RingShape& f, dim3 grid, size_
   }
   return hipErrorInvalidValue;
 }
+// Rows on 4-byte addresses: wavefronts per tensor whose lanes hold a chunk in eight slices, 0 if there is no such number.
+inline int direct_waves(int D, int esize, int L) {
+  const int rpw = kWave / chunk_lpr(D * esize);
+  for (int gw = 1; gw <= 8; gw *= 2)
+    if (L <= 8 * gw * rpw && 2 * gw * rpw <= 128) return gw;
+  return 0;
+}
+inline int direct_lds(int D, int esize, int L, int gw) { return ring_lds(D, esize, L, 8, gw).off_ring; }
+
+template <typename ET, int LPR>
+hipError_t launch_direct_l(const PassArgs& a, int gw, dim3 grid, size_t lds, hipStream_t s) {
+  switch (gw) {
+    case 1: return launch_ring_one(ring::chunk_pass_kernel<ET, LPR, 8, 1, true>, a, grid, 128, lds, s);
+    case 2: return launch_ring_one(ring::chunk_pass_kernel<ET, LPR, 8, 2, true>, a, grid, 256, lds, s);
+    case 4: return launch_ring_one(ring::chunk_pass_kernel<ET, LPR, 8, 4, true>, a, grid, 512, lds, s);
+    case 8:
+      if constexpr (LPR >= 8) return launch_ring_one(ring::chunk_pass_kernel<ET, LPR, 8, 8, true>, a, grid, 1024, lds, s);
+      break;
+    default: break;
+  }
+  return hipErrorInvalidValue;
+}
+template <typename ET>
+hipError_t launch_direct_t(const PassArgs& a, hipStream_t s) {
+  const int gw = direct_waves(a.D, a.esize, a.L);
+  const int64_t nblocks = a.walks + (int64_t)a.B * a.H * a.edge;
+  if (gw == 0 || nblocks <= 0 || nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  const size_t lds = (size_t)direct_lds(a.D, a.esize, a.L, gw);
+  const dim3 grid((unsigned)nblocks);
+  switch (chunk_lpr(a.D * a.esize)) {
+    case 4: return launch_direct_l<ET, 4>(a, gw, grid, lds, s);
+    case 8: return launch_direct_l<ET, 8>(a, gw, grid, lds, s);
+    case 16: return launch_direct_l<ET, 16>(a, gw, grid, lds, s);
+    case 32: return launch_direct_l<ET, 32>(a, gw, grid, lds, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 template <typename ET>
 hipError_t launch_ring_t(const PassArgs& a, hipStream_t s) {
   const RingShape f = ring_shape(a.D, a.esize, a.L);

@@ -52,6 +52,22 @@ def test_shapes_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, va
     assert torch.equal(kept.flatten(2), out.idx[:, :, S:S + n_s * out.plan.k])
 
 
+# rows of partial slices, on 4-byte addresses: two wavefronts (one lane with channels; a lane short of 64 bytes), four, eight
+# with shares over many streams, sixteen with idle wavefronts
+PARTIAL = [
+    (2050, 1, 4, torch.float32, 64), (40, 30, 30, torch.bfloat16, 111), (300, 5, 100, torch.bfloat16, 57), (1, 900, 126, torch.float16, 128),
+    (150, 9, 33, torch.float32, 128), (41, 17, 34, torch.bfloat16, 65), (37, 15, 66, torch.float16, 130), (29, 20, 66, torch.float32, 100),
+    (23, 12, 18, torch.bfloat16, 511),
+]
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL])
+@pytest.mark.parametrize("streams,n_s,D,dtype,L", PARTIAL)
+def test_partial_slices_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, variant):
+    assert D * dtype.itemsize % 4 == 0
+    test_shapes_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, variant)
+
+
 @pytest.mark.parametrize("D,dtype,L", [(64, torch.bfloat16, 64), (128, torch.bfloat16, 100), (128, torch.float32, 128), (128, torch.float16, 300), (64, torch.bfloat16, 900)])
 def test_equal_scores_infinities_and_nan(D, dtype, L):
     """Equal tokens across the edge of the kept set go to the lower positions; a stream with infinities or NaN keeps k
