@@ -83,16 +83,16 @@ __global__ void __launch_bounds__(512, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const
       g.acc.reset();
 #pragma unroll
       for (int j0 = 0; j0 < NSL; j0 += UR) {
-        uint4 q[UR];
+        if (j0 < n) {  // (a batch in one go: behind a branch of its own every load would wait for the one before it)
+          uint4 q[UR];
 #pragma unroll
-        for (int u = 0; u < UR; ++u)
-          if (j0 + u < n) q[u] = load(rb, row + (j0 + u) * R);
+          for (int u = 0; u < UR; ++u) q[u] = load(rb, row + (j0 + u) * R);
 #pragma unroll
-        for (int u = 0; u < UR; ++u)
-          if (j0 + u < n) hold[j0 + u] = load(cb, row + (j0 + u) * R);
+          for (int u = 0; u < UR; ++u) hold[j0 + u] = load(cb, row + (j0 + u) * R);
 #pragma unroll
-        for (int u = 0; u < UR; u += 2)
-          if (j0 + u < n) g.fold_pair(q[u], q[u + 1]);
+          for (int u = 0; u < UR; u += 2)
+            if (j0 + u < n) g.fold_pair(q[u], q[u + 1]);
+        }
       }
       g.park(statbuf);
       lds_barrier();
@@ -101,8 +101,7 @@ __global__ void __launch_bounds__(512, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const
       g.take_ref(refbuf);
     } else {
 #pragma unroll
-      for (int j = 0; j < NSL; ++j)
-        if (j < n) hold[j] = load(cb, row + j * R);
+      for (int j = 0; j < NSL; ++j) hold[j] = load(cb, row + j * R);
     }
   }
 
@@ -145,14 +144,15 @@ __global__ void __launch_bounds__(512, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const
       const int row = here_v(row0), n = here_s(n_iter);
 #pragma unroll
       for (int j = 0; j < NSL; ++j) {
-        if (j < n) {
-          if (gather) {
-            const int sl = slotmap[row + j * R];
-            if (sl >= 0) st16_out_at(dst, (uint32_t)sl * (uint32_t)rowbytes + (uint32_t)coff, hold[j]);
-          }
-          if (more) hold[j] = load(nb, row + j * R);
+        if (gather && j < n) {
+          const int sl = slotmap[row + j * R];
+          if (sl >= 0) st16_out_at(dst, (uint32_t)sl * (uint32_t)rowbytes + (uint32_t)coff, hold[j]);
           __builtin_amdgcn_sched_barrier(0);
         }
+      }
+      if (more) {
+#pragma unroll
+        for (int j = 0; j < NSL; ++j) hold[j] = load(nb, row + j * R);
       }
     }
     if (stats) g.take_ref(refbuf);

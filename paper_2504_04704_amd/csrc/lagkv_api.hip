@@ -252,10 +252,13 @@ bool use_ring(const Norm& n, PassArgs& a, bool brief) {
   a.brief = brief;
   return true;
 }
-// Where use_chunk says yes and use_ring no.
-int launch_chunk(PassArgs& a, const Norm& n, hipStream_t s) {
+// Where use_chunk says yes and use_ring no.  Of the shapes that use_ring is not asked about (whole_slices false), the
+// ring kernel's form for 4-byte addresses takes those that fit its eight slices (64 streams of 8247 rows of 200
+// bytes, lag 128: 74 us, the chunk kernel 110 us); of those that it leaves here the chunk kernel has the shorter chain
+// (2 streams of 17 chunks of 512 rows of 128 bytes by Eq. 14-15: 14.2 us, the other 17.1 us).
+int launch_chunk(PassArgs& a, const Norm& n, bool whole_slices, hipStream_t s) {
   const int64_t chunks = n.streams * a.n_s;
-  if (n.variant != LAGKV_SCORE_L2 && chunks < (1LL << 31) && direct_supported(n.D, n.esize, n.L, a.st)) {
+  if (!whole_slices && n.variant != LAGKV_SCORE_L2 && chunks < (1LL << 31) && direct_supported(n.D, n.esize, n.L, a.st)) {
     const int64_t places = direct_places(n.D, n.esize, n.L);
     a.walks = chunks < places ? chunks : places;
     if (grid_fits(a.walks + most_edge_workgroups(a), direct_threads(n.D, n.esize, n.L)))
@@ -295,7 +298,7 @@ int launch_in_parts(const PassArgs& a, int threads, F launch, hipStream_t s) {
 int launch_fused_any(PassArgs& a, const Norm& n, hipStream_t s) {
   const bool brief = use_chunk(n, a, true);
   if (use_ring(n, a, brief)) return launch_ring_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
-  if (brief) return launch_chunk(a, n, s);
+  if (brief) return launch_chunk(a, n, true, s);
   a.order = n.hint.order;
   a.sel = n.hint.sel;
   if (use_resident(n)) {
@@ -434,7 +437,7 @@ int fill_empty_cache(const Norm& n, lagkv_cache* c, const void* K, const void* V
     if (grid_fits(a.walks + most_edge_workgroups(a), ring_threads(n.D, n.esize, n.L)))
       rc = launch_ring_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
   } else if (use_chunk(n, a, whole && n.variant == LAGKV_SCORE_L2)) {
-    rc = launch_chunk(a, n, s);
+    rc = launch_chunk(a, n, whole, s);
   } else if (whole && (n.variant == LAGKV_SCORE_L2 || !chunk_supported(n.D, n.esize, n.L, st))) {
     a.nwaves = split_nw(n);  // (which takes its means as the general append kernel does)
     a.nseg = pick_segments_split(n, a.n_s, a.nwaves);
@@ -523,7 +526,7 @@ int lagkv_score(const lagkv_params* p, const void* K, const void* V, int64_t T, 
   if ((force == LAGKV_PATH_FUSED || force == LAGKV_PATH_RESIDENT) && !fused_ok) return LAGKV_ESHAPE;
   if (fused_ok && force != LAGKV_PATH_STAGED) return launch_fused_any(a, n, s);
   if (!staged_fits(n)) return LAGKV_ESHAPE;
-  if (use_chunk(n, a, false)) return launch_chunk(a, n, s);
+  if (use_chunk(n, a, false)) return launch_chunk(a, n, false, s);
   return hip_status(launch_staged_score(a, n.S, scores, s));
 }
 
@@ -609,7 +612,7 @@ int lagkv::compress_with_workspace(const lagkv_params* p, const void* K, const v
   const bool chunk = use_chunk(n, a, false);
   if (!(chunk && told_none(n, sb, sh, st)) && (!ws || ws_bytes < w.total || !aligned_to(ws, 16)))
     return LAGKV_EWORKSPACE;
-  if (chunk) return launch_chunk(a, n, s);
+  if (chunk) return launch_chunk(a, n, false, s);
   float* sc = scores_out ? scores_out : (float*)((char*)ws + w.off_scores);
   int32_t* kept = (int32_t*)((char*)ws + w.off_kept);
   hipError_t e = launch_staged_score(a, n.S, sc, s);
