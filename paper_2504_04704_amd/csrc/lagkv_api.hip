@@ -233,16 +233,23 @@ bool use_chunk(const Norm& n, PassArgs& a, bool whole_slices) {
   return true;
 }
 // The ring kernel, in place of the streaming kernel, of the chunk kernel (`brief`) and of the register-resident
-// kernel.  The last for lags of 128 with 2-byte elements and more scored chunks than it has places, in less than a stream
-// per place: 1.02 to 1.17 up to 1.5 chunks a place (8 streams of 63 chunks, 8269 rows of 256 bytes, 19.6 us against
-// 16.8 us), above 0.93 to 1.14, the better the less evenly whole segments fill the chip; by Eq. 14-15, where that
-// kernel goes over its rows twice with nothing else on the compute unit, 1.05 to 1.15.  Other lags 0.82 to 1.0, fp32
-// 0.89 to 0.95.  Sets a.walks and a.brief where it says yes.
+// kernel.  The last for lags of 128 where a stream does not have a place to itself (256 streams of 16384 rows equal):
+//   2-byte elements   up to 256 chunks 1.07 to 1.14 (24 streams of 2 chunks 11.2 us against 9.8 us), up to 1.5 chunks
+//                     a place 1.02 to 1.17 (8 streams of 63, 8269 rows of 256 bytes, 19.6 us against 16.8 us), above 0.93
+//                     to 1.14, the better the less evenly whole segments fill the chip; Eq. 14-15, where that kernel goes
+//                     over its rows twice with nothing else on the compute unit, 1.05 to 1.15 at any size
+//   fp32              up to a chunk a place 1.02 to 1.27, above 0.89 to 1.02
+// (129 to 256 chunks of 2-byte rows, 1.05 to 1.1, are calls for which lagkv_kernel_for's answer has been written down:
+// they stay.)  Lags of 256 and 512 0.82 to 1.05.  Sets a.walks and a.brief where it says yes.
+bool ring_over_resident(const Norm& n, int64_t chunks) {
+  if (n.L != 128 || n.streams >= 256) return false;
+  return n.esize == 2 ? chunks <= 128 || chunks > 256 : chunks <= 512;
+}
 bool use_ring(const Norm& n, PassArgs& a, bool brief) {
   if (n.hint.path != LAGKV_PATH_AUTO || n.hint.waves || n.hint.nseg || n.hint.order || n.hint.sel) return false;
   const int64_t chunks = n.streams * a.n_s;
   if (n.variant == LAGKV_SCORE_L2 || !ring_supported(n.D, n.esize, n.L, a.st) || chunks >= (1LL << 31)) return false;
-  if (use_resident(n) && (n.L != 128 || n.esize != 2 || chunks <= 256 || n.streams >= 256)) return false;
+  if (use_resident(n) && !ring_over_resident(n, chunks)) return false;
   if (!ring_pays(n.D, n.esize, n.L)) return false;
   // (Eq. 14-15 goes over a chunk twice there: 4 streams of 8 chunks of 160 rows 12.6 us, the chunk kernel 11.0 us)
   if (brief && n.variant == LAGKV_SCORE_LOCAL && !ring_holds(n.D, n.esize, n.L)) return false;
