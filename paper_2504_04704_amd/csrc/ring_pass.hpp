@@ -183,16 +183,22 @@ __device__ __forceinline__ void wave_pick(const float* vK, const float* vV, int 
   }
   mK = wave_max(mK);
   mV = wave_max(mV);
-  float aK = 0.f, aV = 0.f;
+  // (denominators, a factor common to the whole chunk, as pairwise sums)
+  float aK[E], aV[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int t = e * kWave + lane;
-    eK[e] = t < L ? __expf(eK[e] - mK) : 0.f;
-    eV[e] = t < L ? __expf(eV[e] - mV) : 0.f;
-    aK += eK[e];
-    aV += eV[e];
+    aK[e] = eK[e] = t < L ? __expf(eK[e] - mK) : 0.f;
+    aV[e] = eV[e] = t < L ? __expf(eV[e] - mV) : 0.f;
   }
-  const float rK = 1.0f / wave_sum(aK), rV = 1.0f / wave_sum(aV);
+#pragma unroll
+  for (int w = 1; w < E; w *= 2)
+#pragma unroll
+    for (int e = 0; e + w < E; e += 2 * w) {
+      aK[e] += aK[e + w];
+      aV[e] += aV[e + w];
+    }
+  const float rK = 1.0f / wave_sum(aK[0]), rV = 1.0f / wave_sum(aV[0]);
   uint32_t key[E], hi = 0, lo = 0xffffffffu;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
