@@ -239,7 +239,7 @@ int lagkv_prefill(const lagkv_params* p, lagkv_cache* cache, const void* K, cons
  * lagkv_launch_hint(0, 0, 0)).
  *   path      LAGKV_PATH_AUTO (the register-resident kernel where it applies, else the
  *             streaming fused kernel, else the three-kernel path; the chunk-at-a-time kernel
- *             in place of the last two where it is faster); LAGKV_PATH_FUSED (the
+ *             in place of the last two, and their ring form in place of any, where it is faster); LAGKV_PATH_FUSED (the
  *             streaming fused kernel; error LAGKV_ESHAPE when the fused kernels do not
  *             cover the shape); LAGKV_PATH_STAGED (three-kernel path); or
  *             LAGKV_PATH_RESIDENT (the one-shot kernel that keeps a batch of rows in
@@ -284,7 +284,8 @@ int lagkv_path_for(const lagkv_params* p, int64_t T);
 
 /*
  * Name of the kernel that scores in that call, for benchmarks and profiles that have to name
- * what they time: "hold_pass_kernel", "split_pass_kernel", "chunk_pass_kernel" or
+ * what they time: "hold_pass_kernel", "split_pass_kernel", "chunk_pass_kernel" (either of
+ * the last two may be the kernel in namespace lagkv::ring or the one in lagkv) or
  * "staged_score_kernel" ("copy_rows_kernel" where nothing is compressed).  Host only; NULL
  * for parameters the call rejects.
  */

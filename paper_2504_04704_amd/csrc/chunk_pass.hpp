@@ -1,5 +1,7 @@
 // Chunk-at-a-time LagKV kernel for gfx950: the one-shot pass for calls that do not fill the chip with
-// long walks (few or short streams), and for rows that are not whole 16-byte slices.
+// long walks (few or short streams), and for rows that are not whole 16-byte slices.  The ring kernel (ring_pass.hpp) has
+// taken most of these; left are Eq. 16, rows of partial slices of which a lane holds 9 to 32, and short calls by Eq. 14-15 of
+// chunks that it would go over twice.
 //
 // What bounds such a call is latency: one launch, a chain of dependent memory reads, the selection.  So a
 // workgroup of eight wavefronts (four on K rows, four on V rows) takes ONE chunk, or a short run of them

@@ -5,7 +5,7 @@
 // ring of its own (asynchronous global->LDS loads), always one chunk ahead: the slots that a pair of steps leaves are
 // filled with the rows of the next chunk at once, across selections, stores and the borders between streams.  A chunk
 // stays in registers until its selection is known and the kept rows are stored from there, so no row is read
-// twice (the streaming kernel in split_pass.hip reads kept rows again).  A compute unit holds 16 wavefronts of up to
+// twice (the streaming kernel in split_pass.hip reads kept rows again, and so does this one where a chunk does not fit).  A compute unit holds 16 wavefronts of up to
 // 128 registers each, as one workgroup or as many as eight: the smallest workgroup whose lanes hold a chunk in eight
 // slices is taken, because the others then have the unit to themselves while one of them selects.  Longer chunks
 // take eight wavefronts of 256 registers, alone on their unit.

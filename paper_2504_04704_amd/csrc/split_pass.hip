@@ -1,6 +1,6 @@
-// Tensor-split streaming LagKV kernel for gfx950: the one-shot pass for everything the
-// register-resident kernel does not take (Eq. 16 scoring, lags other than 128, 256 or 512 rows,
-// rows other than 256 bytes; short calls go to chunk_pass.hpp), and for any shape on request.
+// Tensor-split streaming LagKV kernel for gfx950: the one-shot pass for what neither the register-resident kernel nor
+// the ring kernel (ring_pass.hpp) takes - Eq. 16 scoring, lags above 1024, 2-byte rows of few slices with short lags -
+// and for any shape on request (short calls go to chunk_pass.hpp).
 //
 // A workgroup walks a segment of one stream backwards and scores chunk p with the
 // statistics of chunk p+1 while folding chunk p's own min/max for chunk p-1, so every
