@@ -5,8 +5,8 @@
 // ring of its own (asynchronous global->LDS loads), always one chunk ahead: the slots that a pair of steps leaves are
 // filled with the rows of the next chunk at once, across selections, stores and the borders between streams.  A chunk
 // stays in registers until its selection is known and the kept rows are stored from there, so no row is read
-// twice (the streaming kernel in split_pass.hip reads kept rows again, and so does this one where a chunk does not fit).  A compute unit holds 16 wavefronts of up to
-// 128 registers each, as one workgroup or as many as eight: the smallest workgroup whose lanes hold a chunk in eight
+// twice (the streaming kernel in split_pass.hip reads kept rows again, and so does this one where a chunk does not
+// fit: its rows then pass through the ring only).  A compute unit holds 16 wavefronts of up to 128 registers each, as one workgroup or as many as eight: the smallest workgroup whose lanes hold a chunk in eight
 // slices is taken, because the others then have the unit to themselves while one of them selects.  Longer chunks
 // take eight wavefronts of 256 registers, alone on their unit.
 //
@@ -22,9 +22,10 @@
 // Against the streaming kernel, 600 MB of K and V on 96 streams (lag | own chunk as reference, Eq. 14-15), us:
 //   rows of 128 bytes (bf16), lag  64   277 -> 178 | 284 -> 176        lag 256   209 -> 176 | 230 -> 186
 //   rows of 160 bytes (f16),  lag 100   254 -> 228 | 289 -> 260        rows of 192, lag 128   207 -> 178 | 233 -> 193
-//   rows of 256 bytes (bf16), lag  64   199 -> 179 | 221 -> 174        lag 300   234 -> 212 | 248 -> 244
+//   rows of 256 bytes (bf16), lag  64   199 -> 179 | 221 -> 174        lag 300   235 -> 190 | 250 -> 224
 //   rows of 512 bytes (bf16), lag 128   208 -> 177 | 232 -> 207        lag 256   212 -> 189 | 233 -> 218
 //   rows of 512 bytes (fp32), lag 128   217 -> 170 | 244 -> 174        lag 256   210 -> 178 | 232 -> 195
+//   lag 1024, rows of 128 bytes (bf16)  223 -> 195 | 253 -> 228        of 512 bytes (bf16)  311 -> 248 | 309 -> 256
 #pragma once
 #include "chunk_ops.hpp"
 
