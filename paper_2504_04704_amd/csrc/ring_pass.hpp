@@ -6,9 +6,10 @@
 // filled with the rows of the next chunk at once, across selections, stores and the borders between streams.  A chunk
 // stays in registers until its selection is known and the kept rows are stored from there, so no row is read
 // twice (the streaming kernel in split_pass.hip reads kept rows again, and so does this one where a chunk does not
-// fit: its rows then pass through the ring only).  A compute unit holds 16 wavefronts of up to 128 registers each, as one workgroup or as many as eight: the smallest workgroup whose lanes hold a chunk in eight
-// slices is taken, because the others then have the unit to themselves while one of them selects.  Longer chunks
-// take eight wavefronts of 256 registers, alone on their unit.
+// fit: its rows then pass through the ring only).  A compute unit holds 16 wavefronts of up to 128 registers each, as
+// one workgroup or as many as eight: the smallest workgroup whose lanes hold a chunk in eight slices is taken, because
+// the others then have the unit to themselves while one of them selects.  Longer chunks take eight wavefronts of 256
+// registers, alone on their unit.
 //
 // The scored chunks of a call are cut into equal shares, one per place that the chip has, without regard to where a
 // stream ends: with whole segments of streams 112 streams of 31 chunks left the longest workgroup 9 chunks to read
@@ -44,7 +45,8 @@ __host__ __device__ inline RingLds ring_lds(int D, int esize, int L, int nsl, in
   const int lp = chunk_pad(L);
   l.off_vK = 0;
   l.off_vV = lp * 4;
-  l.off_slot = 2 * lp * 4;                     // nsl = 0: uint32 [k]: the kept rows; else int32 [L]: where the row goes, in bytes from the first kept row of its chunk, or -1
+  // int32 [L]: where the row goes, in bytes from the first kept row of its chunk, or -1; nsl = 0: [k]: the kept rows
+  l.off_slot = 2 * lp * 4;
   l.off_ref = 3 * lp * 4;                      // float [K|V][mn|iv][D], then eight zeros for lanes without channels
   const int full = (D * esize & (D * esize - 1)) == 0 && D * esize >= 64;  // no lane without channels
   l.off_stat = l.off_ref + (4 * D + (full ? 0 : 8)) * 4;  // elements as in the rows: [wave][mn|mx][D]
@@ -635,7 +637,8 @@ inline RingShape ring_hold_shape(int D, int esize, int L) {
 inline RingShape ring_stream_shape(int D, int esize, int L) {
   const int lpr = chunk_lpr(D * esize), rpw = kWave / lpr;
   const int gw = lpr == 4 || (int64_t)L * D * esize < 256 * 1024 ? 4 : 8, nr = ring_slots(0, gw);
-  const bool deep = L - (gw - 1) * rpw > (nr - 2) * gw * rpw;  // its last wavefront has rows in as many steps as slots, in pairs
+  // (its last wavefront has rows in as many steps as slots, in pairs)
+  const bool deep = L - (gw - 1) * rpw > (nr - 2) * gw * rpw;
   return deep && L <= 1024 && ring_lds(D, esize, L, 0, gw).total <= kRingMaxLds ? RingShape{gw, 0} : RingShape{0, 0};
 }
 // Where a chunk in registers takes a compute unit to itself, nothing runs beside its selection, and lanes without rows
