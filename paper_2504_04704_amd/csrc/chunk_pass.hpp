@@ -16,7 +16,11 @@
 
 namespace lagkv {
 
-// NSL: 16-byte row slices a lane holds: chunks of up to NSL * R rows, R = 4 * 64 / LPR per step.
+// NSL: 16-byte row slices a lane holds: chunks of up to NSL * R rows, R = 4 * 64 / LPR per step.  All NSL are asked for
+// in one go (behind a branch of its own every load would wait for the one before it), those past the chunk's end of one
+// row.  So chunks of one or two steps have a kernel of their own: with the six or seven loads too many of the next larger one,
+// 216 streams of 52 chunks of 64 rows of 36 bytes, scores by Eq. 16, took 53.9 us and not 45.9, calls of up to 1024
+// such chunks 3 % longer.
 // PART: rows shorter than LPR slices.
 template <typename ET, int LPR, int NSL, bool PART>
 __global__ void __launch_bounds__(512, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const PassArgs a) {
@@ -169,7 +173,7 @@ hipError_t launch_chunk_t(const PassArgs& a, hipStream_t s) {
   const int rowbytes = a.D * ESIZE, lpr = chunk_lpr(rowbytes);
   const bool part = rowbytes != lpr * 16;
   const int R = chunk_step(lpr), steps = (a.L + R - 1) / R;
-  const int nsl = steps <= 8 ? 8 : steps <= 16 ? 16 : 32;
+  const int nsl = steps <= 2 ? 2 : steps <= 8 ? 8 : steps <= 16 ? 16 : 32;
   const int64_t nblocks = (int64_t)a.B * a.H * (a.nseg + a.edge);
   if (steps > 32 || nblocks <= 0 || nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
   const size_t lds = (size_t)chunk_lds(a.D, a.L).total;
@@ -180,12 +184,16 @@ hipError_t launch_chunk_t(const PassArgs& a, hipStream_t s) {
     else chunk_pass_kernel<ET, LPR, NSL, false><<<grid, block, lds, s>>>(a);                \
     break;
   switch (lpr * 64 + nsl) {
+    LAGKV_CHUNK_CASE(4, 2)
     LAGKV_CHUNK_CASE(4, 8)
+    LAGKV_CHUNK_CASE(8, 2)
     LAGKV_CHUNK_CASE(8, 8)
     LAGKV_CHUNK_CASE(8, 16)
+    LAGKV_CHUNK_CASE(16, 2)
     LAGKV_CHUNK_CASE(16, 8)
     LAGKV_CHUNK_CASE(16, 16)
     LAGKV_CHUNK_CASE(16, 32)
+    LAGKV_CHUNK_CASE(32, 2)
     LAGKV_CHUNK_CASE(32, 8)
     LAGKV_CHUNK_CASE(32, 16)
     LAGKV_CHUNK_CASE(32, 32)

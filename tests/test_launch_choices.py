@@ -195,6 +195,29 @@ def test_several_chunks_per_workgroup_of_the_chunk_kernel(streams, n_s, D, dtype
         assert torch.allclose(out.scores, ref, rtol=4e-6, atol=0)     # (as for partial slices above)
 
 
+# D, dtype, rows of a step of the chunk kernel: whole and partial rows of 64, 128, 256 and 512 bytes
+STEPS = [(16, torch.float32, 64), (9, torch.float32, 64), (64, torch.bfloat16, 32), (50, torch.float16, 32), (128, torch.float16, 16),
+         (100, torch.bfloat16, 16), (128, torch.float32, 8), (250, torch.bfloat16, 8)]
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
+@pytest.mark.parametrize("D,dtype,R", STEPS)
+def test_chunks_of_one_two_and_three_steps(D, dtype, R, variant):
+    """A lag of one row, a row short of a step, one step, one row more, two steps, one row more: the kernel for up to two
+    slices a lane and the one for up to eight, one chunk a workgroup and several."""
+    for streams, n_s in ((3, 3), (280, 4)):
+        for L in (1, R - 1, R, R + 1, 2 * R, 2 * R + 1):
+            S, r = (3, 0.3) if L > 3 else (0, 1.0)
+            T = S + (n_s + 1) * L + L // 2
+            say("steps", streams, D, dtype, L, "variant", variant)
+            K, V = gen(1, streams, T, D, dtype, seed=L)
+            out, _ = run_and_check(K, V, S, L, r, variant=variant, streams=[(0, s) for s in (0, 1, streams - 1)])
+            PU.check_index_invariants(out.idx, T, S, L, out.plan.k, n_s)
+            rows = out.idx.long().unsqueeze(-1).expand(-1, -1, -1, D)
+            assert torch.equal(out.K, K.gather(2, rows)) and torch.equal(out.V, V.gather(2, rows))
+            assert torch.equal(lagkv.score(K, V, S, L, r, variant=variant), out.scores)
+
+
 @pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL, lagkv.SCORE_L2])
 @pytest.mark.parametrize("D,dtype,L", [(100, torch.bfloat16, 60), (100, torch.float16, 128), (33, torch.float32, 250), (66, torch.bfloat16, 400), (80, torch.bfloat16, 300)])
 def test_infinities_and_nan_stay_in_their_streams(D, dtype, L, variant):
