@@ -239,7 +239,7 @@ int lagkv_prefill(const lagkv_params* p, lagkv_cache* cache, const void* K, cons
  * lagkv_launch_hint(0, 0, 0)).
  *   path      LAGKV_PATH_AUTO (the register-resident kernel where it applies, else the
  *             streaming fused kernel, else the three-kernel path; the chunk-at-a-time kernel
- *             in place of the last two, and their ring form in place of any, where it is faster); LAGKV_PATH_FUSED (the
+ *             in place of the last two, and the ring kernel in place of any, where it is faster); LAGKV_PATH_FUSED (the
  *             streaming fused kernel; error LAGKV_ESHAPE when the fused kernels do not
  *             cover the shape); LAGKV_PATH_STAGED (three-kernel path); or
  *             LAGKV_PATH_RESIDENT (the one-shot kernel that keeps a batch of rows in
@@ -273,10 +273,11 @@ int32_t lagkv_launch_hint_ex(int path, int waves, int segments, int order, int s
 
 /*
  * The path lagkv_compress takes for these parameters (launch override included) on a
- * cache of T rows held in 16-byte aligned buffers: LAGKV_PATH_RESIDENT, LAGKV_PATH_FUSED
- * (the streaming one-shot kernel, or for short calls the chunk-at-a-time kernel in its place)
- * or LAGKV_PATH_STAGED (the shapes that need the workspace: the three-kernel path, or the
- * chunk-at-a-time kernel where rows are multiples of 4 bytes).
+ * cache of T rows held in 16-byte aligned buffers: LAGKV_PATH_RESIDENT (shapes of the register-resident
+ * kernel), LAGKV_PATH_FUSED (those of the streaming one-shot kernel) or LAGKV_PATH_STAGED (those that need the
+ * workspace: the three-kernel path).  It depends on the shape alone; by the size of the call the ring kernel may
+ * stand in for any of the three, the chunk-at-a-time kernel for the last two (where rows are multiples of 4
+ * bytes).  lagkv_kernel_for names the kernel itself.
  * Host only.  Returns minus the lagkv_status the call itself would return for parameters
  * it rejects.
  */
@@ -284,8 +285,7 @@ int lagkv_path_for(const lagkv_params* p, int64_t T);
 
 /*
  * Name of the kernel that scores in that call, for benchmarks and profiles that have to name
- * what they time: "hold_pass_kernel", "split_pass_kernel", "chunk_pass_kernel" (either of
- * the last two may be the kernel in namespace lagkv::ring or the one in lagkv) or
+ * what they time: "hold_pass_kernel", "split_pass_kernel", "chunk_pass_kernel", "ring_pass_kernel" or
  * "staged_score_kernel" ("copy_rows_kernel" where nothing is compressed).  Host only; NULL
  * for parameters the call rejects.
  */

@@ -240,7 +240,7 @@ bool use_chunk(const Norm& n, PassArgs& a, bool whole_slices) {
 //                     over its rows twice with nothing else on the compute unit, 1.05 to 1.15 at any size
 //   fp32              up to a chunk a place 1.02 to 1.27, above 0.89 to 1.02
 // (129 to 256 chunks of 2-byte rows, 1.05 to 1.1, are calls for which lagkv_kernel_for's answer has been written down:
-// they stay.)  Lags of 256 and 512 0.82 to 1.05.  Sets a.walks and a.brief where it says yes.
+// they stay.)  Lags of 256 and 512 0.82 to 1.05.  Sets a.walks where it says yes.
 bool ring_over_resident(const Norm& n, int64_t chunks) {
   if (n.L != 128 || n.streams >= 256) return false;
   return n.esize == 2 ? chunks <= 128 || chunks > 256 : chunks <= 512;
@@ -256,21 +256,21 @@ bool use_ring(const Norm& n, PassArgs& a, bool brief) {
   const int64_t places = ring_places(n.D, n.esize, n.L);
   if (!grid_fits(places + most_edge_workgroups(a), ring_threads(n.D, n.esize, n.L))) return false;
   a.walks = chunks < places ? chunks : places;
-  a.brief = brief;
   return true;
 }
-// Where use_chunk says yes and use_ring no.  Of the shapes that use_ring is not asked about (whole_slices false), the
-// ring kernel's form for 4-byte addresses takes those that fit its eight slices (64 streams of 8247 rows of 200
-// bytes, lag 128: 74 us, the chunk kernel 110 us); of those that it leaves here the chunk kernel has the shorter chain
-// (2 streams of 17 chunks of 512 rows of 128 bytes by Eq. 14-15: 14.2 us, the other 17.1 us).
-int launch_chunk(PassArgs& a, const Norm& n, bool whole_slices, hipStream_t s) {
+// The ring kernel's form for rows on 4-byte addresses, in place of the chunk kernel where that takes such rows.  Sets
+// a.walks where it says yes.  (64 streams of 8247 rows of 200 bytes, lag 128: 74 us, the chunk kernel 110 us.)
+bool use_direct(const Norm& n, PassArgs& a) {
   const int64_t chunks = n.streams * a.n_s;
-  if (!whole_slices && n.variant != LAGKV_SCORE_L2 && chunks < (1LL << 31) && direct_supported(n.D, n.esize, n.L, a.st)) {
-    const int64_t places = direct_places(n.D, n.esize, n.L);
-    a.walks = chunks < places ? chunks : places;
-    if (grid_fits(a.walks + most_edge_workgroups(a), direct_threads(n.D, n.esize, n.L)))
-      return launch_direct_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
-  }
+  if (n.variant == LAGKV_SCORE_L2 || chunks >= (1LL << 31) || !direct_supported(n.D, n.esize, n.L, a.st)) return false;
+  const int64_t places = direct_places(n.D, n.esize, n.L);
+  a.walks = chunks < places ? chunks : places;
+  return grid_fits(a.walks + most_edge_workgroups(a), direct_threads(n.D, n.esize, n.L));
+}
+// Where use_chunk says yes and use_ring no.  (Of the whole rows that use_ring leaves here the chunk kernel has the shorter
+// chain: 2 streams of 17 chunks of 512 rows of 128 bytes by Eq. 14-15 14.2 us, the other 17.1 us.)
+int launch_chunk(PassArgs& a, const Norm& n, bool whole_slices, hipStream_t s) {
+  if (!whole_slices && use_direct(n, a)) return launch_direct_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
   return launch_chunk_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
 }
 
@@ -440,7 +440,6 @@ int fill_empty_cache(const Norm& n, lagkv_cache* c, const void* K, const void* V
   if (whole && n.variant != LAGKV_SCORE_L2 && ring_supported(n.D, n.esize, n.L, st) && chunks < (1LL << 31)) {
     const int64_t places = ring_places(n.D, n.esize, n.L);
     a.walks = chunks < places ? chunks : places;
-    a.brief = use_chunk(n, a, true);
     if (grid_fits(a.walks + most_edge_workgroups(a), ring_threads(n.D, n.esize, n.L)))
       rc = launch_ring_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
   } else if (use_chunk(n, a, whole && n.variant == LAGKV_SCORE_L2)) {
@@ -888,8 +887,9 @@ const char* lagkv_kernel_for(const lagkv_params* p, int64_t T) {
   alignas(16) char out[16];  // (a call with outputs; nothing is stored)
   a.K_out = a.V_out = out;
   const bool whole = path != LAGKV_PATH_STAGED;
-  if (use_chunk(n, a, whole)) return "chunk_pass_kernel";
-  if (whole && use_ring(n, a, false)) return "split_pass_kernel";
+  const bool chunk = use_chunk(n, a, whole);
+  if (whole ? use_ring(n, a, chunk) : chunk && use_direct(n, a)) return "ring_pass_kernel";
+  if (chunk) return "chunk_pass_kernel";
   return path == LAGKV_PATH_RESIDENT ? "hold_pass_kernel" : path == LAGKV_PATH_FUSED ? "split_pass_kernel" : "staged_score_kernel";
 }
 

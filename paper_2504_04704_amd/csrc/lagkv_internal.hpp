@@ -35,7 +35,6 @@ struct PassArgs {
   int32_t ddof;
   int32_t variant;
   int64_t walks;       // ring kernel: workgroups that share the scored chunks
-  int32_t brief;       // ... by the name it has in short calls
   int32_t nseg;        // segments each stream is cut into (one-shot kernels)
   int32_t edge;        // workgroups per stream that copy its sink and window rows, after all the others
   int32_t nwaves;      // wavefronts per workgroup (one-shot kernels)

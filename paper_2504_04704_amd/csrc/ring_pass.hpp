@@ -596,18 +596,10 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
   }
 }
 
-// The same under two names, by which lagkv_kernel_for and profiles tell short calls (about a chunk per place) and rows
-// on 4-byte addresses from those that stream.
-namespace ring {
-template <typename ET, int LPR, int NSL, int GW>
-__global__ void __launch_bounds__(GW * 2 * kWave, NSL <= 8 ? 4 : 2) split_pass_kernel(const PassArgs a) {
-  ring_pass<ET, LPR, NSL, GW, false>(a);
-}
 template <typename ET, int LPR, int NSL, int GW, bool DIRECT>
-__global__ void __launch_bounds__(GW * 2 * kWave, NSL <= 8 ? 4 : 2) chunk_pass_kernel(const PassArgs a) {
+__global__ void __launch_bounds__(GW * 2 * kWave, NSL <= 8 ? 4 : 2) ring_pass_kernel(const PassArgs a) {
   ring_pass<ET, LPR, NSL, GW, DIRECT>(a);
 }
-}  // namespace ring
 
 // ------------------------------------------------------------------------ host side
 template <typename K>
@@ -673,8 +665,7 @@ inline RingShape ring_shape(int D, int esize, int L) {
 
 template <typename ET, int LPR, int NSL, int GW>
 hipError_t launch_ring_n(const PassArgs& a, dim3 grid, size_t lds, hipStream_t s) {
-  return a.brief ? launch_ring_one(ring::chunk_pass_kernel<ET, LPR, NSL, GW, false>, a, grid, GW * 2 * kWave, lds, s)
-                 : launch_ring_one(ring::split_pass_kernel<ET, LPR, NSL, GW>, a, grid, GW * 2 * kWave, lds, s);
+  return launch_ring_one(ring_pass_kernel<ET, LPR, NSL, GW, false>, a, grid, GW * 2 * kWave, lds, s);
 }
 template <typename ET, int LPR>
 hipError_t launch_ring_l(const PassArgs& a, const RingShape& f, dim3 grid, size_t lds, hipStream_t s) {
@@ -708,11 +699,11 @@ inline int direct_lds(int D, int esize, int L, int gw) { return ring_lds(D, esiz
 template <typename ET, int LPR>
 hipError_t launch_direct_l(const PassArgs& a, int gw, dim3 grid, size_t lds, hipStream_t s) {
   switch (gw) {
-    case 1: return launch_ring_one(ring::chunk_pass_kernel<ET, LPR, 8, 1, true>, a, grid, 128, lds, s);
-    case 2: return launch_ring_one(ring::chunk_pass_kernel<ET, LPR, 8, 2, true>, a, grid, 256, lds, s);
-    case 4: return launch_ring_one(ring::chunk_pass_kernel<ET, LPR, 8, 4, true>, a, grid, 512, lds, s);
+    case 1: return launch_ring_one(ring_pass_kernel<ET, LPR, 8, 1, true>, a, grid, 128, lds, s);
+    case 2: return launch_ring_one(ring_pass_kernel<ET, LPR, 8, 2, true>, a, grid, 256, lds, s);
+    case 4: return launch_ring_one(ring_pass_kernel<ET, LPR, 8, 4, true>, a, grid, 512, lds, s);
     case 8:
-      if constexpr (LPR >= 8) return launch_ring_one(ring::chunk_pass_kernel<ET, LPR, 8, 8, true>, a, grid, 1024, lds, s);
+      if constexpr (LPR >= 8) return launch_ring_one(ring_pass_kernel<ET, LPR, 8, 8, true>, a, grid, 1024, lds, s);
       break;
     default: break;
   }

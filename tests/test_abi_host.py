@@ -224,9 +224,9 @@ def test_launch_hint_is_a_pure_function(lib):
 
 
 def test_path_for_names_the_kernels_of_a_call(lib):
-    """lagkv_path_for: rows of 256 bytes with a lag of 128, 256 or 512 go to the register-resident
-    kernel (not Eq. 16), other fused shapes to the streaming kernel, the rest to the
-    three-kernel path; hints are honoured or refused as lagkv_compress does."""
+    """lagkv_path_for: rows of 256 bytes with a lag of 128, 256 or 512 are shapes of the register-resident
+    kernel (not Eq. 16), other fused shapes of the streaming kernel, the rest of the
+    three-kernel path, whichever kernel takes a call of theirs by its size; hints are honoured or refused as lagkv_compress does."""
     mk = lagkv.make_params
     T = 16 + 8 * 512
     for L in (128, 256, 512):
@@ -303,26 +303,28 @@ def test_binding_refuses_cpu_tensors():
 
 
 def test_kernel_for_names_the_kernel_that_scores(lib):
-    """lagkv_kernel_for follows the choice of the call: chunk counts against the places of the chunk kernel, slices per
+    """lagkv_kernel_for follows the choice of the call: chunk counts against the places of the kernels, slices per
     lane, Eq. 16, row sizes, hints, and the work items of a grid."""
     def name(streams, D, L, n_s, dtype=lagkv.BF16, variant=lagkv.SCORE_LAG, **kw):
         return lagkv.kernel_for(lagkv.make_params(1, streams, D, 4, L, 1.0, dtype, variant, **kw), 4 + (n_s + 1) * L)
     assert name(8, 128, 128, 20) == name(8, 128, 512, 1) == "hold_pass_kernel"
-    # up to 8 slices a lane: 512 places, two rounds; 16: 256 places, two rounds; more: one
-    assert name(1024, 64, 128, 1) == name(64, 64, 128, 16) == "chunk_pass_kernel"
-    assert name(1025, 64, 128, 1) == "split_pass_kernel"
-    assert name(512, 64, 512, 1) == "chunk_pass_kernel" and name(513, 64, 512, 1) == "split_pass_kernel"
-    assert name(256, 128, 400, 1) == "chunk_pass_kernel" and name(257, 128, 400, 1) == "split_pass_kernel"
-    assert name(1, 128, 513, 1) == "split_pass_kernel"
+    # whole rows: the ring kernel, whatever the number of chunks
+    for streams, D, L, n_s in ((1024, 64, 128, 1), (64, 64, 128, 16), (1025, 64, 128, 1), (512, 64, 512, 1), (513, 64, 512, 1),
+                               (256, 128, 400, 1), (257, 128, 400, 1), (1, 128, 513, 1)):
+        assert name(streams, D, L, n_s) == "ring_pass_kernel"
+    # a chunk that it would go over twice, up to two rounds of the chunk kernel
+    local = dict(variant=lagkv.SCORE_LOCAL)
+    assert name(256, 128, 300, 1, **local) == "chunk_pass_kernel" and name(257, 128, 300, 1, **local) == "ring_pass_kernel"
+    assert name(512, 128, 200, 1, **local) == "chunk_pass_kernel" and name(513, 128, 200, 1, **local) == "ring_pass_kernel"
     # Eq. 16 with outputs: half the places
     assert name(256, 128, 128, 1, variant=lagkv.SCORE_L2) == name(128, 128, 512, 1, variant=lagkv.SCORE_L2) == "chunk_pass_kernel"
     assert name(257, 128, 128, 1, variant=lagkv.SCORE_L2) == name(129, 128, 512, 1, variant=lagkv.SCORE_L2) == "split_pass_kernel"
     # rows that are not whole slices: at any count that fits a grid of 512 threads a workgroup, edge copies included
-    assert name(100000, 100, 128, 1) == "chunk_pass_kernel"
-    assert name((1 << 22) - 1, 5, 2, 1, lagkv.F32) == "chunk_pass_kernel" and name(1 << 22, 5, 2, 1, lagkv.F32) == "staged_score_kernel"
+    assert name(100000, 100, 128, 1) == "ring_pass_kernel" and name(100000, 100, 300, 1) == "chunk_pass_kernel"
+    assert name((1 << 22) - 1, 5, 2, 1, lagkv.F32) == "ring_pass_kernel" and name(1 << 22, 5, 2, 1, lagkv.F32) == "staged_score_kernel"
     assert name(8, 101, 128, 4) == name(8, 300, 128, 4) == name(8, 100, 513, 4) == "staged_score_kernel"
     # strides of 4-byte multiples, and of odd elements
-    assert name(8, 64, 128, 4, strides=(0, 0, 66)) == "chunk_pass_kernel" and name(8, 64, 128, 4, strides=(0, 0, 65)) == "staged_score_kernel"
+    assert name(8, 64, 128, 4, strides=(0, 0, 66)) == "ring_pass_kernel" and name(8, 64, 128, 4, strides=(0, 0, 65)) == "staged_score_kernel"
     # any hint keeps it out
     for hint, want in ((lagkv.launch_hint(lagkv.PATH_FUSED), "split_pass_kernel"), (lagkv.launch_hint(lagkv.PATH_STAGED), "staged_score_kernel"),
                        (lagkv.launch_hint(lagkv.PATH_AUTO, 4), "split_pass_kernel"), (lagkv.launch_hint(lagkv.PATH_AUTO, 0, 3), "split_pass_kernel")):

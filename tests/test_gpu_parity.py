@@ -109,7 +109,7 @@ def test_unaligned_head_dims_on_the_staged_path_and_as_chosen(D, dtype):
         p = lagkv.params_for(K, 8, 50, 0.3, launch=hint(path))
         assert lagkv.workspace_bytes(p, K.shape[2]) > 0
         chunk = path == lagkv.PATH_AUTO and D in (42, 100, 5)   # rows of 16 to 512 bytes, a multiple of 4
-        assert lagkv.kernel_for(p, K.shape[2]) == ("chunk_pass_kernel" if chunk else "staged_score_kernel")
+        assert lagkv.kernel_for(p, K.shape[2]) == ("ring_pass_kernel" if chunk else "staged_score_kernel")
         run_and_check(K, V, 8, 50, 0.3, launch=hint(path))
 
 
