@@ -153,9 +153,12 @@ int split_nw(const Norm& n) {
 // made 6 of 600 shapes 4 to 13 % faster and 4 of them 4 to 7 % slower.  Nor does the cost know of a memory that is
 // saturated already, where one more segment is only one more chunk to read: 456 streams of 9 chunks of 128 rows of
 // 512 bytes, scores alone, three segments 146 us, two 130 us.)
-int pick_segments(int64_t streams, int64_t n_s, int64_t L, int64_t cap, int64_t fixed, int64_t batch,
-                  int64_t per_batch) {
-  int64_t best = 1, best_cost = INT64_MAX;
+struct Cut {
+  int nseg;
+  int64_t chunks, rows;  // of the longest segment; that a place goes through one after another, as above
+};
+Cut pick_cut(int64_t streams, int64_t n_s, int64_t L, int64_t cap, int64_t fixed, int64_t batch, int64_t per_batch) {
+  Cut best = {1, n_s, INT64_MAX};
   const int64_t base = (streams + cap - 1) / cap;  // rounds with whole streams
   for (int64_t rounds = base; rounds < base + 8; ++rounds) {
     int64_t nseg = rounds * cap / streams;
@@ -165,12 +168,13 @@ int pick_segments(int64_t streams, int64_t n_s, int64_t L, int64_t cap, int64_t 
     nseg = (n_s + c - 1) / c;                   // ... which fewer segments may share
     const int64_t waves = (streams * nseg + cap - 1) / cap;
     const int64_t cost = waves * ((c + 1) * L + (c + batch - 1) / batch * per_batch + fixed);
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = nseg;
-    }
+    if (cost < best.rows) best = {(int)nseg, c, cost};
   }
-  return (int)best;
+  return best;
+}
+int pick_segments(int64_t streams, int64_t n_s, int64_t L, int64_t cap, int64_t fixed, int64_t batch,
+                  int64_t per_batch) {
+  return pick_cut(streams, n_s, L, cap, fixed, batch, per_batch).nseg;
 }
 
 int clamp_segments(int64_t nseg, int64_t n_s) { return (int)(nseg > n_s ? n_s : nseg < 1 ? 1 : nseg); }
@@ -184,9 +188,9 @@ int pick_segments_split(const Norm& n, int64_t n_s, int nw) {
 }
 
 // Register-resident kernel: one workgroup per CU, in batches of 512 rows.
+Cut hold_cut(const Norm& n, int64_t n_s) { return pick_cut(n.streams, n_s, n.L, 256, 128, 512 / n.L, 96); }
 int pick_segments_hold(const Norm& n, int64_t n_s) {
-  if (n.hint.nseg) return clamp_segments(n.hint.nseg, n_s);
-  return pick_segments(n.streams, n_s, n.L, 256, 128, 512 / n.L, 96);
+  return n.hint.nseg ? clamp_segments(n.hint.nseg, n_s) : hold_cut(n, n_s).nseg;
 }
 
 // The register-resident kernel is the default wherever it applies (rows of 256 bytes, lags
@@ -232,24 +236,35 @@ bool use_chunk(const Norm& n, PassArgs& a, bool whole_slices) {
   a.nseg = nseg;
   return true;
 }
-// The ring kernel, in place of the streaming kernel, of the chunk kernel (`brief`) and of the register-resident
-// kernel.  The last for lags of 128 where a stream does not have a place to itself (256 streams of 16384 rows equal):
-//   2-byte elements   up to 256 chunks 1.07 to 1.14 (24 streams of 2 chunks 11.2 us against 9.8 us), up to 1.5 chunks
-//                     a place 1.02 to 1.17 (8 streams of 63, 8269 rows of 256 bytes, 19.6 us against 16.8 us), above 0.93
-//                     to 1.14, the better the less evenly whole segments fill the chip; Eq. 14-15, where that kernel goes
-//                     over its rows twice with nothing else on the compute unit, 1.05 to 1.15 at any size
-//   fp32              up to a chunk a place 1.02 to 1.27, above 0.89 to 1.02
-// (129 to 256 chunks of 2-byte rows, 1.05 to 1.1, are calls for which lagkv_kernel_for's answer has been written down:
-// they stay.)  Lags of 256 and 512 0.82 to 1.05.  Sets a.walks where it says yes.
-bool ring_over_resident(const Norm& n, int64_t chunks) {
+// The ring kernel in place of the register-resident kernel, for lags of 128 where a stream does not have a place to itself
+// (256 streams of 16384 rows equal; lags of 256 and 512 0.82 to 1.05).  Its gain, 2554 calls of 1 to 2048 streams:
+//   2-byte elements   up to 512 chunks, about one a place, 1.05 to 1.29 (8 streams of 20 chunks 1.17 in the mean of such);
+//                     scores alone 1.04 to 1.26, Eq. 14-15, where that kernel goes over its rows twice with nothing else
+//                     on the compute unit, 1.05 to 1.28 at any size, both with single calls down to 0.93;
+//                     else by how much longer the other's longest workgroup is than an even share of this one's:
+//                     segments of up to 3 chunks (a batch of four is never full) 1.02 to 1.08, above that less than
+//                     1.2 times the rows 0.98, to 1.25 0.99, to 1.3 1.01, to 1.35 1.03 (all with calls of 0.89 to 0.94
+//                     among them), to 1.4 1.06, to 1.5 1.09, beyond 1.16
+//   fp32              up to 512 chunks 1.04 to 1.16, above 0.94 to 1.05
+// (256 streams and more 1.0 to 1.3 for the same reasons: calls of the other kernel so far, and left to it.)
+bool ring_over_resident(const Norm& n, const PassArgs& a) {
   if (n.L != 128 || n.streams >= 256) return false;
-  return n.esize == 2 ? chunks <= 128 || chunks > 256 : chunks <= 512;
+  const int64_t chunks = n.streams * a.n_s;
+  if (chunks <= 512) return true;
+  if (n.esize == 4) return false;
+  if (n.variant == LAGKV_SCORE_LOCAL || !a.K_out) return true;
+  const Cut cut = hold_cut(n, a.n_s);
+  // two workgroups a compute unit; each reads its share, a first reference and one more for every stream it goes over into
+  const double share = chunks / 512.0, over = n.streams / 512.0;
+  return cut.chunks <= 3 || (double)cut.rows > 1.35 * 256 * (share + 1 + (share < over ? share : over));
 }
+// The ring kernel, in place of that kernel, of the streaming kernel and of the chunk kernel (`brief`).  Sets a.walks where
+// it says yes.
 bool use_ring(const Norm& n, PassArgs& a, bool brief) {
   if (n.hint.path != LAGKV_PATH_AUTO || n.hint.waves || n.hint.nseg || n.hint.order || n.hint.sel) return false;
   const int64_t chunks = n.streams * a.n_s;
   if (n.variant == LAGKV_SCORE_L2 || !ring_supported(n.D, n.esize, n.L, a.st) || chunks >= (1LL << 31)) return false;
-  if (use_resident(n) && !ring_over_resident(n, chunks)) return false;
+  if (use_resident(n) && !ring_over_resident(n, a)) return false;
   if (!ring_pays(n.D, n.esize, n.L)) return false;
   // (Eq. 14-15 goes over a chunk twice there: 4 streams of 8 chunks of 160 rows 12.6 us, the chunk kernel 11.0 us)
   if (brief && n.variant == LAGKV_SCORE_LOCAL && !ring_holds(n.D, n.esize, n.L)) return false;

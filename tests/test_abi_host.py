@@ -307,7 +307,7 @@ def test_kernel_for_names_the_kernel_that_scores(lib):
     lane, Eq. 16, row sizes, hints, and the work items of a grid."""
     def name(streams, D, L, n_s, dtype=lagkv.BF16, variant=lagkv.SCORE_LAG, **kw):
         return lagkv.kernel_for(lagkv.make_params(1, streams, D, 4, L, 1.0, dtype, variant, **kw), 4 + (n_s + 1) * L)
-    assert name(8, 128, 128, 20) == name(8, 128, 512, 1) == "hold_pass_kernel"
+    assert name(8, 128, 512, 1) == "hold_pass_kernel"
     # whole rows: the ring kernel, whatever the number of chunks
     for streams, D, L, n_s in ((1024, 64, 128, 1), (64, 64, 128, 16), (1025, 64, 128, 1), (512, 64, 512, 1), (513, 64, 512, 1),
                                (256, 128, 400, 1), (257, 128, 400, 1), (1, 128, 513, 1)):
@@ -332,3 +332,24 @@ def test_kernel_for_names_the_kernel_that_scores(lib):
     assert name(8, 64, 128, 0) == "copy_rows_kernel"
     with pytest.raises(lagkv.LagKVError):
         name(8, 64, 128, 4, launch=lagkv.launch_hint(lagkv.PATH_RESIDENT))
+
+
+def test_lags_of_128_between_the_resident_and_the_ring_kernel(lib):
+    """The sides of the rule: chunks against the ring kernel's places, whole segments against even shares, 256 streams;
+    lagkv_path_for names the family of the shape on both."""
+    def name(streams, n_s, dtype=lagkv.BF16, variant=lagkv.SCORE_LAG, L=128):
+        p, T = lagkv.make_params(1, streams, 64 if dtype == lagkv.F32 else 128, 4, L, 0.25, dtype, variant), 4 + (n_s + 1) * L
+        assert lagkv.path_for(p, T) == lagkv.PATH_RESIDENT
+        return lagkv.kernel_for(p, T)
+    ring, hold = "ring_pass_kernel", "hold_pass_kernel"
+    for dtype in (lagkv.BF16, lagkv.F16, lagkv.F32):
+        for streams, n_s in ((1, 1), (8, 16), (8, 17), (8, 20), (8, 32), (8, 33), (8, 63), (128, 4), (1, 512)):
+            assert name(streams, n_s, dtype) == ring
+        assert name(255, 2, dtype) == ring and name(256, 2, dtype) == name(256, 200, dtype, lagkv.SCORE_LOCAL) == hold
+        for L in (256, 512):
+            assert name(8, 4, dtype, L=L) == hold
+    assert name(1, 513, lagkv.F32) == name(9, 57, lagkv.F32, lagkv.SCORE_LOCAL) == hold and name(9, 57) == ring
+    # segments of three chunks and of four; longest segments of 1.41 and 1.44, of 1.23 and 1.30 times an even share
+    assert name(1, 768) == ring and name(1, 1000) == hold
+    assert name(70, 26) == name(65, 30) == ring and name(64, 13) == hold and name(117, 249) == hold
+    assert name(64, 13, variant=lagkv.SCORE_LOCAL) == name(117, 249, variant=lagkv.SCORE_LOCAL) == ring
