@@ -501,23 +501,33 @@ def test_single_round_decode_step_repeats_and_without_positions():
     assert torch.equal(without.K[:, :, :n], with_pos.K[:, :, :n]) and torch.equal(without.V[:, :, :n], with_pos.V[:, :, :n])
 
 
+def by_chunks(cache, K, V):
+    """The calls of a prompt that is compressed while it is prefilled - S + 2L rows, then L rows per call (the ablation's
+    chunked prefill) - made one by one, as a server makes them; returns how many."""
+    S, L, T = cache.S, cache.L, K.shape[2]
+    cuts = [0, *range(S + 2 * L, T, L), T] if T > S + 2 * L else [0, T]
+    for a, b in zip(cuts, cuts[1:]):
+        cache.append_and_compress(K[:, :, a:b], V[:, :, a:b])
+    return len(cuts) - 1
+
+
+@pytest.mark.parametrize("fill", [by_chunks, lagkv.Cache.prefill_chunked])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
-def test_prefill_chunk_by_chunk_equals_one_shot(dtype):
-    """S + 2L rows first, then L rows per call (the chunked prefill of the ablation)."""
+def test_prefill_chunk_by_chunk_equals_one_shot(dtype, fill):
+    """The calls one by one, and the one pass that stands for them where all rows are there."""
     S, L, r, D = 16, 64, 0.25, 128
     T = S + 2 * L + 7 * L + 13
     Kh, Vh = gen(2, 2, T, D, dtype, seed=123)
     cache = lagkv.Cache(2, 2, D, T, S, L, r, dtype=dtype)
-    calls = cache.prefill_chunked(Kh, Vh)
+    calls = fill(cache, Kh, Vh)
     torch.cuda.synchronize()
     assert calls == 1 + 8
     oracle_history_check(cache, Kh, Vh, S, L, r)
 
 
-def _prefill_at_scale(cfg, layers, n_sample):
-    """Chunk-by-chunk prefill (S + 2L rows, then one lag per lagkv_append_and_compress call) of
-    `layers` layers of a workload configuration: the final cache against the one-shot oracle on
-    sampled streams, against the one-shot pass on all of them, and both timings."""
+def _prefill_at_scale(cfg, layers, n_sample, fill):
+    """Prefill of `layers` layers of a workload configuration, by the calls or in one pass: the final cache against
+    the one-shot oracle on sampled streams, against the one-shot pass on all of them, and both timings."""
     import time
     sub = cfg.scaled(layers=layers)
     K, V = synth.make_kv(sub, device=DEV)
@@ -525,7 +535,7 @@ def _prefill_at_scale(cfg, layers, n_sample):
     cache = lagkv.Cache(K.shape[0], cfg.H, cfg.D, pl.T_out + 2 * cfg.L, cfg.S, cfg.L, cfg.r)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    calls = cache.prefill_chunked(K, V)
+    calls = fill(cache, K, V)
     torch.cuda.synchronize()
     t_chunked = time.perf_counter() - t0
     assert calls == 1 + -(-(cfg.T - cfg.S - 2 * cfg.L) // cfg.L)
@@ -539,7 +549,7 @@ def _prefill_at_scale(cfg, layers, n_sample):
     gK, gV, gpos = cache.view()
     PU.check_index_invariants(gpos, cfg.T, cfg.S, cfg.L, pl.k, pl.n_scored)
     same = (gpos == one.idx).all(dim=-1)
-    say(f"prefill chunk by chunk, {sub.streams} streams of {cfg.name}: {calls} calls in {t_chunked * 1e3:.1f} ms "
+    say(f"prefill, {fill.__name__}, {sub.streams} streams of {cfg.name}: {calls} calls in {t_chunked * 1e3:.1f} ms "
         f"({cfg.B * cfg.T / t_chunked:.3g} tokens/s per {layers} layers); one-shot pass {t_one * 1e3:.2f} ms; "
         f"{int(same.sum())} of {same.numel()} streams identical to the one-shot pass")
 
@@ -551,24 +561,39 @@ def _prefill_at_scale(cfg, layers, n_sample):
     with ThreadPoolExecutor(8) as ex:
         for r in ex.map(check, synth.stream_sample(sub.streams, n_sample)):
             rep.merge(r)
-    # the recursion and the one-shot pass may differ only where the oracle sees a near-tie
+    # the two may differ only where the oracle sees a near-tie
     assert int((~same).sum()) <= max(2, same.numel() // 16)
     return rep
 
 
-def test_prefill_chunk_by_chunk_at_config2_scale():
-    """All 32 layers of the 16K configuration (256 streams, L = 128): 1 + 126 calls, each the
-    single-round decode kernel."""
-    rep = _prefill_at_scale(synth.CONFIGS["cfg2_llama8b_16k"], 32, 32)
+@pytest.mark.parametrize("fill", [by_chunks, lagkv.Cache.prefill_chunked])
+def test_prefill_chunk_by_chunk_at_config2_scale(fill):
+    """All 32 layers of the 16K configuration (256 streams, L = 128): 1 + 126 calls, each a round in the cache's own
+    buffers on what the last one left there, or one pass that writes them."""
+    rep = _prefill_at_scale(synth.CONFIGS["cfg2_llama8b_16k"], 32, 32, fill)
     assert rep.chunks == 32 * 126
 
 
-def test_prefill_chunk_by_chunk_on_one_layer_of_config4():
-    """One layer of the 128K configuration (B=4 x 8 heads = 32 streams, L = 512): 1 + 254 calls
-    through the general append kernel (a 512-row reference chunk does not fit the LDS of the
-    single-round kernel)."""
-    rep = _prefill_at_scale(synth.CONFIGS["cfg4_llama8b_128k_b4"], 1, 8)
+@pytest.mark.parametrize("fill", [by_chunks, lagkv.Cache.prefill_chunked])
+def test_prefill_chunk_by_chunk_on_one_layer_of_config4(fill):
+    """One layer of the 128K configuration (B=4 x 8 heads = 32 streams, L = 512): 1 + 254 calls, or one pass."""
+    rep = _prefill_at_scale(synth.CONFIGS["cfg4_llama8b_128k_b4"], 1, 8, fill)
     assert rep.chunks == 8 * 254
+
+
+@pytest.mark.parametrize("launch", [lagkv.PATH_FUSED, lagkv.PATH_STAGED])
+def test_long_chains_of_rounds_of_the_other_append_kernels(launch):
+    """1 + 60 calls on what the last one left: decode_step_kernel or fused_append_kernel for whole slices, then the
+    three kernels of the workspace path."""
+    for D, dtype, L in [(128, torch.bfloat16, 128), (128, torch.bfloat16, 512), (64, torch.float32, 100)]:
+        S = 16
+        T = S + 61 * L + 5
+        say("chain of rounds", launch, D, dtype, L)
+        Kh, Vh = gen(1, 2, T, D, dtype, seed=L)
+        cache = lagkv.Cache(1, 2, D, S + 61 * (L // 4) + 2 * L, S, L, 0.25, dtype=dtype, launch=hint(launch))
+        assert by_chunks(cache, Kh, Vh) == 1 + 60
+        torch.cuda.synchronize()
+        oracle_history_check(cache, Kh, Vh, S, L, 0.25)
 
 
 GRID_K = {(128, 0.5): 64, (128, 0.25): 32, (128, 0.167): 21, (128, 0.125): 16,
