@@ -673,12 +673,12 @@ hipError_t launch_ring_l(const PassArgs& a, const RingShape& f, dim3 grid, size_
     case 1 * 64 + 8: return launch_ring_n<ET, LPR, 8, 1>(a, grid, lds, s);
     case 2 * 64 + 8: return launch_ring_n<ET, LPR, 8, 2>(a, grid, lds, s);
     case 4 * 64 + 8: return launch_ring_n<ET, LPR, 8, 4>(a, grid, lds, s);
-    case 8 * 64 + 8:
-      if constexpr (LPR >= 8) return launch_ring_n<ET, LPR, 8, 8>(a, grid, lds, s);
+    case 8 * 64 + 8:  // (2-byte rows of up to 128 bytes: streamed, by ring_hold_pays)
+      if constexpr (LPR >= 16 || (LPR == 8 && ET::VEC == 4)) return launch_ring_n<ET, LPR, 8, 8>(a, grid, lds, s);
       break;
     case 4 * 64: return launch_ring_n<ET, LPR, 0, 4>(a, grid, lds, s);
-    case 8 * 64:
-      if constexpr (LPR >= 8) return launch_ring_n<ET, LPR, 0, 8>(a, grid, lds, s);
+    case 8 * 64:  // (chunks of 256 KiB, at most 1024 rows)
+      if constexpr (LPR >= 16) return launch_ring_n<ET, LPR, 0, 8>(a, grid, lds, s);
       break;
     case 4 * 64 + 32:
       if constexpr (LPR >= 16) return launch_ring_n<ET, LPR, 32, 4>(a, grid, lds, s);

@@ -1,6 +1,8 @@
 """GPU: the kernel that holds a chunk in registers while the next one's rows arrive through an LDS ring, at the sizes
 where it can go wrong: every workgroup size, chunks at and around what its lanes hold, shares that go over from one
 stream into the next, lanes and wavefronts without rows of their own."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -10,29 +12,51 @@ from tests.test_gpu_parity import gen, run_and_check, say
 
 pytestmark = pytest.mark.gpu
 
-# streams, scored chunks, D, dtype, L.  A wavefront takes 1 KiB of rows a step, a lane 8 slices (32 in the last ones).
-SHAPES = [
-    # two wavefronts: rows of 64 bytes, of 48 (a lane in four without channels); one chunk more than places; lag of one row
-    (9, 300, 32, torch.bfloat16, 64), (700, 3, 24, torch.float16, 100), (2049, 1, 16, torch.float32, 128), (64, 40, 32, torch.bfloat16, 1),
-    # four: 17 rows in steps of 8, a step and a row short of full, full
-    (300, 5, 128, torch.bfloat16, 33), (70, 16, 80, torch.float16, 63), (41, 27, 96, torch.bfloat16, 64), (33, 70, 64, torch.float32, 57),
-    # eight: wavefronts with fewer steps than others, one stream in many shares, many in one
-    (1, 1300, 80, torch.float16, 100), (520, 3, 256, torch.bfloat16, 57), (150, 7, 64, torch.bfloat16, 129), (17, 70, 128, torch.float32, 64),
-    # sixteen: just over eight, full
-    (100, 6, 128, torch.float32, 65), (37, 15, 64, torch.float32, 225), (29, 20, 256, torch.bfloat16, 128), (40, 13, 64, torch.float16, 512),
-    # 32 slices: 26 and an odd number of steps, all, nearly all
-    (40, 8, 128, torch.bfloat16, 409), (12, 23, 256, torch.float16, 256), (23, 12, 128, torch.float32, 249), (300, 2, 128, torch.float16, 500),
-    # chunks that pass through the ring only: eight wavefronts, six slots - the fewest steps, an odd number, rows of 64 bytes, the
-    # longest chunk of 2-byte rows below 512 KiB - and sixteen, eight slots
-    (60, 9, 128, torch.float16, 129), (30, 20, 80, torch.bfloat16, 300), (23, 31, 64, torch.bfloat16, 450), (5, 9, 24, torch.bfloat16, 513),
-    (31, 9, 128, torch.bfloat16, 1023), (300, 2, 96, torch.float16, 700), (11, 9, 128, torch.bfloat16, 1024), (3, 12, 128, torch.float32, 513), (9, 5, 256, torch.float16, 1000),
-]
+BF, F16, F32 = torch.bfloat16, torch.float16, torch.float32
+# streams, scored chunks, D, dtype, L: by the kernel that serves them - wavefronts per tensor and slices a lane holds (0: chunks
+# that pass through the ring only) - for rows of up to 64, 128, 256 and 512 bytes.  A wavefront takes 1 KiB of rows a step.
+SHAPES = {
+    # rows of 64 bytes, of 48 (a lane in four without channels); one chunk more than places; lag of one row
+    (1, 8): [(9, 300, 32, BF, 64), (700, 3, 24, F16, 100), (2049, 1, 16, F32, 128), (64, 40, 32, BF, 1), (50, 40, 64, BF, 63), (300, 9, 28, F32, 50),
+             (70, 30, 128, F16, 32), (90, 20, 40, F32, 31), (40, 50, 256, BF, 16), (300, 7, 128, F32, 15)],
+    # 17 rows in steps of 8, a step and a row short of full, full
+    (2, 8): [(300, 5, 128, BF, 33), (70, 16, 80, F16, 63), (41, 27, 96, BF, 64), (33, 70, 64, F32, 57), (90, 12, 24, BF, 129), (37, 15, 16, F32, 256),
+             (200, 7, 64, F16, 65), (33, 31, 32, F32, 128), (75, 17, 256, F16, 17), (23, 60, 100, F32, 32)],
+    # wavefronts with fewer steps than others, one stream in many shares, many in one
+    (4, 8): [(1, 1300, 80, F16, 100), (520, 3, 256, BF, 57), (150, 7, 64, BF, 129), (17, 70, 128, F32, 64), (70, 9, 32, F16, 500), (31, 19, 16, F32, 257),
+             (45, 13, 24, F32, 256), (19, 40, 64, F32, 65)],
+    # just over eight wavefronts, full
+    (8, 8): [(100, 6, 128, F32, 65), (37, 15, 64, F32, 225), (29, 20, 256, BF, 128), (21, 17, 128, F16, 185), (33, 11, 128, BF, 255), (17, 23, 32, F32, 257),
+             (27, 9, 24, F32, 512)],
+    # 26 and an odd number of steps, all, nearly all
+    (4, 32): [(40, 8, 128, BF, 409), (12, 23, 256, F16, 256), (23, 12, 128, F32, 249), (300, 2, 128, F16, 500), (29, 11, 48, F32, 384), (9, 31, 64, F32, 511)],
+    # six slots: the fewest steps, an odd number, rows of 64 bytes, the longest chunk of 2-byte rows below 512 KiB
+    (4, 0): [(60, 9, 128, F16, 129), (30, 20, 80, BF, 300), (23, 31, 64, BF, 450), (40, 13, 64, F16, 512), (5, 9, 24, BF, 513), (31, 9, 128, BF, 1023),
+             (300, 2, 96, F16, 700), (70, 13, 256, BF, 135), (11, 17, 256, F16, 511), (9, 11, 16, F32, 1024), (21, 9, 32, F32, 513), (33, 12, 40, F32, 257),
+             (7, 9, 64, F32, 1023), (15, 20, 68, F32, 129), (17, 7, 128, F32, 511)],
+    # eight slots
+    (8, 0): [(11, 9, 128, BF, 1024), (3, 12, 128, F32, 513), (9, 5, 256, F16, 1000), (13, 7, 64, F32, 1024), (21, 5, 136, BF, 964)],
+}
+
+
+def form(D, esize, L):
+    """The library's own choice."""
+    lib = lagkv.load()
+    lib._ZN5lagkv10ring_holdsEiii.restype = C.c_bool
+    waves, holds = lib._ZN5lagkv12ring_threadsEiii(D, esize, L) // 128, lib._ZN5lagkv10ring_holdsEiii(D, esize, L)
+    lanes = max(4, 1 << (-(-D * esize // 16) - 1).bit_length())  # of a row
+    return waves, 0 if not holds else 8 if L <= 8 * waves * (64 // lanes) else 32
+
+
+def flat(shapes):
+    return [(*x, f) for f, xs in shapes.items() for x in xs]
 
 
 @pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL])
-@pytest.mark.parametrize("streams,n_s,D,dtype,L", SHAPES)
-def test_shapes_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, variant):
-    say("ring", streams, n_s, D, dtype, L, "variant", variant)
+@pytest.mark.parametrize("streams,n_s,D,dtype,L,kind", flat(SHAPES))
+def test_shapes_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, kind, variant):
+    say("ring", streams, n_s, D, dtype, L, kind, "variant", variant)
+    assert kind is None or form(D, dtype.itemsize, L) == kind
     S, r = (3, 0.3) if L > 3 else (0, 1.0)
     T = S + (n_s + 1) * L + L // 3
     K, V = gen(1, streams, T, D, dtype, seed=streams + L)
@@ -65,7 +89,7 @@ PARTIAL = [
 @pytest.mark.parametrize("streams,n_s,D,dtype,L", PARTIAL)
 def test_partial_slices_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, variant):
     assert D * dtype.itemsize % 4 == 0
-    test_shapes_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, variant)
+    test_shapes_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, None, variant)
 
 
 @pytest.mark.parametrize("D,dtype,L", [(64, torch.bfloat16, 64), (128, torch.bfloat16, 100), (128, torch.float32, 128), (128, torch.float16, 300), (64, torch.bfloat16, 900)])
