@@ -43,7 +43,7 @@ def _run(cmd, verbose):
     if verbose and out:
         print(out, flush=True)
     if proc.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({proc.returncode})\n{out}")
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed ({proc.returncode})\n{out}")
 
 
 def build_library(verbose: bool = True, extra_flags=(), out_path: str = LIB_PATH, sources=SOURCES) -> str:
@@ -63,18 +63,18 @@ def build_library(verbose: bool = True, extra_flags=(), out_path: str = LIB_PATH
 
 
 def build_binding(verbose: bool = True, out_path: str = BINDING_PATH) -> str:
-    """Compile csrc/binding.cpp (host code only, against torch's headers) into
-    paper_2504_04704_amd/_lagkv_native.so; returns its path."""
+    """Compile csrc/binding.cpp (host code only, against torch's headers) into paper_2504_04704_amd/_lagkv_native.so, with
+    g++ or, where there is none, the clang that hipcc drives; returns its path."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension
-    cxx = shutil.which("g++") or shutil.which("c++")
-    if cxx is None:
-        raise RuntimeError("g++ not found")
-    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    cxx = [shutil.which("g++") or shutil.which("c++")]
+    if cxx[0] is None:
+        cxx = [hipcc_path(), "-x", "c++"]
+    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], os.path.join(ROOT, "include"), CSRC]
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    _run([cxx, "-O2", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    _run([*cxx, "-O2", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
           *(x for i in inc for x in ("-isystem", i)), os.path.join(CSRC, "binding.cpp"), "-o", out_path + ".tmp",
           "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python", f"-Wl,-rpath,{lib}"], verbose)
     os.replace(out_path + ".tmp", out_path)

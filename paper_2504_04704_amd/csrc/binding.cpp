@@ -4,7 +4,7 @@
 // decode whose kernel takes 3 us.
 //
 // It takes the plain forms only (exact tensors of one device, four dimensions, integers and floats as such).  Anything
-// else - and whatever the library refuses or an allocator throws - it leaves alone and says so (None, or -1): lagkv.py
+// else - and what lagkv_plan refuses or an allocator throws - it leaves alone and says so (None, or -1): lagkv.py
 // then goes through its own steps, which raise what they raise.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -12,6 +12,7 @@
 #include <ATen/ops/empty.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include "compress_ws.h"
 #include "lagkv.h"
 
 namespace {
@@ -85,7 +86,8 @@ PyObject* none() {
 }
 
 // compress(K, V, S, L, r, variant, std_ddof, launch, want_idx, want_scores)
-//   -> (K_out, V_out, idx or None, scores or None, bytes of the plan), or None
+//   -> (K_out, V_out, idx or None, scores or None, bytes of the plan), the status that lagkv_compress refused with (it is
+//      not called a second time), or None: not called
 PyObject* compress(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   if (nargs != 10 || !PyBool_Check(args[8]) || !PyBool_Check(args[9])) return none();
   try {
@@ -103,8 +105,8 @@ PyObject* compress(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     if (args[8] == Py_True) idx = at::empty({B, H, pl.T_out}, opt.dtype(at::kInt));
     if (args[9] == Py_True) scores = at::empty({B, H, pl.n_scored * p.L}, opt.dtype(at::kFloat));
     size_t need = 0;
-    if (workspace_fn(&p, T)) {  // (scores and kept positions: what lagkv_compress needs of it)
-      for (const int64_t n : {(int64_t)p.L, pl.k}) need += ((size_t)4 * B * H * pl.n_scored * n + 255) / 256 * 256;
+    if (workspace_fn(&p, T)) {
+      need = lagkv::compress_ws(B * H, pl.n_scored, p.L, pl.k, true).total;
       ws = at::empty({(int64_t)need}, opt.dtype(at::kByte));
     }
     const void *k = K->data_ptr(), *v = V->data_ptr();
@@ -115,7 +117,7 @@ PyObject* compress(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     Py_BEGIN_ALLOW_THREADS
     rc = compress_fn(&p, k, v, T, ko, vo, ip, sp, w, need, stream);
     Py_END_ALLOW_THREADS
-    if (rc != LAGKV_OK) return none();
+    if (rc != LAGKV_OK) return PyLong_FromLong(rc);
     PyObject* out = PyTuple_New(5);
     if (!out) return nullptr;
     auto put = [&](int i, const at::Tensor& t) {

@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstring>
 
+#include "compress_ws.h"
 #include "lagkv_internal.hpp"
 
 using namespace lagkv;
@@ -32,9 +33,6 @@ bool parse_hint(int32_t v, Hint* h) {
 }
 
 constexpr int64_t kMaxRows = 0x7fffffffLL;  // positions are int32
-constexpr size_t kAlign = 256;
-
-size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Norm {  // validated, normalised parameters
   int B, H, D, S, L, k, esize, f16, ddof, variant;
@@ -358,17 +356,9 @@ bool round_is_faster(const Norm& n, const AppendArgs& a, int64_t tail) {
   return !step && slices <= 16 && n.variant != LAGKV_SCORE_L2 && n.streams >= 512 && n.rowbytes * n.L >= 48 * 1024;
 }
 
-// Workspace of the three-kernel path for one pass: [scores][kept]
-struct StagedWs {
-  size_t off_scores, off_kept, total;
-};
-StagedWs staged_ws(const Norm& n, int64_t n_s, bool need_scores) {
-  StagedWs w;
-  w.off_scores = 0;
-  const size_t sc = need_scores ? align_up((size_t)n.streams * n_s * n.L * 4) : 0;
-  w.off_kept = sc;
-  w.total = sc + align_up((size_t)n.streams * n_s * n.k * 4);
-  return w;
+// Workspace of the three-kernel path for one pass
+CompressWs staged_ws(const Norm& n, int64_t n_s, bool need_scores) {
+  return compress_ws(n.streams, n_s, n.L, n.k, need_scores);
 }
 
 // Workspace of the three-kernel append: [scores][kept][stage K][stage V][stage pos]
@@ -379,15 +369,15 @@ AppendWs append_ws(const Norm& n, int64_t q, int64_t rows_staged) {
   AppendWs w;
   size_t o = 0;
   w.off_scores = o;
-  o += align_up((size_t)n.streams * q * n.L * 4);
+  o += ws_align_up((size_t)n.streams * q * n.L * 4);
   w.off_kept = o;
-  o += align_up((size_t)n.streams * q * n.k * 4);
+  o += ws_align_up((size_t)n.streams * q * n.k * 4);
   w.off_k = o;
-  o += align_up((size_t)n.streams * rows_staged * n.rowbytes);
+  o += ws_align_up((size_t)n.streams * rows_staged * n.rowbytes);
   w.off_v = o;
-  o += align_up((size_t)n.streams * rows_staged * n.rowbytes);
+  o += ws_align_up((size_t)n.streams * rows_staged * n.rowbytes);
   w.off_pos = o;
-  o += align_up((size_t)n.streams * rows_staged * 4);
+  o += ws_align_up((size_t)n.streams * rows_staged * 4);
   w.total = o;
   return w;
 }
@@ -629,7 +619,7 @@ int lagkv::compress_with_workspace(const lagkv_params* p, const void* K, const v
   if ((force == LAGKV_PATH_FUSED || force == LAGKV_PATH_RESIDENT) && !fused_ok) return LAGKV_ESHAPE;
   if (fused_ok && force != LAGKV_PATH_STAGED) return launch_fused_any(a, n, s);
   if (!staged_fits(n)) return LAGKV_ESHAPE;
-  const StagedWs w = staged_ws(n, pl.n_scored, scores_out == nullptr);
+  const CompressWs w = staged_ws(n, pl.n_scored, scores_out == nullptr);
   const bool chunk = use_chunk(n, a, false);
   if (!(chunk && told_none(n, sb, sh, st)) && (!ws || ws_bytes < w.total || !aligned_to(ws, 16)))
     return LAGKV_EWORKSPACE;

@@ -10,7 +10,9 @@ from __future__ import annotations
 
 import ctypes as C
 import functools
+import importlib
 import os
+import warnings
 from dataclasses import dataclass
 from operator import index
 from typing import Optional, Tuple
@@ -118,14 +120,20 @@ def load():
 
 
 def _load_native(lib):
-    try:
-        from . import _lagkv_native
-    except ImportError:
+    """csrc/binding.cpp's module, set up; None where it is not built, or with a torch that has no devices to call it on."""
+    raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw_stream is None:
         return None
-    _lagkv_native.init(*(C.cast(f, C.c_void_p).value for f in (lib.lagkv_plan, lib.lagkv_workspace_bytes, lib.lagkv_compress,
-                                                              lib.lagkv_append_and_compress)),
-                       torch._C._cuda_getCurrentRawStream)
-    return _lagkv_native
+    try:
+        native = importlib.import_module("._lagkv_native", __package__)
+    except ModuleNotFoundError:
+        return None
+    except ImportError as e:  # built for another torch or Python
+        warnings.warn(f"_lagkv_native.so does not load and calls go through ctypes, some microseconds more each: {e}", RuntimeWarning)
+        return None
+    native.init(*(C.cast(f, C.c_void_p).value for f in (lib.lagkv_plan, lib.lagkv_workspace_bytes, lib.lagkv_compress,
+                                                        lib.lagkv_append_and_compress)), raw_stream)
+    return native
 
 
 def strerror(status: int) -> str:
@@ -301,6 +309,8 @@ def compress(K: torch.Tensor, V: torch.Tensor, S: int, L: int, r: float, variant
     """lagkv_compress: one whole pass.  Output buffers may be passed in (benchmarks)."""
     if _native is not None and out is None and idx_out is None and scores_out is None and ws is None:
         got = _native.compress(K, V, S, L, r, variant, std_ddof, launch, want_idx, want_scores)
+        if isinstance(got, int):
+            raise LagKVError(got, "lagkv_compress")
         if got is not None:
             return Compressed(got[0], got[1], got[2], got[3], PlanT.from_buffer_copy(got[4]))
     if not K.is_cuda:

@@ -1,12 +1,14 @@
 """The native part of the binding against the ctypes calls it stands in front of: the same results, counters and exceptions
 whichever of the two takes a call."""
 import ctypes as C
+import importlib.util
+import warnings
 
 import numpy as np
 import pytest
 import torch
 
-from paper_2504_04704_amd import lagkv
+from paper_2504_04704_amd import build, lagkv
 
 
 def native():
@@ -23,6 +25,52 @@ def test_forms_that_are_not_plain_are_left_alone():
     assert n.append(lagkv.CacheT(), x, 1, 8, 0.5, 0, 1, 0, None, None, None) == -1 and n.append() == -1
     with pytest.raises(RuntimeError):
         lagkv.compress(x, x, 1, 8, 0.5)
+
+
+def test_a_call_that_was_refused_is_not_made_again(monkeypatch):
+    class Refuses:
+        calls = 0
+
+        def compress(self, *args):
+            self.calls += 1
+            return lagkv.EHIP
+
+    native()
+    monkeypatch.setattr(lagkv, "_native", Refuses())
+    monkeypatch.setattr(lagkv, "_prepare", lambda *a: pytest.fail("the ctypes steps"))
+    x = torch.zeros(1, 2, 64, 8)
+    with pytest.raises(lagkv.LagKVError) as e:
+        lagkv.compress(x, x, 1, 8, 0.5)
+    assert e.value.status == lagkv.EHIP and "lagkv_compress" in str(e.value) and lagkv._native.calls == 1
+
+
+def test_a_module_that_does_not_load_is_told_of(monkeypatch):
+    """A missing one is not: everything runs through ctypes then.  Nor is a torch without devices one that fails to load."""
+    lib = lagkv.load()
+
+    def fails(with_):
+        def f(*a):
+            raise with_
+        monkeypatch.setattr(lagkv.importlib, "import_module", f)
+
+    fails(ImportError("undefined symbol"))
+    with pytest.warns(RuntimeWarning, match="undefined symbol"):
+        assert lagkv._load_native(lib) is None
+    fails(ModuleNotFoundError("No module named '_lagkv_native'"))
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        assert lagkv._load_native(lib) is None
+        monkeypatch.undo()
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+        assert lagkv._load_native(lib) is None
+
+
+def test_it_builds_without_gcc(monkeypatch, tmp_path):
+    which = build.shutil.which
+    monkeypatch.setattr(build.shutil, "which", lambda name: None if name in ("g++", "c++") else which(name))
+    out = build.build_binding(verbose=False, out_path=str(tmp_path / "_lagkv_native.so"))
+    spec = importlib.util.spec_from_file_location("_lagkv_native", out)
+    assert importlib.util.module_from_spec(spec).compress() is None
 
 
 class Sub(torch.Tensor):
@@ -70,6 +118,29 @@ def test_compress_is_the_same_either_way(monkeypatch):
             m.setattr(lagkv, "_native", None)
             want = outcome(lambda: fields(lagkv.compress(*args, **kw)))
         assert equal(got, want), (n, got, want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D,S,L,r", [(25, 3, 64, 0.25), (50, 0, 100, 0.33), (300, 16, 128, 0.5), (64, 2, 50, 0.02)])
+def test_the_workspace_of_a_call_is_what_it_asks_for(monkeypatch, D, S, L, r):
+    """The size that both ways allocate is the library's own: it takes that and refuses a byte less."""
+    launch = lagkv.launch_hint(lagkv.PATH_STAGED)
+    for B, T in ((1, S + 2 * L), (3, S + 7 * L + 11)):
+        x = torch.randn(B, 2, T, D, device="cuda").half()
+        p = lagkv.params_for(x, S, L, r, launch=launch)
+        need = lagkv._compress_bytes(p, T, lagkv.plan(p, T))
+        print("[gpu-test] binding, workspace", D, B, T, need, flush=True)
+        lagkv.compress(x, x, S, L, r, launch=launch, ws=torch.empty(need, dtype=torch.uint8, device="cuda"))
+        with pytest.raises(lagkv.LagKVError) as e:
+            lagkv.compress(x, x, S, L, r, launch=launch, ws=torch.empty(need - 1, dtype=torch.uint8, device="cuda"))
+        assert e.value.status == lagkv.EWORKSPACE
+        assert isinstance(native().compress(x, x, S, L, r, 0, 1, launch, True, False), tuple)
+        with monkeypatch.context() as m:  # what the library refuses, the native step says itself
+            m.setattr(lagkv, "_prepare", lambda *a: pytest.fail("the ctypes steps"))
+            with pytest.raises(lagkv.LagKVError) as e:
+                lagkv.compress(x, x, S, L, r, launch=lagkv.launch_hint(lagkv.PATH_RESIDENT))
+            assert e.value.status == lagkv.ESHAPE
+    torch.cuda.synchronize()
 
 
 @pytest.mark.gpu
