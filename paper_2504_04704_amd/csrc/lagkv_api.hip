@@ -237,20 +237,22 @@ bool use_chunk(const Norm& n, PassArgs& a, bool whole_slices) {
 // The ring kernel in place of the register-resident kernel, for lags of 128 where a stream does not have a place to itself
 // (256 streams of 16384 rows equal; lags of 256 and 512 0.82 to 1.05).  Its gain, 2554 calls of 1 to 2048 streams:
 //   2-byte elements   up to 512 chunks, about one a place, 1.05 to 1.29 (8 streams of 20 chunks 1.17 in the mean of such);
-//                     scores alone 1.04 to 1.26, Eq. 14-15, where that kernel goes over its rows twice with nothing else
-//                     on the compute unit, 1.05 to 1.28 at any size, both with single calls down to 0.93;
+//                     Eq. 14-15, where that kernel goes over its rows twice with nothing else on the compute unit, 1.05
+//                     to 1.28 at any size, with single calls down to 0.93;
 //                     else by how much longer the other's longest workgroup is than an even share of this one's:
 //                     segments of up to 3 chunks (a batch of four is never full) 1.02 to 1.08, above that less than
 //                     1.2 times the rows 0.98, to 1.25 0.99, to 1.3 1.01, to 1.35 1.03 (all with calls of 0.89 to 0.94
 //                     among them), to 1.4 1.06, to 1.5 1.09, beyond 1.16
 //   fp32              up to 512 chunks 1.04 to 1.16, above 0.94 to 1.05
-// (256 streams and more 1.0 to 1.3 for the same reasons: calls of the other kernel so far, and left to it.)
+// (256 streams and more 1.0 to 1.3 for the same reasons: calls of the other kernel so far, and left to it.)  Whether kept rows are
+// stored or only scores asked for makes no difference to the rules of Eq. 7-8 and 14-15: lagkv_score gives the scores
+// that lagkv_compress selects by, to the bit.
 bool ring_over_resident(const Norm& n, const PassArgs& a) {
   if (n.L != 128 || n.streams >= 256) return false;
   const int64_t chunks = n.streams * a.n_s;
   if (chunks <= 512) return true;
   if (n.esize == 4) return false;
-  if (n.variant == LAGKV_SCORE_LOCAL || !a.K_out) return true;
+  if (n.variant == LAGKV_SCORE_LOCAL) return true;
   const Cut cut = hold_cut(n, a.n_s);
   // two workgroups a compute unit; each reads its share, a first reference and one more for every stream it goes over into
   const double share = chunks / 512.0, over = n.streams / 512.0;

@@ -92,6 +92,28 @@ def test_partial_slices_and_shares_against_the_staged_path(streams, n_s, D, dtyp
     test_shapes_and_shares_against_the_staged_path(streams, n_s, D, dtype, L, None, variant)
 
 
+# both sides of the rules between the resident, the chunk and the ring kernel
+CHOICES = [
+    (64, 13, 128, BF, 128), (9, 57, 128, BF, 128), (70, 26, 128, F16, 128), (117, 20, 128, BF, 128), (1, 513, 64, F32, 128), (255, 2, 128, BF, 128),
+    (8, 1, 64, BF, 49), (8, 1, 64, BF, 48), (256, 1, 64, F16, 64), (64, 1, 256, BF, 64), (65, 1, 256, BF, 64), (4, 15, 128, F32, 128), (3, 3, 64, F16, 512),
+    (256, 1, 50, BF, 64), (257, 1, 50, BF, 64), (40, 6, 18, BF, 300), (512, 1, 50, BF, 129), (4, 60, 100, BF, 49),
+]
+
+
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL])
+@pytest.mark.parametrize("streams,n_s,D,dtype,L", CHOICES)
+def test_scores_alone_are_those_of_the_pass(streams, n_s, D, dtype, L, variant):
+    """... to the bit, so that lagkv_select on them keeps what lagkv_compress keeps."""
+    say("ring, scores alone", streams, n_s, D, dtype, L, "variant", variant)
+    S, T = 3, 3 + (n_s + 1) * L + 5
+    K, V = gen(1, streams, T, D, dtype, seed=streams + D)
+    out, _ = run_and_check(K, V, S, L, 0.25, variant=variant, streams=[(0, 0), (0, streams - 1)])
+    scores = lagkv.score(K, V, S, L, 0.25, variant=variant)
+    assert torch.equal(scores, out.scores)
+    kept = lagkv.select(scores, T, S, L, 0.25)
+    assert torch.equal(kept.flatten(2), out.idx[:, :, S:S + n_s * out.plan.k])
+
+
 @pytest.mark.parametrize("D,dtype,L", [(64, torch.bfloat16, 64), (128, torch.bfloat16, 100), (128, torch.float32, 128), (128, torch.float16, 300), (64, torch.bfloat16, 900)])
 def test_equal_scores_infinities_and_nan(D, dtype, L):
     """Equal tokens across the edge of the kept set go to the lower positions; a stream with infinities or NaN keeps k
