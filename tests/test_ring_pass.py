@@ -114,6 +114,31 @@ def test_scores_alone_are_those_of_the_pass(streams, n_s, D, dtype, L, variant):
     assert torch.equal(kept.flatten(2), out.idx[:, :, S:S + n_s * out.plan.k])
 
 
+@pytest.mark.parametrize("variant", [lagkv.SCORE_LAG, lagkv.SCORE_LOCAL])
+def test_the_error_of_scores_of_long_lags(variant):
+    """Against 64 bits, 2-norms.  A score is the sum of two products of an exponential and a reciprocal, each rounded to
+    2^-24 of itself at worst; an exponential's own error, that of a standard deviation of order one, is as large.  What a
+    chunk's denominator is off by comes on top for all of its tokens, so it may not be off by more than its rounding:
+    4.2e-8 in the mean of these shapes then, 4.5e-8 and more with its last additions in 32 bits."""
+    errs = []
+    for D, dtype, L in [(128, BF, 329), (16, F32, 334), (32, BF, 386), (160, BF, 274), (256, F16, 277), (128, F32, 250), (64, F16, 512),
+                        (128, BF, 1000), (64, F32, 700), (128, F16, 200), (80, F16, 450), (96, BF, 600)]:
+        streams, n_s, S = 70, 12, 2
+        T = S + (n_s + 1) * L
+        say("ring, error", D, dtype, L, "variant", variant)
+        K, V = gen(1, streams, T, D, dtype, seed=L)
+        assert lagkv.kernel_for(lagkv.params_for(K, S, L, 0.25, variant), T) == "ring_pass_kernel"
+        got = lagkv.score(K, V, S, L, 0.25, variant=variant).double()
+        want = 0
+        for x in (K, V):
+            x = x.double()[:, :, S:].reshape(1, streams, n_s + 1, L, D)
+            own, ref = x[:, :, :-1], x[:, :, 1:] if variant == lagkv.SCORE_LAG else x[:, :, :-1]
+            mn, mx = ref.amin(3, keepdim=True), ref.amax(3, keepdim=True)
+            want = want + torch.softmax(((own - mn) / (mx - mn)).std(-1), -1)
+        errs.append(float((got - want.flatten(2)).norm() / want.norm()))
+    assert sum(errs) / len(errs) <= 4.2e-8 and max(errs) <= 5e-8, errs
+
+
 @pytest.mark.parametrize("D,dtype,L", [(64, torch.bfloat16, 64), (128, torch.bfloat16, 100), (128, torch.float32, 128), (128, torch.float16, 300), (64, torch.bfloat16, 900)])
 def test_equal_scores_infinities_and_nan(D, dtype, L):
     """Equal tokens across the edge of the kept set go to the lower positions; a stream with infinities or NaN keeps k
