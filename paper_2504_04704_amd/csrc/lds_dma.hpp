@@ -132,16 +132,25 @@ __device__ __forceinline__ void dma_rows16(uint32_t lane_off, const char* sbase,
         : "memory");
 }
 // ... at a compile-time byte offset from lds_addr
-template <int OFF>
+template <int OFF, bool NT>
 __device__ __forceinline__ void dma_rows16_at(uint32_t lane_off, const char* sbase, uint32_t lds_addr) {
   uint64_t base;
-  asm volatile(
-      "s_add_u32 m0, %3, %4\n\t"
-      "s_mov_b64 %0, %2\n\t"
-      "global_load_lds_dwordx4 %1, %0 " LAGKV_DMA16_FLAGS
-      : "=&s"(base)
-      : "v"(lane_off), "s"(sbase), "s"(lds_addr), "n"(OFF)
-      : "memory", "scc");
+  if constexpr (NT)
+    asm volatile(
+        "s_add_u32 m0, %3, %4\n\t"
+        "s_mov_b64 %0, %2\n\t"
+        "global_load_lds_dwordx4 %1, %0 " LAGKV_DMA16_FLAGS
+        : "=&s"(base)
+        : "v"(lane_off), "s"(sbase), "s"(lds_addr), "n"(OFF)
+        : "memory", "scc");
+  else
+    asm volatile(
+        "s_add_u32 m0, %3, %4\n\t"
+        "s_mov_b64 %0, %2\n\t"
+        "global_load_lds_dwordx4 %1, %0"
+        : "=&s"(base)
+        : "v"(lane_off), "s"(sbase), "s"(lds_addr), "n"(OFF)
+        : "memory", "scc");
 }
 
 // Stores like st16_out (not known to the compiler) with a wave-uniform base and a 32-bit lane

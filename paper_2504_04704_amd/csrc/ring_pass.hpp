@@ -336,12 +336,13 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
   // Where the chunk does not stay in registers, its own statistics (Eq. 14-15) are an item before it.
   bool ref = !HOLD || !local;
   const char* cur = chunk_at(stream, p + (local ? 0 : 1));
-  auto dma = [&](const char* base, auto tag) __attribute__((always_inline)) {
+  auto dma = [&](const char* base, auto tag, auto keep) __attribute__((always_inline)) {
     constexpr int j = decltype(tag)::value;
-    const uint32_t off = lane_off + (uint32_t)(j * R) * st;
-    if constexpr (HOLD) dma_rows16_at<(j % NR) * 1024>(off < lane_max ? off : lane_max, base, ring_base);
-    else dma_rows16<false>(off < lane_max ? off : lane_max, base, ring_base + (j % NR) * 1024u);
+    const uint32_t off = lane_off + (uint32_t)(j * R) * st, at = off < lane_max ? off : lane_max;
+    if constexpr (HOLD) dma_rows16_at<(j % NR) * 1024, !decltype(keep)::value>(at, base, ring_base);
+    else dma_rows16<false>(at, base, ring_base + (j % NR) * 1024u);
   };
+  constexpr std::false_type once{};
   uint4 hold[HOLD ? NSL : 1], ahead[DIRECT ? NSL : 1];
   // (All slices in one go, without a branch: behind one, the compiler waits for the loads before it.  Steps this
   // wavefront does not have, and with `rows` 1 the whole of it, repeat one row.)
@@ -355,9 +356,16 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
     load(ahead, cur, L);
     load(hold, ref ? cur - (int64_t)L * a.st : cur, L);
   } else {
-    ring_for<0, NR, 1>([&](auto tag) __attribute__((always_inline)) {
-      if (decltype(tag)::value < n) dma(cur, tag);
-    });
+    auto fill = [&](auto keep) __attribute__((always_inline)) {
+      ring_for<0, NR, 1>([&](auto tag) __attribute__((always_inline)) {
+        if (decltype(tag)::value < n) dma(cur, tag, keep);
+      });
+    };
+    // The chunk behind the scored ones, which the workgroups that copy the window read too, stays in the caches for them
+    // (388 streams of one chunk of 64 rows of 512 bytes 23.3 us, loaded like the others 28.6 us; asked about at every later turn as
+    // well, the code of twice the loads cost calls of 6 us 0.35 us).
+    if (HOLD && gather && !local && p == (int)n_s - 1) fill(std::true_type{});
+    else fill(once);
   }
   if (tid < 8 && rowbytes < LPR * 16) refbuf[4 * D + tid] = 0.f;
   if constexpr (HOLD)
@@ -504,17 +512,17 @@ __device__ __forceinline__ void ring_pass(const PassArgs& a) {
       if constexpr (DIRECT) {
       } else if constexpr (NSL == 8) {
         if (j < n && more) {
-          dma(next, tag);
-          dma(next, std::integral_constant<int, j + 1>{});
+          dma(next, tag, once);
+          dma(next, std::integral_constant<int, j + 1>{}, once);
         }
       } else if constexpr (j < 16) {
         if (j + 16 < n) {
-          dma(cur, std::integral_constant<int, j + 16>{});
-          dma(cur, std::integral_constant<int, j + 17>{});
+          dma(cur, std::integral_constant<int, j + 16>{}, once);
+          dma(cur, std::integral_constant<int, j + 17>{}, once);
         }
       } else if (more) {
-        dma(next, std::integral_constant<int, j - 16>{});
-        dma(next, std::integral_constant<int, j - 15>{});
+        dma(next, std::integral_constant<int, j - 16>{}, once);
+        dma(next, std::integral_constant<int, j - 15>{}, once);
       }
       if (j < n) {
         float x0[VEC], x1[VEC];
