@@ -258,32 +258,62 @@ bool ring_over_resident(const Norm& n, const PassArgs& a) {
   const double share = chunks / 512.0, over = n.streams / 512.0;
   return cut.chunks <= 3 || (double)cut.rows > 1.35 * 256 * (share + 1 + (share < over ? share : over));
 }
-// The ring kernel, in place of that kernel, of the streaming kernel and of the chunk kernel (`brief`).  Sets a.walks where
-// it says yes.
+// The ring kernel in place of the chunk kernel, for the short calls that use_chunk takes.  A call of at most a chunk a
+// compute unit is as long as one workgroup, and the chunk kernel's is the shorter one where its eight wavefronts share the
+// seven or eight steps that the ring kernel gives two, and for rows that fill their lanes and steps that fill them (elsewhere
+// the ring kernel has the fewer instructions).  The chunk kernel over the ring kernel, compressions | scores alone,
+// means of 3000 random calls of 1 to 1100 chunks (all the others 0.91 | 0.88):
+//   two wavefronts                up to 64 chunks 1.04 to 1.22, 1.12 | 1.04   to 256 chunks 0.96 to 1.20, 1.08 | 0.98
+//                                 (8 chunks of 64 rows of 128 bytes 6.1 us, 7.1 us)
+//   full rows, four, Eq. 14-15    up to 64 chunks 1.01 | 0.93                 to 256 chunks 1.01 to 1.11, 1.05 | 0.94
+//   eight, Eq. 14-15              up to 64 chunks 0.86 to 1.15, 1.05 | 0.99   to 256 chunks 0.98 to 1.16, 1.07 | 0.96
+//          (more steps)           up to 64 chunks 1.02 to 1.12, 1.04 | 0.99   to 256 chunks 0.92 to 1.12, 1.00 | 0.90
+//          Eq. 7-8, 2 bytes       up to 64 chunks 0.95 to 1.18, 1.07 | 1.01   (fp32 0.98 | 0.93; above, all 0.97 | 0.89)
+//   sixteen                       0.99 | 0.99
+bool ring_over_chunk(const Norm& n, const PassArgs& a) {
+  const bool local = n.variant == LAGKV_SCORE_LOCAL;
+  if (local && !ring_holds(n.D, n.esize, n.L)) return false;  // (a chunk gone over twice: 12.6 us, 11.0 us)
+  const int64_t chunks = n.streams * a.n_s;
+  const int waves = ring_threads(n.D, n.esize, n.L) / 128;  // of each tensor
+  const int steps = ring_steps(n.D, n.esize, n.L, waves);
+  if (steps < 7 || chunks > 256 || waves > 4) return true;
+  if (waves == 1) return false;
+  if (n.rowbytes < 64 || (n.rowbytes & (n.rowbytes - 1)) != 0) return true;  // lanes without channels
+  if (chunks <= 64) return waves == 2 || (!local && n.esize == 4);
+  return !local || steps > 8;
+}
+// The ring kernel, in place of the resident, of the streaming and of the chunk kernel (`brief`).  Sets a.walks where
+// it says yes.  (Streaming kernel: 1.29 in the mean of 2012 calls of 300 to 8000 chunks, 57 of them below 0.97, the least
+// 0.83: Eq. 14-15 with rows of 512 bytes and one to four chunks a place.)
 bool use_ring(const Norm& n, PassArgs& a, bool brief) {
   if (n.hint.path != LAGKV_PATH_AUTO || n.hint.waves || n.hint.nseg || n.hint.order || n.hint.sel) return false;
   const int64_t chunks = n.streams * a.n_s;
   if (n.variant == LAGKV_SCORE_L2 || !ring_supported(n.D, n.esize, n.L, a.st) || chunks >= (1LL << 31)) return false;
   if (use_resident(n) && !ring_over_resident(n, a)) return false;
-  if (!ring_pays(n.D, n.esize, n.L)) return false;
-  // (Eq. 14-15 goes over a chunk twice there: 4 streams of 8 chunks of 160 rows 12.6 us, the chunk kernel 11.0 us)
-  if (brief && n.variant == LAGKV_SCORE_LOCAL && !ring_holds(n.D, n.esize, n.L)) return false;
+  if (!ring_pays(n.D, n.esize, n.L) || (brief && !ring_over_chunk(n, a))) return false;
   const int64_t places = ring_places(n.D, n.esize, n.L);
   if (!grid_fits(places + most_edge_workgroups(a), ring_threads(n.D, n.esize, n.L))) return false;
   a.walks = chunks < places ? chunks : places;
   return true;
 }
 // The ring kernel's form for rows on 4-byte addresses, in place of the chunk kernel where that takes such rows.  Sets
-// a.walks where it says yes.  (64 streams of 8247 rows of 200 bytes, lag 128: 74 us, the chunk kernel 110 us.)
+// a.walks where it says yes.  (64 streams of 8247 rows of 200 bytes, lag 128: 74 us, the chunk kernel 110 us.)  Its gain, 998
+// calls of 1 to 4000 chunks, 1.17 in the mean of those it takes, 4 of them below 0.97; not taken, for the reasons above:
+//   Eq. 14-15, eight wavefronts and more   up to 512 chunks 0.84 to 1.10 (195 streams of one of 512 rows of 56 bytes: 0.84)
+//   lags above 256                         up to 256 chunks 0.88 to 1.08
+//   seven or eight steps                   up to 256 chunks, two wavefronts 0.89 to 1.13, four (Eq. 14-15) 0.93 to 1.10
 bool use_direct(const Norm& n, PassArgs& a) {
   const int64_t chunks = n.streams * a.n_s;
   if (n.variant == LAGKV_SCORE_L2 || chunks >= (1LL << 31) || !direct_supported(n.D, n.esize, n.L, a.st)) return false;
+  const int waves = direct_threads(n.D, n.esize, n.L) / 128;
+  const bool local = n.variant == LAGKV_SCORE_LOCAL;
+  if (chunks <= 512 && local && waves >= 4) return false;
+  if (chunks <= 256 && (n.L > 256 || ((local || waves == 1) && ring_steps(n.D, n.esize, n.L, waves) >= 7))) return false;
   const int64_t places = direct_places(n.D, n.esize, n.L);
   a.walks = chunks < places ? chunks : places;
   return grid_fits(a.walks + most_edge_workgroups(a), direct_threads(n.D, n.esize, n.L));
 }
-// Where use_chunk says yes and use_ring no.  (Of the whole rows that use_ring leaves here the chunk kernel has the shorter
-// chain: 2 streams of 17 chunks of 512 rows of 128 bytes by Eq. 14-15 14.2 us, the other 17.1 us.)
+// Where use_chunk says yes and use_ring no.
 int launch_chunk(PassArgs& a, const Norm& n, bool whole_slices, hipStream_t s) {
   if (!whole_slices && use_direct(n, a)) return launch_direct_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;
   return launch_chunk_pass(a, s) == hipSuccess ? LAGKV_OK : LAGKV_EHIP;

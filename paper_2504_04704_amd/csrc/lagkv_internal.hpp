@@ -139,6 +139,7 @@ bool ring_pays(int D, int esize, int L);
 bool ring_holds(int D, int esize, int L);
 int ring_places(int D, int esize, int L);
 int ring_threads(int D, int esize, int L);
+int ring_steps(int D, int esize, int L, int waves);  // of a chunk, by this many wavefronts per tensor
 hipError_t launch_ring_pass(const PassArgs& a, hipStream_t s);
 hipError_t launch_ring_f32(const PassArgs& a, hipStream_t s);
 hipError_t launch_ring_bf16(const PassArgs& a, hipStream_t s);

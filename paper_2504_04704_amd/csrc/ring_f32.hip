@@ -18,6 +18,11 @@ bool ring_holds(int D, int esize, int L) { return ring_shape(D, esize, L).nsl !=
 
 int ring_threads(int D, int esize, int L) { return ring_shape(D, esize, L).gw * 2 * kWave; }
 
+int ring_steps(int D, int esize, int L, int waves) {
+  const int rows = waves * (kWave / chunk_lpr(D * esize));
+  return (L + rows - 1) / rows;
+}
+
 int ring_places(int D, int esize, int L) {
   const RingShape f = ring_shape(D, esize, L);
   const int lds = kRingMaxLds / ring_lds(D, esize, L, f.nsl, f.gw).total, regs = (f.nsl == 32 ? 8 : 16) / (2 * f.gw);

@@ -353,3 +353,30 @@ def test_lags_of_128_between_the_resident_and_the_ring_kernel(lib):
     assert name(1, 768) == ring and name(1, 1000) == hold
     assert name(70, 26) == name(65, 30) == ring and name(64, 13) == hold and name(117, 249) == hold
     assert name(64, 13, variant=lagkv.SCORE_LOCAL) == name(117, 249, variant=lagkv.SCORE_LOCAL) == ring
+
+
+def test_short_calls_between_the_chunk_and_the_ring_kernel(lib):
+    """The sides of the rules: chunks, wavefronts, steps, rows that fill their lanes or not, partial slices.  The variant
+    decides with them, what is asked for (scores, rows) does not: one name serves lagkv_score and lagkv_compress."""
+    def name(streams, D, L, n_s, dtype=lagkv.BF16, variant=lagkv.SCORE_LAG):
+        return lagkv.kernel_for(lagkv.make_params(1, streams, D, 4, L, 1.0, dtype, variant), 4 + (n_s + 1) * L)
+    ring, chunk, local = "ring_pass_kernel", "chunk_pass_kernel", lagkv.SCORE_LOCAL
+    # two wavefronts: steps of 8 rows of 128 bytes, of 4 rows of 208
+    assert name(8, 64, 48, 1) == name(8, 104, 24, 32) == name(257, 64, 64, 1) == ring
+    assert name(8, 64, 49, 1) == name(8, 104, 25, 32) == name(256, 64, 64, 1) == name(8, 64, 64, 32, variant=local) == chunk
+    # four: Eq. 14-15 of full rows and steps, above 64 chunks
+    assert name(65, 64, 128, 1) == name(65, 56, 128, 1, variant=local) == name(65, 64, 96, 1, variant=local) == ring
+    assert name(64, 64, 128, 1, variant=local) == name(257, 64, 128, 1, variant=local) == ring
+    assert name(65, 64, 97, 1, variant=local) == name(256, 64, 128, 1, variant=local) == chunk
+    # eight, and chunks that pass through or take 32 slices: full rows and steps, 2-byte elements with Eq. 7-8
+    for D, L, dtype in ((64, 193, lagkv.BF16), (256, 64, lagkv.F16), (64, 512, lagkv.F16), (256, 256, lagkv.BF16)):
+        assert name(64, D, L, 1, dtype) == chunk and name(65, D, L, 1, dtype) == name(64, D - 8, L, 1, dtype) == ring
+    assert name(64, 64, 192, 1) == name(64, 32, 256, 1, lagkv.F32) == name(1, 128, 513, 1) == ring
+    assert name(64, 32, 256, 1, lagkv.F32, local) == name(256, 64, 256, 1, variant=local) == name(64, 256, 256, 1, variant=local) == chunk
+    assert name(257, 64, 256, 1, variant=local) == name(65, 256, 256, 1, variant=local) == ring
+    # sixteen
+    assert name(8, 256, 128, 1) == name(8, 128, 128, 1, lagkv.F32, local) == ring
+    # partial slices
+    assert name(1, 100, 128, 1) == name(512, 50, 129, 2, variant=local) == name(257, 18, 300, 1) == name(257, 50, 64, 1) == ring
+    assert name(512, 50, 129, 1, variant=local) == name(256, 18, 300, 1) == name(256, 50, 64, 1) == name(4, 100, 49, 64, variant=local) == chunk
+    assert name(1, 50, 48, 1) == name(4, 100, 49, 64) == name(257, 100, 49, 1, variant=local) == ring
