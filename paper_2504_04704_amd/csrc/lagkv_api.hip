@@ -266,20 +266,27 @@ bool ring_over_resident(const Norm& n, const PassArgs& a) {
 //   two wavefronts                up to 64 chunks 1.04 to 1.22, 1.12 | 1.04   to 256 chunks 0.96 to 1.20, 1.08 | 0.98
 //                                 (8 chunks of 64 rows of 128 bytes 6.1 us, 7.1 us)
 //   full rows, four, Eq. 14-15    up to 64 chunks 1.01 | 0.93                 to 256 chunks 1.01 to 1.11, 1.05 | 0.94
+//          (eight steps)          up to 64 chunks, rows of 64 and 256 bytes 1.03 to 1.08, 1.05 | 0.93, of 128 0.99 | 0.93
 //   eight, Eq. 14-15              up to 64 chunks 0.86 to 1.15, 1.05 | 0.99   to 256 chunks 0.98 to 1.16, 1.07 | 0.96
 //          (more steps)           up to 64 chunks 1.02 to 1.12, 1.04 | 0.99   to 256 chunks 0.92 to 1.12, 1.00 | 0.90
 //          Eq. 7-8, 2 bytes       up to 64 chunks 0.95 to 1.18, 1.07 | 1.01   (fp32 0.98 | 0.93; above, all 0.97 | 0.89)
 //   sixteen                       0.99 | 0.99
+// Lags above 256 in eight slices are searched by one wavefront with eight keys a lane, in the chunk kernel by four: rows of up to
+// 128 bytes, up to 256 chunks, inputs in the caches | in memory, means of 600 calls: Eq. 14-15 1.13 | 1.05 (scores alone
+// 1.02 | 0.94), Eq. 7-8 1.11 | 0.96 (1.00 | 0.83); 257 to 512 chunks 0.98 | 0.94 (0.93 | 0.86).  33 streams of one chunk of 512
+// rows of 64 bytes, in the caches: 9.8 us before the ring kernel, 11.7 us with it.
 bool ring_over_chunk(const Norm& n, const PassArgs& a) {
   const bool local = n.variant == LAGKV_SCORE_LOCAL;
   if (local && !ring_holds(n.D, n.esize, n.L)) return false;  // (a chunk gone over twice: 12.6 us, 11.0 us)
   const int64_t chunks = n.streams * a.n_s;
   const int waves = ring_threads(n.D, n.esize, n.L) / 128;  // of each tensor
   const int steps = ring_steps(n.D, n.esize, n.L, waves);
-  if (steps < 7 || chunks > 256 || waves > 4) return true;
+  if (chunks > 256) return true;
+  if (n.L > 256 && steps <= 8 && ring_holds(n.D, n.esize, n.L)) return false;
+  if (steps < 7 || waves > 4) return true;
   if (waves == 1) return false;
   if (n.rowbytes < 64 || (n.rowbytes & (n.rowbytes - 1)) != 0) return true;  // lanes without channels
-  if (chunks <= 64) return waves == 2 || (!local && n.esize == 4);
+  if (chunks <= 64) return waves == 2 ? !local || (n.rowbytes != 64 && n.rowbytes != 256) : !local && n.esize == 4;
   return !local || steps > 8;
 }
 // The ring kernel, in place of the resident, of the streaming and of the chunk kernel (`brief`).  Sets a.walks where
@@ -292,7 +299,6 @@ bool use_ring(const Norm& n, PassArgs& a, bool brief) {
   if (use_resident(n) && !ring_over_resident(n, a)) return false;
   if (!ring_pays(n.D, n.esize, n.L) || (brief && !ring_over_chunk(n, a))) return false;
   const int64_t places = ring_places(n.D, n.esize, n.L);
-  if (!grid_fits(places + most_edge_workgroups(a), ring_threads(n.D, n.esize, n.L))) return false;
   a.walks = chunks < places ? chunks : places;
   return true;
 }

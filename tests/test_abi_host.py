@@ -367,6 +367,7 @@ def test_short_calls_between_the_chunk_and_the_ring_kernel(lib):
     # four: Eq. 14-15 of full rows and steps, above 64 chunks
     assert name(65, 64, 128, 1) == name(65, 56, 128, 1, variant=local) == name(65, 64, 96, 1, variant=local) == ring
     assert name(64, 64, 128, 1, variant=local) == name(257, 64, 128, 1, variant=local) == ring
+    assert name(64, 128, 64, 1, variant=local) == name(8, 32, 256, 2, variant=local) == chunk and name(64, 128, 64, 1) == ring
     assert name(65, 64, 97, 1, variant=local) == name(256, 64, 128, 1, variant=local) == chunk
     # eight, and chunks that pass through or take 32 slices: full rows and steps, 2-byte elements with Eq. 7-8
     for D, L, dtype in ((64, 193, lagkv.BF16), (256, 64, lagkv.F16), (64, 512, lagkv.F16), (256, 256, lagkv.BF16)):
@@ -374,6 +375,11 @@ def test_short_calls_between_the_chunk_and_the_ring_kernel(lib):
     assert name(64, 64, 192, 1) == name(64, 32, 256, 1, lagkv.F32) == name(1, 128, 513, 1) == ring
     assert name(64, 32, 256, 1, lagkv.F32, local) == name(256, 64, 256, 1, variant=local) == name(64, 256, 256, 1, variant=local) == chunk
     assert name(257, 64, 256, 1, variant=local) == name(65, 256, 256, 1, variant=local) == ring
+    # lags above 256 in eight slices
+    for D, L, dtype in ((32, 257, lagkv.BF16), (16, 512, lagkv.F32), (28, 300, lagkv.F32)):
+        assert name(256, D, L, 1, dtype) == name(8, D, L, 32, dtype, local) == chunk
+        assert name(257, D, L, 1, dtype) == name(257, D, L, 1, dtype, local) == ring
+    assert name(8, 48, 256, 1, lagkv.F32) == name(8, 96, 257, 1) == ring
     # sixteen
     assert name(8, 256, 128, 1) == name(8, 128, 128, 1, lagkv.F32, local) == ring
     # partial slices

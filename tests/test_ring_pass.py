@@ -27,7 +27,7 @@ SHAPES = {
              (45, 13, 24, F32, 256), (19, 40, 64, F32, 65)],
     # just over eight wavefronts, full
     (8, 8): [(100, 6, 128, F32, 65), (37, 15, 64, F32, 225), (29, 20, 256, BF, 128), (21, 17, 128, F16, 185), (33, 11, 128, BF, 255), (17, 23, 32, F32, 257),
-             (27, 9, 24, F32, 512)],
+             (30, 9, 24, F32, 512)],
     # 26 and an odd number of steps, all, nearly all
     (4, 32): [(40, 8, 128, BF, 409), (12, 23, 256, F16, 256), (23, 12, 128, F32, 249), (300, 2, 128, F16, 500), (29, 11, 48, F32, 384), (9, 31, 64, F32, 511)],
     # six slots: the fewest steps, an odd number, rows of 64 bytes, the longest chunk of 2-byte rows below 512 KiB
@@ -96,7 +96,7 @@ def test_partial_slices_and_shares_against_the_staged_path(streams, n_s, D, dtyp
 CHOICES = [
     (64, 13, 128, BF, 128), (9, 57, 128, BF, 128), (70, 26, 128, F16, 128), (117, 20, 128, BF, 128), (1, 513, 64, F32, 128), (255, 2, 128, BF, 128),
     (8, 1, 64, BF, 49), (8, 1, 64, BF, 48), (256, 1, 64, F16, 64), (64, 1, 256, BF, 64), (65, 1, 256, BF, 64), (4, 15, 128, F32, 128), (3, 3, 64, F16, 512),
-    (256, 1, 50, BF, 64), (257, 1, 50, BF, 64), (40, 6, 18, BF, 300), (512, 1, 50, BF, 129), (4, 60, 100, BF, 49),
+    (256, 1, 50, BF, 64), (257, 1, 50, BF, 64), (33, 1, 16, F32, 512), (257, 1, 16, F32, 257), (256, 1, 32, F16, 300), (64, 1, 128, BF, 64), (40, 6, 18, BF, 300), (512, 1, 50, BF, 129), (4, 60, 100, BF, 49),
 ]
 
 
