@@ -291,7 +291,7 @@ bool ring_over_chunk(const Norm& n, const PassArgs& a) {
 }
 // The ring kernel, in place of the resident, of the streaming and of the chunk kernel (`brief`).  Sets a.walks where
 // it says yes.  (Streaming kernel: 1.29 in the mean of 2012 calls of 300 to 8000 chunks, 57 of them below 0.97, the least
-// 0.83: Eq. 14-15 with rows of 512 bytes and one to four chunks a place.)
+// 0.83, most of which the rule for Eq. 14-15 below leaves to it.)
 bool use_ring(const Norm& n, PassArgs& a, bool brief) {
   if (n.hint.path != LAGKV_PATH_AUTO || n.hint.waves || n.hint.nseg || n.hint.order || n.hint.sel) return false;
   const int64_t chunks = n.streams * a.n_s;
@@ -299,6 +299,11 @@ bool use_ring(const Norm& n, PassArgs& a, bool brief) {
   if (use_resident(n) && !ring_over_resident(n, a)) return false;
   if (!ring_pays(n.D, n.esize, n.L) || (brief && !ring_over_chunk(n, a))) return false;
   const int64_t places = ring_places(n.D, n.esize, n.L);
+  // Eq. 14-15 streamed by a workgroup a compute unit, some of them two chunks and more of them one: where a place has 1 to 1.6
+  // chunks, inputs in the caches | in memory, 0.95 (least 0.86) | 1.01, of 48 calls; with more 1.03 | 1.05
+  if (n.variant == LAGKV_SCORE_LOCAL && places == 256 && chunks > places && 5 * chunks <= 8 * places &&
+      !ring_holds(n.D, n.esize, n.L))
+    return false;
   a.walks = chunks < places ? chunks : places;
   return true;
 }

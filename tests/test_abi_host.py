@@ -380,6 +380,9 @@ def test_short_calls_between_the_chunk_and_the_ring_kernel(lib):
         assert name(256, D, L, 1, dtype) == name(8, D, L, 32, dtype, local) == chunk
         assert name(257, D, L, 1, dtype) == name(257, D, L, 1, dtype, local) == ring
     assert name(8, 48, 256, 1, lagkv.F32) == name(8, 96, 257, 1) == ring
+    # streamed by sixteen: more than a chunk a place
+    assert name(257, 128, 1024, 1) == name(256, 128, 1024, 1, variant=local) == name(410, 128, 1024, 1, variant=local) == ring
+    assert name(257, 128, 1024, 1, variant=local) == name(409, 128, 1024, 1, variant=local) == "split_pass_kernel"
     # sixteen
     assert name(8, 256, 128, 1) == name(8, 128, 128, 1, lagkv.F32, local) == ring
     # partial slices

@@ -96,7 +96,7 @@ def test_partial_slices_and_shares_against_the_staged_path(streams, n_s, D, dtyp
 CHOICES = [
     (64, 13, 128, BF, 128), (9, 57, 128, BF, 128), (70, 26, 128, F16, 128), (117, 20, 128, BF, 128), (1, 513, 64, F32, 128), (255, 2, 128, BF, 128),
     (8, 1, 64, BF, 49), (8, 1, 64, BF, 48), (256, 1, 64, F16, 64), (64, 1, 256, BF, 64), (65, 1, 256, BF, 64), (4, 15, 128, F32, 128), (3, 3, 64, F16, 512),
-    (256, 1, 50, BF, 64), (257, 1, 50, BF, 64), (33, 1, 16, F32, 512), (257, 1, 16, F32, 257), (256, 1, 32, F16, 300), (64, 1, 128, BF, 64), (40, 6, 18, BF, 300), (512, 1, 50, BF, 129), (4, 60, 100, BF, 49),
+    (256, 1, 50, BF, 64), (257, 1, 50, BF, 64), (33, 1, 16, F32, 512), (257, 1, 16, F32, 257), (256, 1, 32, F16, 300), (4, 75, 64, F32, 1024), (64, 1, 128, BF, 64), (40, 6, 18, BF, 300), (512, 1, 50, BF, 129), (4, 60, 100, BF, 49),
 ]
 
 
